@@ -4,7 +4,9 @@
 // 1/sqrt(hd) scale and a max-subtracted softmax (online form: running max and
 // running sum, rescaled as new keys arrive).
 //
-// bf16 path, head_dim 64 or 128: one workgroup of NW waves per (row, KV
+// bf16 path, head_dim 64 or 128, prefill: k_attn_prefill (128 query columns x 64 keys, K/V through LDS).
+//
+// bf16 path, head_dim 64 or 128, decode: one workgroup of NW waves per (row, KV
 // head), covering the whole context.  All query heads of the KV head's group
 // ride in one MFMA (up to 16 heads): with the scores computed transposed,
 // S^T = K Q^T (16 tokens x 16 heads per v_mfma_f32_16x16x32_bf16 step over
@@ -240,7 +242,7 @@ constexpr int kQkvBatch = 8;       // of which the first this many are loaded wi
 constexpr int kMaxTableBlocks = 16384;
 
 struct AttnQKV {
-  const float* part;  // NULL: q is read from the q buffer and the cache already holds the current token
+  const float* part;
   int splits;
   const float* rope_cos;
   const float* rope_sin;
@@ -256,28 +258,25 @@ struct AttnQKV {
 // the partials of a single group are held (fewer registers, more workgroups per CU); else up to 16 query
 // heads per KV head.  QBX: QKV split partials loaded with the block table (0: kQkvBatch, half for ONE); the
 // launch takes 4 when the QKV projection has at most 4 splits, so no loads are spent on surplus partials.
-template <int HD, int NW, int DR, bool FQ, bool SPLIT = false, bool ONE = false, int QBX = 0>
+template <int HD, int NW, int DR, bool SPLIT = false, bool ONE = false, int QBX = 0>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ONE && NW == 4 ? 3 : 1)))
-void k_attn_mfma(Dims D, const uint16_t* __restrict__ q,
-                                                       uint16_t* __restrict__ kv, int n_blocks,
-                                                       const int32_t* __restrict__ tables, int max_blocks, RowMap rm,
-                                                       int R, int layer, AttnQKV Q, uint16_t* __restrict__ out,
-                                                       int32_t* __restrict__ err) {
+void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t* __restrict__ tables, int max_blocks,
+                 RowMap rm, int R, int layer, AttnQKV Q, uint16_t* __restrict__ out, int32_t* __restrict__ err) {
   constexpr int KC = HD / 32;  // QK^T k-steps
   constexpr int DT = HD / 16;  // P.V output tiles
   constexpr int NT = NW * 64;
   __shared__ float s_m[NW][16], s_l[NW][16];
   __shared__ float s_o[NW][16][HD + 4];
-  __shared__ __align__(16) uint16_t s_q[FQ ? 16 : 1][HD];
-  __shared__ float s_kv[FQ ? 2 : 1][HD];  // current token's k (rotated) and v, bf16 values
-  __shared__ __align__(16) float s_raw[FQ ? 18 : 1][HD];  // split sums: q heads, then k, then v
-  __shared__ float s_rope[FQ ? HD : 1];                   // cos (first half), sin (second half) at pos
+  __shared__ __align__(16) uint16_t s_q[16][HD];
+  __shared__ float s_kv[2][HD];  // current token's k (rotated) and v, bf16 values
+  __shared__ __align__(16) float s_raw[18][HD];  // split sums: q heads, then k, then v
+  __shared__ float s_rope[HD];                   // cos (first half), sin (second half) at pos
   __shared__ float s_cur[16];             // current token's scaled score per head
   extern __shared__ int s_tab[];          // the sequence's block table (dynamic, max_blocks entries)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // XCD-aware order (workgroup b runs on XCD b % 8, and the grid is a multiple of 8): each XCD takes a
-  // contiguous range of (row, KV head) items, so the rows of one group (or one prompt) -- which read the
-  // same prompt KV blocks -- fetch them into one L2 instead of all eight
+  // contiguous range of (row, KV head) items, so the rows of one group -- which read the same prompt KV
+  // blocks -- fetch them into one L2 instead of all eight
   const int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
   if (item >= R * D.nkv) return;
   const int kvh = item % D.nkv;
@@ -293,12 +292,7 @@ void k_attn_mfma(Dims D, const uint16_t* __restrict__ q,
   const size_t block_stride = (size_t)D.nkv * kv_head_stride;
   const int32_t* trow = tables + (size_t)seq * max_blocks;
   const float scale = 1.0f / sqrtf((float)HD);
-  bf16x8_t zero8;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) zero8[e] = (__bf16)0.0f;
-
-  int t_end = pos + 1;  // keys read from the cache
-  if constexpr (FQ) t_end = pos;
+  const int t_end = pos;  // keys read from the cache
   // One round trip for the block table, the row's rotary factors and the first QB QKV split
   // partials of this thread's column groups (float4 groups; every load in flight at once).  The table
   // goes to LDS as soon as it arrives and the first K/V tiles go out before the partials are summed, so
@@ -307,41 +301,36 @@ void k_attn_mfma(Dims D, const uint16_t* __restrict__ q,
   constexpr int GI = ONE ? 1 : (18 * (HD / 4) + NT - 1) / NT;  // column groups per thread (nrep <= 16)
   constexpr int QB = QBX ? QBX : (ONE ? kQkvBatch / 2 : kQkvBatch);  // partials loaded with the table
   const int ng = (nrep + 2) * (HD / 4);
-  const float* pr = FQ ? Q.part + (size_t)r * D.nqkv : nullptr;
+  const float* pr = Q.part + (size_t)r * D.nqkv;
   const size_t split_stride = (size_t)R * D.nqkv;
-  const int s1 = FQ ? min(Q.splits, QB) : 1;
-  float4 pv[FQ ? GI : 1][QB];
+  const int s1 = min(Q.splits, QB);
+  float4 pv[GI][QB];
   auto group_col = [&](int gi) {
     const int slot = gi / (HD / 4), i4 = (gi % (HD / 4)) * 4;
     return (slot < nrep ? (kvh * nrep + slot) * HD : D.qd + (slot - nrep) * D.kvd + kvh * HD) + i4;
   };
-  if constexpr (FQ) {
-    // Every load here is unconditional (indices clamped; the clamped threads store the same value to
-    // the same LDS word as their neighbour), so the compiler's waits stay per load: the table store
-    // waits for the table alone and the partials stay in flight behind it.
-    constexpr int half = HD / 2;
-    for (int i = tid + NT; i < ntab; i += NT) s_tab[i] = trow[i];  // contexts of more than NT blocks
-    const int ti = min(tid, max(ntab - 1, 0));
-    const int tab0 = trow[ti];
-    __builtin_amdgcn_sched_barrier(0);
-    const int tr = min(tid, HD - 1);
-    const float rope0 = tr < half ? Q.rope_cos[(size_t)pos * half + tr] : Q.rope_sin[(size_t)pos * half + tr - half];
-    __builtin_amdgcn_sched_barrier(0);
+  // Every load here is unconditional (indices clamped; the clamped threads store the same value to
+  // the same LDS word as their neighbour), so the compiler's waits stay per load: the table store
+  // waits for the table alone and the partials stay in flight behind it.
+  constexpr int half = HD / 2;
+  for (int i = tid + NT; i < ntab; i += NT) s_tab[i] = trow[i];  // contexts of more than NT blocks
+  const int ti = min(tid, max(ntab - 1, 0));
+  const int tab0 = trow[ti];
+  __builtin_amdgcn_sched_barrier(0);
+  const int tr = min(tid, HD - 1);
+  const float rope0 = tr < half ? Q.rope_cos[(size_t)pos * half + tr] : Q.rope_sin[(size_t)pos * half + tr - half];
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int it = 0; it < GI; ++it) {
-      const int c = group_col(min(tid + it * NT, ng - 1));
+  for (int it = 0; it < GI; ++it) {
+    const int c = group_col(min(tid + it * NT, ng - 1));
 #pragma unroll
-      for (int sp = 0; sp < QB; ++sp)
-        pv[it][sp] = *reinterpret_cast<const float4*>(pr + (size_t)min(sp, s1 - 1) * split_stride + c);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    s_tab[ti] = tab0;
-    s_rope[tr] = rope0;
-    lds_barrier();
-  } else {
-    for (int i = tid; i < ntab; i += NT) s_tab[i] = trow[i];
-    __syncthreads();
+    for (int sp = 0; sp < QB; ++sp)
+      pv[it][sp] = *reinterpret_cast<const float4*>(pr + (size_t)min(sp, s1 - 1) * split_stride + c);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  s_tab[ti] = tab0;
+  s_rope[tr] = rope0;
+  lds_barrier();
 
   // wave w: tiles w, w + NW, ...  They pass through a ring of DR tiles in
   // registers: while one is attended, the next DR - 1 are loading.  The first
@@ -353,105 +342,95 @@ void k_attn_mfma(Dims D, const uint16_t* __restrict__ q,
   KVTile<HD> ring[DR];
   // unconditional, so that no branch sits between these loads and the waits for the partials: a wave
   // with no tile here (n_w == 0) reloads tile 0's clamped rows and never uses them
-  if (FQ || n_w > 0) {
 #pragma unroll
-    for (int d = 0; d < DR; ++d) {
-      load_tile<HD>(ring[d], first + STRIDE * max(0, min(d, n_w - 1)), max(t_end, 1), hh, g, s_tab, blk, kv,
-                    block_stride, layer_base, blk_elems, n_blocks, &bad);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (n_w == 0) bad = false;
+  for (int d = 0; d < DR; ++d) {
+    load_tile<HD>(ring[d], first + STRIDE * max(0, min(d, n_w - 1)), max(t_end, 1), hh, g, s_tab, blk, kv,
+                  block_stride, layer_base, blk_elems, n_blocks, &bad);
+    __builtin_amdgcn_sched_barrier(0);
   }
+  if (n_w == 0) bad = false;
 
   // Q^T as the B operand: lane supplies head hh, dimensions 32c + 8g .. +7
   bf16x8_t qf[KC];
-  if constexpr (FQ) {
-    // split sums in split order: the first QB from registers (threads past the last column
-    // group store group ng - 1 again), then any further partials, loaded now
-    float4 acc[GI];
+  // split sums in split order: the first QB from registers (threads past the last column
+  // group store group ng - 1 again), then any further partials, loaded now
+  float4 acc[GI];
 #pragma unroll
-    for (int it = 0; it < GI; ++it) {
-      acc[it] = pv[it][0];
+  for (int it = 0; it < GI; ++it) {
+    acc[it] = pv[it][0];
 #pragma unroll
-      for (int sp = 1; sp < QB; ++sp) {
-        if (sp < s1) {
-          acc[it].x += pv[it][sp].x;
-          acc[it].y += pv[it][sp].y;
-          acc[it].z += pv[it][sp].z;
-          acc[it].w += pv[it][sp].w;
-        }
+    for (int sp = 1; sp < QB; ++sp) {
+      if (sp < s1) {
+        acc[it].x += pv[it][sp].x;
+        acc[it].y += pv[it][sp].y;
+        acc[it].z += pv[it][sp].z;
+        acc[it].w += pv[it][sp].w;
       }
     }
-    for (int sp = QB; sp < Q.splits; ++sp) {
-#pragma unroll
-      for (int it = 0; it < GI; ++it) {
-        const float4 t = *reinterpret_cast<const float4*>(pr + (size_t)sp * split_stride + group_col(min(tid + it * NT, ng - 1)));
-        acc[it].x += t.x;
-        acc[it].y += t.y;
-        acc[it].z += t.z;
-        acc[it].w += t.w;
-      }
-    }
+  }
+  for (int sp = QB; sp < Q.splits; ++sp) {
 #pragma unroll
     for (int it = 0; it < GI; ++it) {
-      const int gi = min(tid + it * NT, ng - 1);
-      *reinterpret_cast<float4*>(&s_raw[gi / (HD / 4)][(gi % (HD / 4)) * 4]) = acc[it];
+      const float4 t = *reinterpret_cast<const float4*>(pr + (size_t)sp * split_stride + group_col(min(tid + it * NT, ng - 1)));
+      acc[it].x += t.x;
+      acc[it].y += t.y;
+      acc[it].z += t.z;
+      acc[it].w += t.w;
     }
-    lds_barrier();
-    // rotary embedding of q and k, bf16 rounding, cache append of k and v
-    constexpr int half = HD / 2;
-    const float* cs = s_rope;
-    const float* sn = s_rope + half;
-    const int b = trow[pos / blk];
-    const bool bok = b >= 0 && b < n_blocks;
-    uint16_t* kdst = kv + (size_t)(bok ? b : 0) * block_stride + layer_base;
-    const int npair = (nrep + 1) * half;
-    for (int it = tid; it < npair + HD; it += NT) {
-      if (it < npair) {
-        const int h = it / half, i = it - h * half;
-        const float x1 = s_raw[h][i], x2 = s_raw[h][i + half];
-        const uint16_t b1 = f32_to_bf16(x1 * cs[i] - x2 * sn[i]);
-        const uint16_t b2 = f32_to_bf16(x2 * cs[i] + x1 * sn[i]);
-        if (h < nrep) {
-          s_q[h][i] = b1;
-          s_q[h][i + half] = b2;
-          if constexpr (SPLIT) {
-            uint16_t* qk = Q.q_keep + (size_t)r * D.qd + (size_t)(kvh * nrep + h) * HD;
-            qk[i] = b1;
-            qk[i + half] = b2;
-          }
-        } else {
-          s_kv[0][i] = bf16_to_f32(b1);
-          s_kv[0][i + half] = bf16_to_f32(b2);
-          if (bok) {
-            kdst[(size_t)(pos % blk) * HD + i] = b1;
-            kdst[(size_t)(pos % blk) * HD + i + half] = b2;
-          }
+  }
+#pragma unroll
+  for (int it = 0; it < GI; ++it) {
+    const int gi = min(tid + it * NT, ng - 1);
+    *reinterpret_cast<float4*>(&s_raw[gi / (HD / 4)][(gi % (HD / 4)) * 4]) = acc[it];
+  }
+  lds_barrier();
+  // rotary embedding of q and k, bf16 rounding, cache append of k and v
+  const float* cs = s_rope;
+  const float* sn = s_rope + half;
+  const int b = trow[pos / blk];
+  const bool bok = b >= 0 && b < n_blocks;
+  uint16_t* kdst = kv + (size_t)(bok ? b : 0) * block_stride + layer_base;
+  const int npair = (nrep + 1) * half;
+  for (int it = tid; it < npair + HD; it += NT) {
+    if (it < npair) {
+      const int h = it / half, i = it - h * half;
+      const float x1 = s_raw[h][i], x2 = s_raw[h][i + half];
+      const uint16_t b1 = f32_to_bf16(x1 * cs[i] - x2 * sn[i]);
+      const uint16_t b2 = f32_to_bf16(x2 * cs[i] + x1 * sn[i]);
+      if (h < nrep) {
+        s_q[h][i] = b1;
+        s_q[h][i + half] = b2;
+        if constexpr (SPLIT) {
+          uint16_t* qk = Q.q_keep + (size_t)r * D.qd + (size_t)(kvh * nrep + h) * HD;
+          qk[i] = b1;
+          qk[i + half] = b2;
         }
       } else {
-        const int i = it - npair;
-        const uint16_t bv = f32_to_bf16(s_raw[nrep + 1][i]);
-        s_kv[1][i] = bf16_to_f32(bv);
-        if (bok) kdst[blk_elems + (size_t)i * blk + pos % blk] = bv;
+        s_kv[0][i] = bf16_to_f32(b1);
+        s_kv[0][i + half] = bf16_to_f32(b2);
+        if (bok) {
+          kdst[(size_t)(pos % blk) * HD + i] = b1;
+          kdst[(size_t)(pos % blk) * HD + i + half] = b2;
+        }
       }
+    } else {
+      const int i = it - npair;
+      const uint16_t bv = f32_to_bf16(s_raw[nrep + 1][i]);
+      s_kv[1][i] = bf16_to_f32(bv);
+      if (bok) kdst[blk_elems + (size_t)i * blk + pos % blk] = bv;
     }
-    if (!bok && tid == 0) atomicOr(err, 2);
-    for (int it = tid; it < (16 - nrep) * HD; it += NT) s_q[nrep + it / HD][it % HD] = 0;
-    lds_barrier();  // LDS only: the tile loads and the cache stores stay in flight
+  }
+  if (!bok && tid == 0) atomicOr(err, 2);
+  for (int it = tid; it < (16 - nrep) * HD; it += NT) s_q[nrep + it / HD][it % HD] = 0;
+  lds_barrier();  // LDS only: the tile loads and the cache stores stay in flight
 #pragma unroll
-    for (int c = 0; c < KC; ++c) qf[c] = *reinterpret_cast<const bf16x8_t*>(&s_q[hh][32 * c + 8 * g]);
-    // score of the current token: one wave per head
-    for (int h = wave; h < nrep; h += NW) {
-      float acc = 0.f;
-      for (int d = lane; d < HD; d += 64) acc += bf16_to_f32(s_q[h][d]) * s_kv[0][d];
-      acc = wave_sum(acc);
-      if (lane == 0) s_cur[h] = acc * scale;
-    }
-  } else {
-    const uint16_t* qrow = q + (size_t)r * D.qd + (size_t)(kvh * nrep + hh) * HD;
-#pragma unroll
-    for (int c = 0; c < KC; ++c)
-      qf[c] = hh < nrep ? *reinterpret_cast<const bf16x8_t*>(qrow + 32 * c + 8 * g) : zero8;
+  for (int c = 0; c < KC; ++c) qf[c] = *reinterpret_cast<const bf16x8_t*>(&s_q[hh][32 * c + 8 * g]);
+  // score of the current token: one wave per head
+  for (int h = wave; h < nrep; h += NW) {
+    float acc = 0.f;
+    for (int d = lane; d < HD; d += 64) acc += bf16_to_f32(s_q[h][d]) * s_kv[0][d];
+    acc = wave_sum(acc);
+    if (lane == 0) s_cur[h] = acc * scale;
   }
   float m_run = -INFINITY, l_run = 0.f;
   floatx4_t o[DT];
@@ -477,7 +456,7 @@ void k_attn_mfma(Dims D, const uint16_t* __restrict__ q,
   const int Mb = (R + 15) >> 4;
   for (int item = tid; item < nrep * (HD / 8); item += NT) {
     const int h = item / (HD / 8), d0 = (item % (HD / 8)) * 8;
-    float mx = FQ ? s_cur[h] : -INFINITY;
+    float mx = s_cur[h];
 #pragma unroll
     for (int w = 0; w < NW; ++w)
       if (s_l[w][h] > 0.f) mx = fmaxf(mx, s_m[w][h]);
@@ -491,12 +470,10 @@ void k_attn_mfma(Dims D, const uint16_t* __restrict__ q,
         for (int e = 0; e < 8; ++e) num[e] += wt * s_o[w][h][d0 + e];
       }
     }
-    if constexpr (FQ) {
-      const float wt = expf(s_cur[h] - mx);
-      den += wt;
+    const float wc = expf(s_cur[h] - mx);
+    den += wc;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) num[e] += wt * s_kv[1][d0 + e];
-    }
+    for (int e = 0; e < 8; ++e) num[e] += wc * s_kv[1][d0 + e];
     if constexpr (SPLIT) {
       const size_t hr = (size_t)r * D.nh + kvh * nrep + h;
       float4* so = reinterpret_cast<float4*>(Q.st_o + hr * HD + d0);
@@ -633,6 +610,206 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
     for (int e = 0; e < 8; ++e) v[e] = den > 0.f ? num[e] / den : 0.f;
     st8(out, xoff(out, rr, hd_ * HD + d0, D.qd, Mb), v);
   }
+}
+
+// Prefill attention (head_dim 64 or 128): queries of one prompt against its own cached keys, tiled.
+//
+// A query column is one (token, query head) pair of a KV head's group, c = token * nrep + head; a workgroup
+// of four waves owns kPreCols = 128 consecutive columns (so a few tokens with all their heads: the keys a
+// workgroup visits end close to each of its columns' causal limit) and walks the keys 0 .. its last token
+// in tiles of 64.  Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: a lane holds
+// one column's scores of 32 of the tile's keys, so the softmax needs one cross-lane step per tile (the
+// maximum; the sums are joined once at the end), and the probabilities already lie in the B operand's order
+// of O^T = V^T P^T.  For that the rows of K enter the first product permuted inside every 16 keys (kv_perm,
+// bits 2 and 3 of the row exchanged): registers 8 i .. 8 i + 7 of a score tile then hold the keys
+// 16 i + 8 (lane / 32) .. + 7, the eight consecutive keys that the second product's lane supplies.  V's
+// rows (dimensions) are permuted the same way, so a lane ends with runs of eight consecutive dimensions.
+// P enters as hi + lo bf16 terms (2^-17 relative, as in attend_tile); scores and sums stay fp32.
+//
+// K and V tiles go from the cache straight into LDS (dma_lds16), double buffered: tile i + 1 is in flight
+// while tile i is used, one barrier per tile.  K keeps its rows (chunks of 16 bytes exchanged inside the
+// row, so that eight lanes reading eight rows meet eight different bank groups), V is stored in the order
+// the fragments are read.  Tokens past the prompt are clamped: as keys the causal mask drops them, as
+// values they may be stale, so the last tile's values past the prompt are zeroed in LDS.  (A masked key of
+// the prompt itself enters P V with weight 0.)
+//
+// Bound: the matrix pipe and the softmax's vector instructions side by side (48 MFMAs of 32 cycles against
+// about 1,400 vector cycles per wave and tile), two waves per SIMD.  Why tiles: one workgroup per token and
+// KV head read the whole prefix again for every token.  Per layer, before -> now: 7B width, one prompt of
+// 3,967 tokens 2,940 -> 224 us (0.75 PFLOP/s of MFMA work); 8 x 512 tokens at 14B width 797 -> 54 us; 8 x 256 at
+// 7B width 173 -> 20 us; 4 x 512 at 72B width 485 -> 45 us; one prompt of 203 tokens 23 -> 13 us.
+constexpr int kPreCols = 128, kPreKeys = 64;
+
+typedef float floatx16_t __attribute__((ext_vector_type(16)));
+typedef float floatx2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ int kv_perm(int a) { return (a & ~12) | ((a & 4) << 1) | ((a & 8) >> 1); }
+
+template <int HD>
+__global__ __launch_bounds__(256, 2) void k_attn_prefill(Dims D, const uint16_t* __restrict__ q,
+                                                         const uint16_t* __restrict__ kv, int n_blocks,
+                                                         const int32_t* __restrict__ tables, int max_blocks, RowMap rm,
+                                                         int R, int layer, uint16_t* __restrict__ out,
+                                                         int32_t* __restrict__ err) {
+  constexpr int KS = HD / 16;  // k-steps of Q K^T
+  constexpr int DT = HD / 32;  // 32-dimension tiles of the output
+  constexpr int CH = HD / 8;   // 16-byte chunks of a key row
+  constexpr int TB = kPreKeys * HD;
+  __shared__ __align__(16) uint16_t s_k[2][TB];
+  __shared__ __align__(16) uint16_t s_v[2][TB];
+  extern __shared__ int s_tab[];  // the prompt's block ids (ceil(P / blk) entries)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int a = lane & 31, half = lane >> 5;
+  const int P = rm.P, nrep = D.nh / D.nkv, ncol = P * nrep;
+  const int npair = R / P * D.nkv;  // (prompt, KV head) pairs; workgroup order: the longest key ranges first
+  const int pair = (int)(blockIdx.x % npair), qb = (int)(gridDim.x / npair) - 1 - (int)(blockIdx.x / npair);
+  const int prompt = pair / D.nkv, kvh = pair % D.nkv;
+  const int blk = D.blk, sh = __ffs(blk) - 1;  // 8, 16 or 32 tokens
+  const size_t blk_elems = (size_t)blk * HD;
+  const size_t head_elems = 2 * blk_elems;
+  const size_t layer_base = kv_offset(layer, 0, kvh, n_blocks, D.nkv, head_elems);
+  const size_t block_stride = (size_t)D.nkv * head_elems;
+  const int32_t* trow = tables + (size_t)(rm.seq0 + prompt * rm.G) * max_blocks;
+  bool bad = false;
+  for (int i = tid; i < (P + blk - 1) / blk; i += 256) {
+    int b = trow[i];
+    if ((unsigned)b >= (unsigned)n_blocks) { bad = true; b = 0; }
+    s_tab[i] = b;
+  }
+  if (bad) atomicOr(err, 4);
+  __syncthreads();
+
+  const int col0 = qb * kPreCols + 32 * wave;                 // the wave's first column
+  const int col = min(col0 + a, ncol - 1);
+  const int tok = col / nrep, head = kvh * nrep + col % nrep;  // this lane's query
+  const int row = prompt * P + tok;
+  const int wg_last = min((qb + 1) * kPreCols, ncol) - 1;
+  const int n_tiles = (wg_last / nrep) / kPreKeys + 1;
+  const int w_first = min(col0, ncol - 1) / nrep, w_last = min(col0 + 31, ncol - 1) / nrep;  // the wave's tokens
+
+  bf16x8_t qf[KS];
+#pragma unroll
+  for (int c = 0; c < KS; ++c)
+    qf[c] = *reinterpret_cast<const bf16x8_t*>(q + (size_t)row * D.qd + (size_t)head * HD + 16 * c + 8 * half);
+
+  auto load = [&](int buf, int tile) {
+    const int t0 = tile * kPreKeys;
+    // K: rows 16 wave .. + 15; an instruction covers 64 / CH rows, row chunk j stored at j ^ (kv_perm(row) % CH)
+    const uint16_t* src[HD / 32];
+#pragma unroll
+    for (int i = 0; i < HD / 32; ++i) {
+      const int r = 16 * wave + i * (64 / CH) + lane / CH;
+      const int t = min(t0 + r, P - 1);
+      const int ch = (lane % CH) ^ (kv_perm(r & 15) & (CH - 1));
+      src[i] = kv + (size_t)s_tab[t >> sh] * block_stride + layer_base + (size_t)(t & (blk - 1)) * HD + 8 * ch;
+    }
+    // V: fragments of key step `wave`; lane = dimension (permuted) + 32 * (eight-key half)
+    const int t8 = min(t0 + 16 * wave + 8 * half, (P - 1) & ~7);
+    const uint16_t* vb = kv + (size_t)s_tab[t8 >> sh] * block_stride + layer_base + blk_elems + (t8 & (blk - 1)) +
+                         (size_t)kv_perm(a) * blk;
+#pragma unroll
+    for (int i = 0; i < HD / 32; ++i) dma_lds16(src[i], &s_k[buf][(16 * wave + i * (64 / CH)) * HD]);
+#pragma unroll
+    for (int d = 0; d < DT; ++d) dma_lds16(vb + (size_t)32 * d * blk, &s_v[buf][(wave * DT + d) * 512]);
+  };
+#pragma unroll
+  for (int c = 0; c < KS; ++c) asm volatile("" : "+v"(qf[c]));  // q has arrived: no wait for it among the tiles
+
+  floatx16_t o[DT];
+#pragma unroll
+  for (int d = 0; d < DT; ++d)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[d][e] = 0.f;
+  // scores are kept in units of log 2: p = 2^(s c - m)
+  const float c2 = 1.44269504088896341f / sqrtf((float)HD);
+  float m_run = -INFINITY, l_run = 0.f;
+
+  load(0, 0);
+  for (int it = 0; it < n_tiles; ++it) {
+    dma_wait_barrier();  // tile `it` is in LDS for every wave, and nobody reads the other buffer any more
+    if (it + 1 < n_tiles) load((it + 1) & 1, it + 1);
+    const int t0 = it * kPreKeys;
+    const uint16_t* kb = s_k[it & 1];
+    uint16_t* vb = s_v[it & 1];
+    if (t0 + kPreKeys > P) {  // the prompt's last tile: values past its end are zeroed
+      for (int i = tid; i < 4 * DT * 64; i += 256) {
+        const int ok = P - (t0 + 16 * (i / (DT * 64)) + 8 * ((i >> 5) & 1));  // values of this chunk inside the prompt
+        for (int e = max(ok, 0); e < 8; ++e) vb[8 * i + e] = 0;
+      }
+      lds_barrier();
+    }
+    if (t0 > w_last) continue;  // (wave-uniform) every key of the tile lies past the wave's tokens
+    floatx16_t s[2];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[kt][e] = 0.f;
+      const int r = 32 * kt + kv_perm(a);
+#pragma unroll
+      for (int c = 0; c < KS; ++c) {
+        const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(kb + r * HD + 8 * ((2 * c + half) ^ (a & (CH - 1) & 15)));
+        s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], s[kt], 0, 0, 0);
+      }
+    }
+    if (t0 + kPreKeys - 1 > w_first) {  // causal limit inside the tile for some column
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (t0 + 32 * kt + 16 * (e >> 3) + 8 * half + (e & 7) > tok) s[kt][e] = -INFINITY;
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[kt][e]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
+    if (__any(mx > m_run)) {  // no column has a new maximum in most tiles after the first
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int d = 0; d < DT; ++d) o[d] *= alpha;
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      bf16x8_t ph, pl;
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kk >> 1][8 * (kk & 1) + e], c2, -m_run));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kk >> 1][8 * (kk & 1) + e + 1], c2, -m_run));
+        l_run += p0 + p1;
+        const bf16x2_t h = __builtin_convertvector((floatx2_t{p0, p1}), bf16x2_t);
+        const bf16x2_t w = __builtin_convertvector((floatx2_t{p0 - (float)h[0], p1 - (float)h[1]}), bf16x2_t);
+        ph[e] = h[0];
+        ph[e + 1] = h[1];
+        pl[e] = w[0];
+        pl[e + 1] = w[1];
+      }
+#pragma unroll
+      for (int d = 0; d < DT; ++d) {
+        const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(vb + (kk * DT + d) * 512 + lane * 8);
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ph, o[d], 0, 0, 0);
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl, o[d], 0, 0, 0);
+      }
+    }
+  }
+  if (col0 + a >= ncol) return;
+  const float l = l_run + __shfl_xor(l_run, 32, 64);
+  const float inv = 1.0f / l;
+  const int Mb = (R + 15) >> 4;
+#pragma unroll
+  for (int d = 0; d < DT; ++d)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = o[d][8 * i + e] * inv;
+      st8(out, xoff(out, row, head * HD + 32 * d + 16 * i + 8 * half, D.qd, Mb), v);
+    }
 }
 
 template <typename T, int HD>
@@ -814,11 +991,11 @@ hipError_t launch_attention_shared(hipStream_t s, const Dims& D, void* kv_pool, 
 #define ROLLOUT_SUFFIX(HD, NW)                                                                                       \
   do {                                                                                                               \
     if (one_group(D, NW))                                                                                            \
-      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, true, true, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,          \
-                         (const uint16_t*)nullptr, kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);      \
+      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, true, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,          \
+                         kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);      \
     else                                                                                                             \
-      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, true, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,                \
-                         (const uint16_t*)nullptr, kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);      \
+      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,                \
+                         kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);      \
   } while (0)
   const int nws = attn_waves(R * D.nkv);
   if (D.hd == 128) {
@@ -870,6 +1047,20 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
     return hipErrorInvalidValue;
   if (mfma_attention(D)) {
     if (max_blocks > kMaxTableBlocks) return hipErrorInvalidValue;  // the block table is staged in LDS
+    if ((rm.P > 0) == (qkv_part != nullptr)) return hipErrorInvalidValue;  // decode rows bring their partials
+    if (rm.P > 0) {
+      if (R % rm.P) return hipErrorInvalidValue;  // whole prompts
+      const int ncol = rm.P * (D.nh / D.nkv);
+      const dim3 pgrid((unsigned)(R / rm.P * D.nkv) * (unsigned)((ncol + kPreCols - 1) / kPreCols));
+      const size_t ptab = (size_t)((rm.P + D.blk - 1) / D.blk) * 4;
+      if (D.hd == 128)
+        hipLaunchKernelGGL((k_attn_prefill<128>), pgrid, dim3(256), ptab, s, D, (const uint16_t*)q,
+                           (const uint16_t*)kv_pool, n_blocks, tables, max_blocks, rm, R, layer, (uint16_t*)out, err);
+      else
+        hipLaunchKernelGGL((k_attn_prefill<64>), pgrid, dim3(256), ptab, s, D, (const uint16_t*)q,
+                           (const uint16_t*)kv_pool, n_blocks, tables, max_blocks, rm, R, layer, (uint16_t*)out, err);
+      return hipGetLastError();
+    }
     const int nw = attn_waves(R * D.nkv);
     static const int dr = [] {
       const char* v = std::getenv("ROLLOUT_ATTN_RING");
@@ -878,43 +1069,37 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
     }();
     const dim3 grid(attn_grid(R, D));
     const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, nullptr, nullptr};
-    const uint16_t* qq = (const uint16_t*)q;
     uint16_t* kk = (uint16_t*)kv_pool;
     uint16_t* oo = (uint16_t*)out;
     const size_t tab_bytes = (size_t)max_blocks * 4;
-#define ROLLOUT_MFMA_ATTN(HD, NW, DR, FQ)                                                                              \
+#define ROLLOUT_MFMA_ATTN(HD, NW, DR)                                                                                  \
   do {                                                                                                                 \
-    if constexpr (FQ && DR == 2) {                                                                                     \
+    if constexpr (DR == 2) {                                                                                           \
       if (one_group(D, NW)) {                                                                                          \
-        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, FQ, false, true>), grid, dim3(NW * 64), tab_bytes, s, D, qq, kk,   \
+        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, false, true>), grid, dim3(NW * 64), tab_bytes, s, D, kk, n_blocks, \
+                           tables, max_blocks, rm, R, layer, Q, oo, err);                                              \
+        break;                                                                                                         \
+      }                                                                                                                \
+    }                                                                                                                  \
+    if constexpr (DR == 2 && NW == 4) {                                                                                \
+      if (qkv_splits <= 4) {                                                                                           \
+        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, false, false, 4>), grid, dim3(NW * 64), tab_bytes, s, D, kk,       \
                            n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);                                    \
         break;                                                                                                         \
       }                                                                                                                \
     }                                                                                                                  \
-    if constexpr (FQ && DR == 2 && NW == 4) {                                                                      \
-      if (qkv_splits <= 4) {                                                                                           \
-        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, FQ, false, false, 4>), grid, dim3(NW * 64), tab_bytes, s, D, qq,   \
-                           kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);                                \
-        break;                                                                                                         \
-      }                                                                                                                \
-    }                                                                                                                  \
-    hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, FQ>), grid, dim3(NW * 64), tab_bytes, s, D, qq, kk, n_blocks, tables,  \
+    hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR>), grid, dim3(NW * 64), tab_bytes, s, D, kk, n_blocks, tables,          \
                        max_blocks, rm, R, layer, Q, oo, err);                                                          \
   } while (0)
-#define ROLLOUT_MFMA_ATTN_NW(HD, FQ)                    \
-  do {                                                  \
-    if (nw == 4) ROLLOUT_MFMA_ATTN(HD, 4, 2, FQ);         \
-    else if (dr == 3) ROLLOUT_MFMA_ATTN(HD, 8, 3, FQ);    \
-    else if (dr == 4) ROLLOUT_MFMA_ATTN(HD, 8, 4, FQ);    \
-    else ROLLOUT_MFMA_ATTN(HD, 8, 2, FQ);                 \
+#define ROLLOUT_MFMA_ATTN_NW(HD)                    \
+  do {                                              \
+    if (nw == 4) ROLLOUT_MFMA_ATTN(HD, 4, 2);       \
+    else if (dr == 3) ROLLOUT_MFMA_ATTN(HD, 8, 3);  \
+    else if (dr == 4) ROLLOUT_MFMA_ATTN(HD, 8, 4);  \
+    else ROLLOUT_MFMA_ATTN(HD, 8, 2);               \
   } while (0)
-    if (D.hd == 128) {
-      if (qkv_part) ROLLOUT_MFMA_ATTN_NW(128, true);
-      else ROLLOUT_MFMA_ATTN_NW(128, false);
-    } else {
-      if (qkv_part) ROLLOUT_MFMA_ATTN_NW(64, true);
-      else ROLLOUT_MFMA_ATTN_NW(64, false);
-    }
+    if (D.hd == 128) ROLLOUT_MFMA_ATTN_NW(128);
+    else ROLLOUT_MFMA_ATTN_NW(64);
 #undef ROLLOUT_MFMA_ATTN_NW
 #undef ROLLOUT_MFMA_ATTN
     return hipGetLastError();

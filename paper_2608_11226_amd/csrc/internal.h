@@ -267,6 +267,21 @@ __device__ __forceinline__ void ld8(const uint16_t* p, size_t i, float* v) {
 // outstanding global memory operations (a register prefetch, stores) is added.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// 16 bytes per lane from global memory straight into LDS: lane i's bytes land at dst + 16 i (dst is the same
+// for the whole wave; src is each lane's own).  Counted like a global load (vmcnt).  Written as asm because
+// the compiler otherwise waits for every transfer in flight before the next LDS read of any buffer; the
+// kernel waits itself (dma_wait_barrier) before it reads what a transfer wrote.  M0 is set here and used by
+// nothing else in kernels that call this.
+__device__ __forceinline__ void dma_lds16(const void* src, void* dst) {
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)dst);
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
+}
+
+// The wave's outstanding transfers into LDS and LDS accesses are complete, then every wave has arrived.
+__device__ __forceinline__ void dma_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

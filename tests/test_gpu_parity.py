@@ -301,6 +301,44 @@ def test_bf16_gqa7_teacher_forced_logits(blk, n_prompts, G, P, shared, waves, mo
     eng.close()
 
 
+# prefill attention: tiles of 128 (token, head) columns and 64 keys.  Prompts of one token, around a key tile
+# and around two, column tiles that end inside a token's heads (7 and 5 heads per KV head, 16 with one token
+# left over) and head_dim 64, block sizes 8, 16 and 32, several prompts per launch.
+PREFILL_ATTN = [
+    # (model shape, block size, prompts, prompt length)
+    ((1, 256, 14, 2, 128, 256, 2048, 1e6), 16, 2, 1), ((1, 256, 14, 2, 128, 256, 2048, 1e6), 16, 3, 63),
+    ((1, 256, 14, 2, 128, 256, 2048, 1e6), 8, 1, 64), ((1, 256, 14, 2, 128, 256, 2048, 1e6), 32, 2, 65),
+    ((2, 256, 10, 2, 128, 256, 2048, 1e6), 16, 2, 203), ((1, 256, 16, 1, 64, 256, 2048, 1e6), 8, 3, 129),
+    ((1, 256, 3, 3, 64, 256, 2048, 1e6), 32, 1, 127),
+]
+
+
+@pytest.mark.parametrize("shape,blk,n_prompts,P", PREFILL_ATTN)
+def test_bf16_prefill_attention_tiles(shape, blk, n_prompts, P):
+    log(f"bf16 prefill attention shape={shape} blk={blk} prompts={n_prompts} P={P}")
+    G, N = 2, 3
+    S = n_prompts * G
+    cfg = R.model_config(shape, R.DTYPE_BF16, P, N, S, kv_block_size=blk)
+    eng = R.Engine(cfg)
+    model = OracleModel(shape_of(cfg), mode="bf16")
+    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=47)
+    ref = rollout(model, prompts, G, N, 1.0, 1.0, W.uniforms(S, N, seed=48))
+    logits = torch.empty((S, cfg.vocab), dtype=torch.float32, device="cuda:0")
+    # stale values (NaN bit patterns) in the pool must not reach a prompt's outputs
+    eng.arena[eng.plan.arena_bytes - eng.plan.kv_bytes:].fill_(255)
+    torch.cuda.synchronize()
+    R.rollout_prefill(eng.ctx, to_dev(prompts, torch), n_prompts, P, G, logits)
+    eng.synchronize()
+    err = [float(np.max(np.abs(logits.cpu().numpy() - ref["logits"][0])))]
+    for t in range(1, N):
+        R.rollout_decode_step(eng.ctx, to_dev(ref["tokens"][:, t - 1], torch), logits)
+        eng.synchronize()
+        err.append(float(np.max(np.abs(logits.cpu().numpy() - ref["logits"][t]))))
+    log(f"  max abs logit error per step: {[round(e, 5) for e in err]}")
+    assert max(err) <= 3e-2  # the bf16 contract's bound, as in the tests above
+    eng.close()
+
+
 @pytest.mark.parametrize("shared", ["0", "2"])
 def test_bf16_gqa7_context_beyond_4096_tokens_teacher_forced(shared, monkeypatch):
     # A context of more than 256 blocks of 16 (4,096 tokens): the decode attention's workgroup of 256
