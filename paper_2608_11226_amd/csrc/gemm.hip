@@ -31,22 +31,9 @@
 // balanced grid instead: one workgroup of two waves per CU, the blocks shared out evenly (BAL below); so
 // does the LM head, with four one-wave workgroups per CU.
 //
-// k_gemm_wlds (decode batches of 129..256 rows): one workgroup holds all activation rows, so each weight
-// byte enters one CU; the weights of a k-step are staged in LDS for the four waves and each wave reads its
-// own activation rows straight from L2 (details at the kernel).
-//
-// k_gemm_tile (prefill, and batches of 65..128 or more than 256 rows): a workgroup of four
-// waves owns 256 weight rows x 128 activation rows; each wave owns its own 64
-// weight rows against all 128 activation rows (4 x 8 MFMA tiles, 128
-// accumulator registers, two waves per SIMD).  The weights never touch LDS:
-// each wave streams its own weight fragments from global memory straight into
-// a three-deep register ring (no two waves read the same weight fragment).
-// The activation fragments are shared by the four waves through a double LDS
-// buffer, staged global -> registers -> LDS three k-steps ahead.  Per k-step
-// a wave reads 8 KB from LDS for 32 MFMAs; one barrier per k-step.  All waits
-// are compiler-placed on loads issued a step or more earlier.  Workgroup order
-// is XCD-aware: the M tiles of one N tile run on one XCD, so its weight tile
-// is fetched into that XCD's L2 once and served to the rest from there.
+// k_gemm_pp (prefill and decode batches of more than 64 rows): eight waves in two groups that take turns
+// between LDS reads and MFMAs, both operands through an LDS ring filled by direct loads; tile and K splits
+// chosen per shape (details at the kernel and at tile_plan).
 //
 // k_gemm_q4 (decode with int4 layer weights, M <= 64): weights as 4-bit codes
 // in groups of 128 inputs with an fp32 scale and a zero point per row and
@@ -54,13 +41,13 @@
 // weights are never rounded.  The codes enter the MFMA as exact bf16 integers
 // (128 + q); a workgroup of four waves shares each group's activation
 // fragments and their sums through LDS.  Larger batches with int4 weights
-// dequantise a projection into two bf16 tile matrices (hi + lo) and take the
-// tile kernel twice.
+// dequantise a projection into two bf16 tile matrices (hi + lo) and take
+// k_gemm_pp twice.
 //
 // fp32 path: a plain LDS-tiled VALU GEMM over row-major X and W (the fp32
 // path exists for exact parity on small models, not for speed).
 #include <algorithm>
-#include <cstdlib>
+#include <cmath>
 
 #include "internal.h"
 
@@ -75,241 +62,123 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
 }
 
-// Tile kernel: 4 waves; a workgroup owns NB 16-row weight blocks per wave against MBW 16-row activation
-// blocks (NB = 4, MBW = 8: 256 weight rows x 128 activation rows, each wave 64 x 128).
-constexpr int kTileWaves = 4;
-constexpr int kTileNB = 4, kTileMB = 8;
-
-// SWI: gate/up with SwiGLU applied to the output (one K split): h in the down projection's operand layout
-// XD: activation register stages (each k-step's X fragments are loaded XD steps before they are staged
-// into LDS); OCC: waves per SIMD the registers are sized for.  Batches above 256 rows (prefill, MFMA-bound)
-// take XD = 3 at two waves per SIMD; decode-sized batches, one wave per SIMD anyway, take XD = 6.
-// Workgroups run in XCD-aware order: the M tiles of one N tile share one XCD and its L2.
-template <int NB, int MBW, bool SWI, int XD, int OCC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-void k_gemm_tile(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, float* __restrict__ out,
-                 int M, int N, int K, int kslice, uint16_t* __restrict__ h) {
-  constexpr int XPW = MBW / kTileWaves;  // activation fragments each wave stages per k-step
-  __shared__ bf16x8_t xs[2][MBW][64];
+// k_gemm_pp: batches of more than 64 rows.  A workgroup of eight waves owns TN = NB * WN weight blocks (16 rows
+// each) x TM = MBW * WM activation blocks; wave (wn, wm) multiplies NB of the weight blocks with MBW of the
+// activation blocks (NB x MBW MFMA tiles in registers).  Each k-step's TN + TM fragments (1 KB each) go from
+// global memory straight into LDS (dma_lds16: both operands are stored fragment by fragment, so a transfer
+// is one contiguous KB and an LDS read is conflict-free) through a ring of NS k-steps, NS - 1 in flight.
+//
+// The two waves of every SIMD take turns: waves 0..3 and waves 4..7 run the same two phases per k-step, one
+// phase apart -- memory (read the step's NB + MBW fragments from LDS, wait for the next step's transfers) and
+// multiply (NB * MBW MFMAs) -- with a barrier between phases, so the matrix pipe of a SIMD always has one
+// wave's MFMAs while the other wave's LDS reads and transfers run beside them.  (Waves of a workgroup are
+// placed on the SIMDs in turn; another placement costs time, not correctness.)  With eight waves in step
+// instead, the same tile, ring and fragments take 5 to 15% longer, also with the next step's fragments read
+// into a second register set during the MFMAs.
+//
+// Phases and slots: barrier b0 follows the prologue; group 0 multiplies step s between barriers 2 s + 1 and
+// 2 s + 2, group 1 between 2 s + 2 and 2 s + 3, and each reads step s from LDS in the phase before.  A wave
+// refills the slot of step s - 1 (with step s + NS - 1) after its multiply phase of step s: both groups have
+// read that slot by then.  Before the barrier that ends its reads of step s a wave waits until its own
+// transfers of step s + 1 have landed, so the step is whole when group 0 comes to read it.
+//
+// Why: the previous kernels (a 256 x 128 tile of four waves with weights in a register ring; for 129..256 rows
+// weights staged through registers and LDS by four waves) ran at the rate a CU fetches its operands or at
+// one wave's latency per k-step.  us before -> now (sum of its partials' reads included), PFLOP/s now:
+//   2,048 rows: 7B gate/up 479-553 -> 416-440 (1.3), 7B QKV 119 -> 70, O 75 -> 57, down 258 -> 214
+//   4,096 rows: 14B gate/up 1,000 -> 840 (1.38), 14B O 235 -> 172, down 566 -> 415, 72B gate/up 3,150 -> 2,690 (1.48)
+//   512 rows:   7B QKV 64 -> 31, down 95 -> 73, gate/up 147 -> 102;  256 rows: 7B gate/up 109 -> 71,
+//   14B head 424 -> 369;  128 rows: 14B gate/up 84 -> 62, 7B down 45 -> 38, 7B head 248 -> 234
+// All sums are bit-equal to the previous kernels' at equal splits (k order).
+template <int NB, int MBW, int WN, int WM, int NS, bool SWI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, float* __restrict__ out, int M, int N,
+               int K, int kslice, int Nt, uint16_t* __restrict__ h) {
+  constexpr int TN = NB * WN, TM = MBW * WM, FR = TN + TM;
+  constexpr int PER = (FR + 7) / 8;  // fragments a wave transfers per k-step (surplus ones repeat the last)
+  static_assert(WN * WM == 8 && NS >= 3, "eight waves");
+  __shared__ bf16x8_t ls[NS][FR][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nbt = N >> 4, kbt = K >> 5, Mb = (M + 15) >> 4;
-  const int Mt = (Mb + MBW - 1) / MBW, Nt = (nbt + NB * kTileWaves - 1) / (NB * kTileWaves);
-  // XCD-aware order (workgroup b runs on XCD b % 8): the M tiles of N tile nt share one XCD and its L2
-  const int b = blockIdx.x;
-  const int grp = b / (8 * Mt), rem = b % (8 * Mt);
-  const int nt = grp * 8 + rem % 8, mt = rem / 8;
-  if (nt >= Nt) return;
-  // the workgroup's first weight block and its block count, its first activation block
-  const int wb0 = nt * NB * kTileWaves, wbc = min(NB * kTileWaves, nbt - wb0), mb0 = mt * MBW;
-  const int lb0 = wave * NB;  // the wave's first block within the workgroup's
+  const int Mt = (Mb + TM - 1) / TM, tiles = Mt * Nt;
+  // XCD-aware order (workgroup b runs on XCD b % 8): each XCD takes a contiguous range of tiles, M fastest, so
+  // the M tiles of one N tile share its weights through one L2
+  const int x = blockIdx.x & 7, t0 = (int)((long long)x * tiles / 8), t1 = (int)((long long)(x + 1) * tiles / 8);
+  const int tile = t0 + (int)(blockIdx.x >> 3);
+  if (tile >= t1) return;
+  const int nt = tile / Mt, mb0 = tile % Mt * TM;
+  const int wb0 = (int)((long long)nt * nbt / Nt), wbc = (int)((long long)(nt + 1) * nbt / Nt) - wb0;  // wbc <= TN
   const int kb0 = (int)blockIdx.y * (kslice >> 5);
   const int nk = min(kbt, kb0 + (kslice >> 5)) - kb0;
+  const int wn = wave % WN, wm = wave / WN;
   floatx4_t acc[NB][MBW];
 #pragma unroll
   for (int j = 0; j < NB; ++j)
 #pragma unroll
     for (int i = 0; i < MBW; ++i) acc[j][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  if (nk > 0) {
-    // every load is unconditional: block and k indices are clamped into range, surplus k-steps are not computed
-    const bf16x8_t* wp[NB];
-    int ws[NB];  // k-step stride of each block's fragments
+  // the wave's fragments of a k-step (blocks past the tile's or the matrix's repeat the last one)
+  const char* fb[PER];
+  uint32_t fs[PER];  // bytes from one k-step to the next
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int nb = wb0 + min(lb0 + j, wbc - 1);
-      wp[j] = W + wfrag(nb, kb0, nbt, kbt) * 64 + lane;
-      ws[j] = wgroup_blocks(nb, nbt) * 64;
+  for (int i = 0; i < PER; ++i) {
+    const int f = min(PER * wave + i, FR - 1);
+    if (f < TN) {
+      const int nb = wb0 + min(f, wbc - 1);
+      fb[i] = (const char*)(W + wfrag(nb, kb0, nbt, kbt) * 64);
+      fs[i] = wgroup_blocks(nb, nbt) * 1024;
+    } else {
+      fb[i] = (const char*)(XF + ((size_t)kb0 * Mb + min(mb0 + f - TN, Mb - 1)) * 64);
+      fs[i] = (uint32_t)Mb * 1024;
     }
-    const bf16x8_t* xp[XPW];
+  }
+  auto transfer = [&](int slot, int st) {  // steps past the last repeat it into slots that are not read again
+    const size_t kk = (size_t)min(st, nk - 1);
 #pragma unroll
-    for (int i = 0; i < XPW; ++i)
-      xp[i] = XF + ((size_t)kb0 * Mb + min(mb0 + XPW * wave + i, Mb - 1)) * 64 + lane;
-    const size_t xstride = (size_t)Mb * 64;
-    static_assert(6 % XD == 0, "the k-step loop is unrolled by 6");
-    bf16x8_t wr[3][NB], xg[XD][XPW];
-    auto load_w = [&](int slot, int st) {
-      const size_t kk = (size_t)min(st, nk - 1);
+    for (int i = 0; i < PER; ++i)
+      dma_lds16_at(fb[i] + kk * fs[i], lane * 16, &ls[slot][min(PER * wave + i, FR - 1)][0]);
+  };
+  if (nk > 0) {
+    bf16x8_t wf[NB], xf[MBW];
 #pragma unroll
-      for (int j = 0; j < NB; ++j) wr[slot][j] = wp[j][kk * ws[j]];
-    };
-    auto load_x = [&](int slot, int st) {
-      const size_t kk = (size_t)min(st, nk - 1);
+    for (int s = 0; s < NS - 1; ++s) transfer(s, s);
+    dma_wait_barrier<(NS - 2) * PER>();
+    if (wave >= 4) phase_barrier();  // the second group runs one phase behind
+    for (int s0 = 0; s0 < nk; s0 += NS) {
 #pragma unroll
-      for (int i = 0; i < XPW; ++i) xg[slot][i] = xp[i][kk * xstride];
-    };
-    auto stage_x = [&](int buf, int slot) {
-#pragma unroll
-      for (int i = 0; i < XPW; ++i) xs[buf][XPW * wave + i][lane] = xg[slot][i];
-    };
-    // k-step st computes from LDS buffer st % 2 and weight slot st % 3.  Before it, the step loads
-    // W(st + 2), writes X(st + 1) (loaded XD steps earlier, register slot (st + 1) % XD) into the other LDS
-    // buffer and loads X(st + 1 + XD) into that slot; every wait the compiler inserts is then on loads
-    // issued at least one step earlier.
-    load_w(0, 0);
-    load_w(1, 1);
-#pragma unroll
-    for (int d = 0; d < XD; ++d) load_x(d, d);
-    stage_x(0, 0);
-    load_x(0, XD);
-    lds_barrier();
-    for (int s0 = 0; s0 < nk; s0 += 6) {
-#pragma unroll
-      for (int u = 0; u < 6; ++u) {
+      for (int u = 0; u < NS; ++u) {
         const int st = s0 + u;
-        load_w((u + 2) % 3, st + 2);
-        stage_x((u + 1) & 1, (u + 1) % XD);
-        load_x((u + 1) % XD, st + 1 + XD);
         if (st < nk) {
 #pragma unroll
-          for (int i = 0; i < MBW; ++i) {
-            const bf16x8_t xf = xs[u & 1][i][lane];
+          for (int j = 0; j < NB; ++j) wf[j] = ls[u][wn * NB + j][lane];
+#pragma unroll
+          for (int i = 0; i < MBW; ++i) xf[i] = ls[u][TN + wm * MBW + i][lane];
+          dma_wait_barrier<(NS - 3) * PER>();
+          __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+          for (int i = 0; i < MBW; ++i)
 #pragma unroll
             for (int j = 0; j < NB; ++j)
-              acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[u % 3][j], xf, acc[j][i], 0, 0, 0);
-          }
-          // two LDS fragment reads ahead of the MFMAs, then one more per fragment's NB MFMAs
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-          for (int i = 0; i < MBW - 2; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB, 0);
+              acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[j][i], 0, 0, 0);
+          __builtin_amdgcn_s_setprio(0);
+          __builtin_amdgcn_sched_barrier(0);  // the MFMAs stay in their phase
+          phase_barrier();
+          transfer((u + NS - 1) % NS, st + NS - 1);
         }
-        lds_barrier();
       }
     }
+    if (wave < 4) phase_barrier();  // as many barriers as the second group
+    dma_wait();                     // no transfer outlives the workgroup's LDS
   }
   // D layout of the 16x16 MFMA: lane holds rows 4*(lane/16)+r (weight rows n) of column lane%16 (row m of X)
   float* o = out + (size_t)blockIdx.y * M * N;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    if (lb0 + j >= wbc) continue;
-    const int n = (wb0 + lb0 + j) * 16 + 4 * (lane >> 4);
+    if (wn * NB + j >= wbc) continue;
+    const int n = (wb0 + wn * NB + j) * 16 + 4 * (lane >> 4);
 #pragma unroll
     for (int i = 0; i < MBW; ++i) {
-      const int m = (mb0 + i) * 16 + (lane & 15);
-      if (m >= M) continue;
-      if constexpr (SWI) {
-        // rows n, n+1 are (gate, up) of output f = n/2; rows n+2, n+3 of output f + 1
-        const float g0 = acc[j][i][0], u0 = acc[j][i][1], g1 = acc[j][i][2], u1 = acc[j][i][3];
-        const float h0 = g0 / (1.0f + expf(-g0)) * u0, h1 = g1 / (1.0f + expf(-g1)) * u1;
-        *reinterpret_cast<uint32_t*>(h + xoff(h, m, n >> 1, N >> 1, Mb)) = pack_bf16x2(h0, h1);
-      } else {
-        *reinterpret_cast<float4*>(o + (size_t)m * N + n) = make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]);
-      }
-    }
-  }
-}
-
-// Tall decode batches (129..256 rows), weights staged in LDS: a workgroup of four waves owns up to
-// kWldsBlocks weight blocks (128 rows; the grid shares the blocks out evenly, floor(nbt / grid) or one more
-// each) and all 16 activation blocks; wave w owns activation blocks 4w .. 4w + 3 against every weight block
-// of the workgroup (8 x 4 MFMA tiles).  A k-step's weight fragments (8 KB) are streamed from HBM once per
-// workgroup -- each wave stages two of them, global -> registers (three steps ahead) -> LDS (double
-// buffered) -- and read from LDS by all four waves, while each wave loads its own activation fragments
-// from L2 straight into registers, XD steps ahead.  Per k-step and CU: 40 KB of LDS traffic for 128 MFMAs
-// (staging the 16 KB activation tile instead would take 80 KB), and every weight byte enters one CU.
-// One LDS barrier per k-step; loads are unconditional (indices clamped, surplus steps not computed).
-constexpr int kWldsBlocks = 8;
-template <bool SWI, int XD, int WD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void k_gemm_wlds(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, float* __restrict__ out, int M,
-                 int N, int K, int kslice, uint16_t* __restrict__ h) {
-  constexpr int NBG = kWldsBlocks;           // weight blocks per workgroup
-  constexpr int MBV = 4;                     // activation blocks per wave
-  constexpr int WPW = NBG / kTileWaves;      // weight fragments each wave stages per k-step
-  __shared__ bf16x8_t wl[2][NBG][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nbt = N >> 4, kbt = K >> 5, Mb = (M + 15) >> 4;
-  const int wb0 = (int)((long long)blockIdx.x * nbt / gridDim.x);
-  const int wbc = (int)((long long)(blockIdx.x + 1) * nbt / gridDim.x) - wb0;
-  const int kb0 = (int)blockIdx.y * (kslice >> 5);
-  const int nk = min(kbt, kb0 + (kslice >> 5)) - kb0;
-  floatx4_t acc[NBG][MBV];
-#pragma unroll
-  for (int j = 0; j < NBG; ++j)
-#pragma unroll
-    for (int i = 0; i < MBV; ++i) acc[j][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  if (nk > 0) {
-    const bf16x8_t* wp[WPW];
-    int wsd[WPW];  // k-step stride of each staged block's fragments
-#pragma unroll
-    for (int j = 0; j < WPW; ++j) {
-      const int nb = wb0 + min(WPW * wave + j, wbc - 1);
-      wp[j] = W + wfrag(nb, kb0, nbt, kbt) * 64 + lane;
-      wsd[j] = wgroup_blocks(nb, nbt) * 64;
-    }
-    const bf16x8_t* xp[MBV];
-#pragma unroll
-    for (int i = 0; i < MBV; ++i) xp[i] = XF + ((size_t)kb0 * Mb + min(MBV * wave + i, Mb - 1)) * 64 + lane;
-    const size_t xstride = (size_t)Mb * 64;
-    static_assert(6 % XD == 0 && 6 % WD == 0 && WD >= 3, "the k-step loop is unrolled by 6");
-    bf16x8_t wg[WD][WPW], xr[XD][MBV], wf[2][NBG];
-    auto load_w = [&](int slot, int st) {
-      const size_t kk = (size_t)min(st, nk - 1);
-#pragma unroll
-      for (int j = 0; j < WPW; ++j) wg[slot][j] = __builtin_nontemporal_load(wp[j] + kk * wsd[j]);
-    };
-    auto store_w = [&](int buf, int slot) {
-#pragma unroll
-      for (int j = 0; j < WPW; ++j) wl[buf][WPW * wave + j][lane] = wg[slot][j];
-    };
-    auto read_w = [&](int reg, int buf) {
-#pragma unroll
-      for (int j = 0; j < NBG; ++j) wf[reg][j] = wl[buf][j][lane];
-    };
-    auto load_x = [&](int slot, int st) {
-      const size_t kk = (size_t)min(st, nk - 1);
-#pragma unroll
-      for (int i = 0; i < MBV; ++i) xr[slot][i] = xp[i][kk * xstride];
-    };
-    // W(k) passes through global register slot k % WD, LDS buffer k % 2 and fragment registers wf[k % 2].
-    // k-step st multiplies wf[st % 2] (read from LDS during step st - 1) with activation slot st % XD, and
-    // meanwhile reads W(st + 1) out of LDS, writes W(st + 2) into the LDS buffer W(st) came from (every wave
-    // finished reading it before the barrier that ended step st - 1), loads W(st + 2 + WD) into the freed
-    // register slot and X(st + XD) into its slot.  WD - 2 steps of weights stay in flight; one barrier per
-    // step.
-#pragma unroll
-    for (int d = 0; d < WD; ++d) load_w(d, d);
-#pragma unroll
-    for (int d = 0; d < XD; ++d) load_x(d, d);
-    store_w(0, 0);
-    store_w(1, 1);
-    load_w(0, WD);
-    load_w(1, WD + 1);
-    lds_barrier();
-    read_w(0, 0);
-    lds_barrier();  // every wave holds W(0) before step 0 overwrites LDS buffer 0
-    for (int s0 = 0; s0 < nk; s0 += 6) {
-#pragma unroll
-      for (int u = 0; u < 6; ++u) {
-        const int st = s0 + u;
-        read_w((u + 1) & 1, (u + 1) & 1);
-        store_w(u & 1, (u + 2) % WD);
-        load_w((u + 2) % WD, st + 2 + WD);
-        if (st < nk) {
-#pragma unroll
-          for (int j = 0; j < NBG; ++j)
-#pragma unroll
-            for (int i = 0; i < MBV; ++i)
-              acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[u & 1][j], xr[u % XD][i], acc[j][i], 0, 0, 0);
-        }
-        load_x(u % XD, st + XD);
-        lds_barrier();
-      }
-    }
-  }
-  // D layout of the 16x16 MFMA: lane holds rows 4*(lane/16)+r (weight rows n) of column lane%16 (row m of X)
-  float* o = out + (size_t)blockIdx.y * M * N;
-#pragma unroll
-  for (int j = 0; j < NBG; ++j) {
-    if (j >= wbc) continue;
-    const int n = (wb0 + j) * 16 + 4 * (lane >> 4);
-#pragma unroll
-    for (int i = 0; i < MBV; ++i) {
-      const int m = (MBV * wave + i) * 16 + (lane & 15);
+      const int m = (mb0 + wm * MBW + i) * 16 + (lane & 15);
       if (m >= M) continue;
       if constexpr (SWI) {
         // rows n, n+1 are (gate, up) of output f = n/2; rows n+2, n+3 of output f + 1
@@ -656,46 +525,99 @@ int device_cus() {
   return cached[dev];
 }
 
-// Tile kernel grid: (padded N tiles) x (M tiles) workgroups in XCD-aware order, K splits in y.
-int tile_m_tiles(int M) { return ((M + 15) / 16 + kTileMB - 1) / kTileMB; }
-int tile_n_tiles(int N) { return (N / 16 + kTileNB * kTileWaves - 1) / (kTileNB * kTileWaves); }
-int tile_groups(int M, int N) { return (tile_n_tiles(N) + 7) / 8 * 8 * tile_m_tiles(M); }
+// Tiles of k_gemm_pp (weight blocks x activation blocks), with the time of one k-step when every CU runs one
+// (us, fitted over 1-8 splits of the 7B, 14B and 72B projections at 72 to 4,096 rows).
+struct Tile {
+  int tn, tm;
+  float step;
+};
+enum { T_10x8, T_16x8, T_8x16, T_10x16, T_16x16, T_20x16, kTiles };
+constexpr Tile kTile[kTiles] = {{10, 8, 0.305f}, {16, 8, 0.373f}, {8, 16, 0.383f}, {10, 16, 0.468f}, {16, 16, 0.679f}, {20, 16, 0.827f}};
 
-// Tall decode batches (129..256 rows, one activation tile) take k_gemm_wlds on a balanced grid of
-// workgroups with at most kWldsBlocks weight blocks each, about one per CU per K split.
-constexpr int kTallMinRows = 129, kTallMaxRows = 256;
-constexpr int kTallWgBlocks = kWldsBlocks;
-bool tall_batch(int M) { return M >= kTallMinRows && M <= kTallMaxRows; }
-int tall_groups(int N, int splits) {
-  const int nbt = N / 16;
-  const int need = (nbt + kTallWgBlocks - 1) / kTallWgBlocks;
-  return std::min(nbt, std::max(need, device_cus() / splits));
+struct TilePlan {
+  int tile, splits, nt;  // nt: N tiles (they share the weight blocks out evenly)
+};
+
+int kslice_splits(int K, int splits) {  // splits that K slices of kslice_for(K, splits) come to
+  const int ks = kslice_for(K, splits);
+  return (K + ks - 1) / ks;
 }
 
-// Decode-sized batches (at most kTileDecodeRows rows) run one wave per SIMD whatever the register budget, so
-// they take the deeper activation staging (14B at 256 rows: QKV -6%, O -8%, gate/up -3.5%); prefill keeps
-// two waves per SIMD with three stages (7B prefill gate/up -3% against two).
-constexpr int kTileDecodeRows = 256;
-template <bool SWI>
-void launch_tile_kernel(hipStream_t s, int splits, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N,
-                        int K, uint16_t* h) {
-  const int kslice = kslice_for(K, splits);
-  const dim3 block(64 * kTileWaves);
-  if (tall_batch(M)) {
-    const dim3 grid(tall_groups(N, splits), splits);
-    hipLaunchKernelGGL((k_gemm_wlds<SWI, 3, 3>), grid, block, 0, s, x, w, out, M, N, K, kslice, h);
-  } else if (M <= kTileDecodeRows) {
-    const dim3 grid(tile_groups(M, N), splits);
-    hipLaunchKernelGGL((k_gemm_tile<kTileNB, kTileMB, SWI, 6, 1>), grid, block, 0, s, x, w, out, M, N, K, kslice, h);
-  } else {
-    const dim3 grid(tile_groups(M, N), splits);
-    hipLaunchKernelGGL((k_gemm_tile<kTileNB, kTileMB, SWI, 3, 2>), grid, block, 0, s, x, w, out, M, N, K, kslice, h);
+// Tile and K splits of a batch of more than 64 rows: the least of (rounds of one workgroup per CU x k-steps x
+// the tile's step time + about 6 us a round, against the weights' stream, + what the partials cost to write
+// and read).  A round's last workgroups leave CUs idle, so the tile that divides a shape evenly wins (4,096 x
+// 5,120 rows: 16 x 16 tiles of 20 x 16 blocks are one round of 256, 16 x 20 of 16 x 16 two; 172 against 235 us).
+// Over 162 (projection, rows) pairs the choice is on average 1.5% above the best of all tiles and splits.
+// Which tiles are looked at: up to 128 rows those with one 128-row activation tile (two to four times fewer
+// multiplications of padding rows); up to 256 rows the wide ones only where K is not split, since with several
+// splits their few workgroups do not fill the chip.  Up to 384 rows a third 128-row tile wastes less than a
+// second 256-row one (300 rows, 72B gate/up 344 against 384 us).
+TilePlan tile_plan(int M, int N, int K, int smin, int smax) {
+  const int nbt = N / 16, mb = (M + 15) / 16, cus = device_cus(), per_xcd = std::max(1, cus / 8);
+  const bool single = smax == 1;
+  TilePlan best{T_16x16, 1, 1};
+  float best_cost = 3e38f;
+  for (int t = 0; t < kTiles; ++t) {
+    bool look;
+    if (M <= 128) look = t == T_10x8 || (t == T_16x8 && single);
+    else if (M <= 256) look = single ? t >= T_8x16 : (t == T_10x8 || t == T_8x16);
+    else look = t >= T_8x16 || (t == T_16x8 && M <= 384);
+    if (!look) continue;
+    const Tile& T = kTile[t];
+    const int mt = (mb + T.tm - 1) / T.tm, need = (nbt + T.tn - 1) / T.tn;
+    for (int s = smin; s <= smax; ++s) {
+      if (kslice_splits(K, s) != s) continue;
+      const int nk = kslice_for(K, s) / 32;
+      const float stream = (float)N * K * 2 / 5.45e6f;
+      const float part = single ? 0.f : 1.6f * s * (float)M * N * 4 / 4.5e6f;
+      auto cost = [&](int nt) {
+        const int rounds = ((mt * nt + 7) / 8 * s + per_xcd - 1) / per_xcd;
+        const float step = std::max(T.step, (float)nbt / nt * 1024 / 41e3f / mt);
+        const float tm = rounds * (nk * step + 6.f);
+        return std::cbrt(tm * tm * tm + stream * stream * stream) + part;
+      };
+      const float c = cost(need);
+      if (c < best_cost) {
+        best_cost = c;
+        best = {t, s, need};
+      }
+      // one activation tile of 128 rows: bound by the weights' stream, so every CU of the last round gets a share
+      const int rounds = ((mt * need + 7) / 8 * s + per_xcd - 1) / per_xcd;
+      const int spread = std::min(nbt, rounds * cus / s);
+      if (T.tm == 8 && mt == 1 && spread > need) {
+        const float cs = cost(spread);
+        if (cs <= best_cost) {
+          best_cost = cs;
+          best = {t, s, spread};
+        }
+      }
+    }
   }
+  return best;
 }
 
-hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
-                       int splits) {
-  launch_tile_kernel<false>(s, splits, x, w, out, M, N, K, nullptr);
+template <int NB, int MBW, int WN, int WM, int NS, bool SWI>
+void launch_pp(hipStream_t s, const TilePlan& p, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
+               uint16_t* h) {
+  const int mt = ((M + 15) / 16 + MBW * WM - 1) / (MBW * WM);
+  const dim3 grid((unsigned)(mt * p.nt + 7) / 8 * 8, p.splits);
+  hipLaunchKernelGGL((k_gemm_pp<NB, MBW, WN, WM, NS, SWI>), grid, dim3(512), 0, s, x, w, out, M, N, K,
+                     kslice_for(K, p.splits), p.nt, h);
+}
+
+// LDS of a tile: NS x (TN + TM) KB, at most 160
+template <bool SWI>
+hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K, int splits,
+                       uint16_t* h) {
+  const TilePlan p = tile_plan(M, N, K, splits, splits);
+  switch (p.tile) {
+    case T_10x8: launch_pp<5, 2, 2, 4, 6, SWI>(s, p, x, w, out, M, N, K, h); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 5, SWI>(s, p, x, w, out, M, N, K, h); break;
+    case T_8x16: launch_pp<4, 4, 2, 4, 5, SWI>(s, p, x, w, out, M, N, K, h); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 5, SWI>(s, p, x, w, out, M, N, K, h); break;
+    case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI>(s, p, x, w, out, M, N, K, h); break;
+    default: launch_pp<5, 8, 4, 2, 4, SWI>(s, p, x, w, out, M, N, K, h); break;
+  }
   return hipGetLastError();
 }
 
@@ -890,30 +812,7 @@ hipError_t launch_gemm_swiglu_q4(hipStream_t s, const void* X, const void* W, in
 int gemm_splits(int dtype, int M, int N, int K, int max_splits) {
   if (dtype != ROLLOUT_DTYPE_BF16 || max_splits <= 1) return 1;
   if (M <= kRingMaxRows) return ring_splits(N, K, max_splits);
-  const int nwg = tile_m_tiles(M) * tile_n_tiles(N);
-  int s;
-  if (tall_batch(M)) {
-    // one activation tile: K splits until the 128-row weight tiles of all splits fill the 256 CUs once
-    // (a partial costs M x N x 4 bytes, so no more than that)
-    const int tiles = (N / 16 + kTallWgBlocks - 1) / kTallWgBlocks;
-    s = std::max(1, std::min(std::min(max_splits, std::max(1, K / 256)), 256 / tiles));
-  } else if (M <= 256) {
-    // decode-sized batches: workgroup x of a split runs on XCD x % 8, which holds N tiles nt % 8 == j for
-    // every M tile.  Split K until the busiest XCD holds one workgroup per CU (32); with long K slices
-    // (> 64 k-steps) two per CU.  Fewer splits leave CUs idle, more add partial-sum traffic and a second
-    // round of workgroups on the busiest XCD.
-    const int per_xcd = tile_m_tiles(M) * ((tile_n_tiles(N) + 7) / 8);
-    const int smax = std::max(1, std::min(max_splits, K / 256));
-    s = std::max(1, std::min(smax, 32 / per_xcd));
-    if (K / 32 / s > 64) s = std::max(s, std::min(smax, 64 / per_xcd));
-  } else {
-    // MFMA-bound batches: enough K splits for ~1.5 workgroups per CU, K slices of at least 512
-    s = (384 + nwg - 1) / nwg;
-    s = std::min(s, std::max(1, K / 512));
-    s = std::max(1, std::min(s, max_splits));
-  }
-  const int ks = kslice_for(K, s);
-  return (K + ks - 1) / ks;
+  return tile_plan(M, N, K, 1, std::max(1, std::min(max_splits, K / 256))).splits;
 }
 
 hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const void* W, float* out, int M, int N,
@@ -932,16 +831,14 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const v
       return launch_ring_balanced<false, 1>(s, x, w, out, M, N, K, kBalWavesPerCU * device_cus(), nullptr);
     return launch_ring_split(s, x, w, out, M, N, K, splits);
   }
-  return launch_tile(s, x, w, out, M, N, K, splits);
+  return launch_tile<false>(s, x, w, out, M, N, K, splits, nullptr);
 }
 
 hipError_t launch_gemm_swiglu(hipStream_t s, const void* X, const void* W, int M, int N, int K, void* h) {
   if (M <= 0) return hipSuccess;
   if (N % 32 || K % 32) return hipErrorInvalidValue;
-  if (M > kRingMaxRows) {  // larger batches: the tile kernel with the same epilogue, one K split
-    launch_tile_kernel<true>(s, 1, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, (uint16_t*)h);
-    return hipGetLastError();
-  }
+  if (M > kRingMaxRows)  // larger batches: the same epilogue on k_gemm_pp, one K split
+    return launch_tile<true>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, 1, (uint16_t*)h);
   if (use_balanced_swiglu(M, N))
     return launch_ring_balanced<true, 2>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, device_cus(),
                                          (uint16_t*)h);

@@ -277,10 +277,19 @@ __device__ __forceinline__ void dma_lds16(const void* src, void* dst) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
 }
 
-// The wave's outstanding transfers into LDS and LDS accesses are complete, then every wave has arrived.
-__device__ __forceinline__ void dma_wait_barrier() {
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// The same with a wave-uniform base (src) and each lane's byte offset.
+__device__ __forceinline__ void dma_lds16_at(const void* src, uint32_t offset, void* dst) {
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)dst);
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(src), "s"(lds) : "memory");
 }
+
+// All but the wave's latest N transfers into LDS and all its LDS accesses are complete, then every wave has arrived.
+template <int N = 0>
+__device__ __forceinline__ void dma_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void phase_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

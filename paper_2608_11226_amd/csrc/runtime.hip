@@ -124,18 +124,10 @@ int prefill_chunk_rows(int max_prompt_len) {
   return std::max(max_prompt_len, kPrefillRows / max_prompt_len * max_prompt_len);
 }
 
+// Split-K workspace: one whole output of the widest projection over all R rows (two for int4, whose larger
+// batches run two GEMMs).  Smaller batches and narrower projections split K as far as it goes.
 size_t max_part_elems(const Dims& D, int R) {
-  size_t best = 0;
-  const int Ns[4] = {D.nqkv, D.d, 2 * D.ff, D.d};
-  const int Ks[4] = {D.d, D.qd, D.d, D.ff};
-  for (int M = 1; M <= R; ++M)
-    for (int j = 0; j < 4; ++j) {
-      int s = gemm_splits(D.dtype, M, Ns[j], Ks[j], kMaxSplits);
-      if (D.wq4)  // int4: the ring's splits, or two bf16 GEMMs (hi and lo) of up to half the splits each
-        s = std::max(gemm_splits_q4(M, Ns[j], Ks[j], kMaxSplits), 2 * gemm_splits(D.dtype, M, Ns[j], Ks[j], kMaxSplits / 2));
-      best = std::max(best, (size_t)s * (size_t)M * (size_t)Ns[j]);
-    }
-  return best;
+  return (size_t)(D.wq4 ? 2 : 1) * R * std::max(std::max(D.nqkv, D.d), 2 * D.ff);
 }
 
 // Layout of weights and work buffers for S sequences in flight; the KV pool follows work_end.
@@ -348,9 +340,10 @@ struct Scope {
 rollout_status gemm(rollout_ctx* c, const void* X, const void* W, float* out, int M, int N, int K, int max_splits,
                     int* splits_out) {
   const Dims& D = c->D;
+  // as many splits as the workspace holds (max_splits 1: the output is not the workspace)
+  if (max_splits > 1) max_splits = (int)std::min<size_t>(max_splits, c->Lo.part_elems / (D.wq4 ? 2 : 1) / ((size_t)M * N));
+  if (max_splits < 1) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
   const int s = gemm_splits(D.dtype, M, N, K, max_splits);
-  if ((size_t)s * M * N > c->Lo.part_elems && out == c->at<float>(c->Lo.part))
-    return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
   const double eb = (double)elem_bytes(D.dtype);
   Scope sc(c, 0, (double)N * K * eb + (double)M * K * eb + (double)M * N * 4, 2.0 * M * N * K);
   HIP_TRY(c, launch_gemm(c->stream, D.dtype, X, K, W, out, M, N, K, s), "gemm");

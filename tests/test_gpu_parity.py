@@ -339,6 +339,29 @@ def test_bf16_prefill_attention_tiles(shape, blk, n_prompts, P):
     eng.close()
 
 
+# row counts around the tile choices of the GEMM for more than 64 rows (128- and 256-row activation tiles, two
+# and three of them), K and N that leave odd k-steps, short K splits and partial weight tiles
+TILE_ROWS = [(1, 65), (1, 128), (3, 43), (1, 256), (1, 257), (5, 77), (1, 513), (9, 117)]
+TILE_BF16 = (1, 544, 10, 2, 64, 1056, 2064, 1e6)
+
+
+@pytest.mark.parametrize("n_prompts,P", TILE_ROWS)
+def test_bf16_tile_gemm_rows(n_prompts, P):
+    log(f"bf16 tile GEMM rows {n_prompts} x {P}")
+    cfg = R.model_config(TILE_BF16, R.DTYPE_BF16, P, 2, n_prompts)
+    eng = R.Engine(cfg)
+    model = OracleModel(shape_of(cfg), mode="bf16")
+    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=49)
+    want = np.stack([model.prefill(p)[1] for p in prompts])
+    logits = torch.empty((n_prompts, cfg.vocab), dtype=torch.float32, device="cuda:0")
+    R.rollout_prefill(eng.ctx, to_dev(prompts, torch), n_prompts, P, 1, logits)
+    eng.synchronize()
+    err = float(np.max(np.abs(logits.cpu().numpy() - want)))
+    log(f"  max abs logit error {err:.4g}")
+    assert err <= 3e-2  # the bf16 contract's bound, as in the tests above
+    eng.close()
+
+
 @pytest.mark.parametrize("shared", ["0", "2"])
 def test_bf16_gqa7_context_beyond_4096_tokens_teacher_forced(shared, monkeypatch):
     # A context of more than 256 blocks of 16 (4,096 tokens): the decode attention's workgroup of 256
