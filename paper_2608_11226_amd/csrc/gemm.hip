@@ -41,8 +41,8 @@
 // weights are never rounded.  The codes enter the MFMA as exact bf16 integers
 // (128 + q); a workgroup of four waves shares each group's activation
 // fragments and their sums through LDS.  Larger batches with int4 weights
-// dequantise a projection into two bf16 tile matrices (hi + lo) and take
-// k_gemm_pp twice.
+// write a projection's integers q - z (exact in bf16) into fragments first and take k_gemm_pp on those,
+// which scales every group's sum in fp32.
 //
 // fp32 path: a plain LDS-tiled VALU GEMM over row-major X and W (the fp32
 // path exists for exact parity on small models, not for speed).
@@ -90,13 +90,21 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 //   512 rows:   7B QKV 64 -> 31, down 95 -> 73, gate/up 147 -> 102;  256 rows: 7B gate/up 109 -> 71,
 //   14B head 424 -> 369;  128 rows: 14B gate/up 84 -> 62, 7B down 45 -> 38, 7B head 248 -> 234
 // All sums are bit-equal to the previous kernels' at equal splits (k order).
-template <int NB, int MBW, int WN, int WM, int NS, bool SWI>
+//
+// Q4 (int4 weights): W holds the integers q - z, exact in bf16 (k_dequant_q4), and Ws the fp32 scale of every
+// (16-row block, 128-input group, row).  A group's four k-steps sum into P, and acc += s * P in fp32 while the
+// wave reads the next step's fragments, so the weights are never rounded and the vector work runs beside the
+// other group's MFMAs.  The tile's scales of a group ride in the ring as one more fragment per k-step.  Half
+// of the previous form's MFMAs (two GEMMs over bf16 hi + lo tiles of the dequantised weight) and half of its
+// dequantised bytes; needs twice the accumulators, so wave tiles stay at 20 MFMA tiles.
+template <int NB, int MBW, int WN, int WM, int NS, bool SWI, bool Q4>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, float* __restrict__ out, int M, int N,
-               int K, int kslice, int Nt, uint16_t* __restrict__ h) {
-  constexpr int TN = NB * WN, TM = MBW * WM, FR = TN + TM;
+void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, const floatx4_t* __restrict__ Ws,
+               float* __restrict__ out, int M, int N, int K, int kslice, int Nt, uint16_t* __restrict__ h) {
+  constexpr int TN = NB * WN, TM = MBW * WM, FR = TN + TM + (Q4 ? 1 : 0);
   constexpr int PER = (FR + 7) / 8;  // fragments a wave transfers per k-step (surplus ones repeat the last)
   static_assert(WN * WM == 8 && NS >= 3, "eight waves");
+  static_assert(!Q4 || (NS % 4 == 0 && TN <= 16), "a group is four unrolled k-steps; its scales fit one fragment");
   __shared__ bf16x8_t ls[NS][FR][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -120,6 +128,7 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
   // the wave's fragments of a k-step (blocks past the tile's or the matrix's repeat the last one)
   const char* fb[PER];
   uint32_t fs[PER];  // bytes from one k-step to the next
+  const uint32_t soff = Q4 ? (uint32_t)min(lane >> 2, wbc - 1) * (uint32_t)(kbt >> 2) * 64 + (lane & 3) * 16 : 0;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int f = min(PER * wave + i, FR - 1);
@@ -127,16 +136,37 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
       const int nb = wb0 + min(f, wbc - 1);
       fb[i] = (const char*)(W + wfrag(nb, kb0, nbt, kbt) * 64);
       fs[i] = wgroup_blocks(nb, nbt) * 1024;
-    } else {
+    } else if (f < TN + TM) {
       fb[i] = (const char*)(XF + ((size_t)kb0 * Mb + min(mb0 + f - TN, Mb - 1)) * 64);
       fs[i] = (uint32_t)Mb * 1024;
+    } else {  // scales: 64 bytes per (block, group); lane = 4 * block + four rows
+      fb[i] = (const char*)(Ws + ((size_t)wb0 * (kbt >> 2) + (kb0 >> 2)) * 4);
+      fs[i] = 64;
     }
   }
   auto transfer = [&](int slot, int st) {  // steps past the last repeat it into slots that are not read again
     const size_t kk = (size_t)min(st, nk - 1);
 #pragma unroll
-    for (int i = 0; i < PER; ++i)
-      dma_lds16_at(fb[i] + kk * fs[i], lane * 16, &ls[slot][min(PER * wave + i, FR - 1)][0]);
+    for (int i = 0; i < PER; ++i) {
+      const int f = min(PER * wave + i, FR - 1);
+      if (Q4 && f == FR - 1)
+        dma_lds16_at(fb[i] + (kk >> 2) * fs[i], soff, &ls[slot][f][0]);
+      else
+        dma_lds16_at(fb[i] + kk * fs[i], lane * 16, &ls[slot][f][0]);
+    }
+  };
+  floatx4_t P[Q4 ? NB : 1][Q4 ? MBW : 1];
+  auto scale_group = [&](int slot) {  // acc += s * P with the scales of the group that k-step's slot belongs to
+    if constexpr (Q4) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const floatx4_t sc = reinterpret_cast<const floatx4_t*>(&ls[slot][FR - 1][0])[(wn * NB + j) * 4 + (lane >> 4)];
+#pragma unroll
+        for (int i = 0; i < MBW; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[j][i][r] = fmaf(sc[r], P[j][i][r], acc[j][i][r]);
+      }
+    }
   };
   if (nk > 0) {
     bf16x8_t wf[NB], xf[MBW];
@@ -153,13 +183,20 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
           for (int j = 0; j < NB; ++j) wf[j] = ls[u][wn * NB + j][lane];
 #pragma unroll
           for (int i = 0; i < MBW; ++i) xf[i] = ls[u][TN + wm * MBW + i][lane];
+          // the group that ended with step st - 1 (its slot is refilled after this step's multiply phase)
+          if (Q4 && u % 4 == 0 && st > 0) scale_group((u + NS - 1) % NS);
           dma_wait_barrier<(NS - 3) * PER>();
           __builtin_amdgcn_s_setprio(1);
 #pragma unroll
           for (int i = 0; i < MBW; ++i)
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
-              acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[j][i], 0, 0, 0);
+            for (int j = 0; j < NB; ++j) {
+              if constexpr (Q4)
+                P[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    wf[j], xf[i], u % 4 == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : P[j][i], 0, 0, 0);
+              else
+                acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[j][i], 0, 0, 0);
+            }
           __builtin_amdgcn_s_setprio(0);
           __builtin_amdgcn_sched_barrier(0);  // the MFMAs stay in their phase
           phase_barrier();
@@ -168,6 +205,7 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
       }
     }
     if (wave < 4) phase_barrier();  // as many barriers as the second group
+    if constexpr (Q4) scale_group((nk - 1) % NS);  // the last group
     dma_wait();                     // no transfer outlives the workgroup's LDS
   }
   // D layout of the 16x16 MFMA: lane holds rows 4*(lane/16)+r (weight rows n) of column lane%16 (row m of X)
@@ -538,10 +576,8 @@ struct TilePlan {
   int tile, splits, nt;  // nt: N tiles (they share the weight blocks out evenly)
 };
 
-int kslice_splits(int K, int splits) {  // splits that K slices of kslice_for(K, splits) come to
-  const int ks = kslice_for(K, splits);
-  return (K + ks - 1) / ks;
-}
+// K slice of one split (int4: whole groups of 128 inputs)
+int tile_kslice(int K, int splits, bool q4) { return q4 ? (kslice_for(K, splits) + 127) / 128 * 128 : kslice_for(K, splits); }
 
 // Tile and K splits of a batch of more than 64 rows: the least of (rounds of one workgroup per CU x k-steps x
 // the tile's step time + about 6 us a round, against the weights' stream, + what the partials cost to write
@@ -552,22 +588,24 @@ int kslice_splits(int K, int splits) {  // splits that K slices of kslice_for(K,
 // multiplications of padding rows); up to 256 rows the wide ones only where K is not split, since with several
 // splits their few workgroups do not fill the chip.  Up to 384 rows a third 128-row tile wastes less than a
 // second 256-row one (300 rows, 72B gate/up 344 against 384 us).
-TilePlan tile_plan(int M, int N, int K, int smin, int smax) {
+// int4 weights take the tiles of at most 20 MFMA tiles a wave, and K slices of whole groups.
+TilePlan tile_plan(int M, int N, int K, int smin, int smax, bool q4 = false) {
   const int nbt = N / 16, mb = (M + 15) / 16, cus = device_cus(), per_xcd = std::max(1, cus / 8);
   const bool single = smax == 1;
-  TilePlan best{T_16x16, 1, 1};
+  TilePlan best{T_8x16, 1, 1};
   float best_cost = 3e38f;
   for (int t = 0; t < kTiles; ++t) {
     bool look;
     if (M <= 128) look = t == T_10x8 || (t == T_16x8 && single);
     else if (M <= 256) look = single ? t >= T_8x16 : (t == T_10x8 || t == T_8x16);
-    else look = t >= T_8x16 || (t == T_16x8 && M <= 384);
-    if (!look) continue;
+    else look = t >= T_8x16 || (t == T_16x8 && (M <= 384 || q4));
+    if (!look || (q4 && t >= T_16x16)) continue;
     const Tile& T = kTile[t];
     const int mt = (mb + T.tm - 1) / T.tm, need = (nbt + T.tn - 1) / T.tn;
     for (int s = smin; s <= smax; ++s) {
-      if (kslice_splits(K, s) != s) continue;
-      const int nk = kslice_for(K, s) / 32;
+      const int ks = tile_kslice(K, s, q4);
+      if ((K + ks - 1) / ks != s) continue;
+      const int nk = ks / 32;
       const float stream = (float)N * K * 2 / 5.45e6f;
       const float part = single ? 0.f : 1.6f * s * (float)M * N * 4 / 4.5e6f;
       auto cost = [&](int nt) {
@@ -596,27 +634,40 @@ TilePlan tile_plan(int M, int N, int K, int smin, int smax) {
   return best;
 }
 
-template <int NB, int MBW, int WN, int WM, int NS, bool SWI>
-void launch_pp(hipStream_t s, const TilePlan& p, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
-               uint16_t* h) {
+template <int NB, int MBW, int WN, int WM, int NS, bool SWI, bool Q4>
+void launch_pp(hipStream_t s, const TilePlan& p, const bf16x8_t* x, const bf16x8_t* w, const floatx4_t* ws, float* out,
+               int M, int N, int K, uint16_t* h) {
   const int mt = ((M + 15) / 16 + MBW * WM - 1) / (MBW * WM);
   const dim3 grid((unsigned)(mt * p.nt + 7) / 8 * 8, p.splits);
-  hipLaunchKernelGGL((k_gemm_pp<NB, MBW, WN, WM, NS, SWI>), grid, dim3(512), 0, s, x, w, out, M, N, K,
-                     kslice_for(K, p.splits), p.nt, h);
+  hipLaunchKernelGGL((k_gemm_pp<NB, MBW, WN, WM, NS, SWI, Q4>), grid, dim3(512), 0, s, x, w, ws, out, M, N, K,
+                     tile_kslice(K, p.splits, Q4), p.nt, h);
 }
 
-// LDS of a tile: NS x (TN + TM) KB, at most 160
+// LDS of a tile: NS x (TN + TM) KB (int4 one more fragment), at most 160
 template <bool SWI>
 hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K, int splits,
                        uint16_t* h) {
   const TilePlan p = tile_plan(M, N, K, splits, splits);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 6, SWI>(s, p, x, w, out, M, N, K, h); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 5, SWI>(s, p, x, w, out, M, N, K, h); break;
-    case T_8x16: launch_pp<4, 4, 2, 4, 5, SWI>(s, p, x, w, out, M, N, K, h); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 5, SWI>(s, p, x, w, out, M, N, K, h); break;
-    case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI>(s, p, x, w, out, M, N, K, h); break;
-    default: launch_pp<5, 8, 4, 2, 4, SWI>(s, p, x, w, out, M, N, K, h); break;
+    case T_10x8: launch_pp<5, 2, 2, 4, 6, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+    case T_8x16: launch_pp<4, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+    case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+    default: launch_pp<5, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+  }
+  return hipGetLastError();
+}
+
+template <bool SWI>
+hipError_t launch_tile_q4(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, const floatx4_t* ws, float* out, int M,
+                          int N, int K, int splits, uint16_t* h) {
+  const TilePlan p = tile_plan(M, N, K, splits, splits, true);
+  switch (p.tile) {
+    case T_10x8: launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
+    default: launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
   }
   return hipGetLastError();
 }
@@ -784,7 +835,8 @@ hipError_t launch_q4(hipStream_t s, const bf16x8_t* x, const void* w, float* out
 }  // namespace
 
 int gemm_splits_q4(int M, int N, int K, int max_splits) {
-  if (M > kRingMaxRows || max_splits <= 1) return 1;
+  if (max_splits <= 1) return 1;
+  if (M > kRingMaxRows) return tile_plan(M, N, K, 1, std::max(1, std::min(max_splits, K / 256)), true).splits;
   const int groups = (N / 16 + 4 * q4_blocks(M) - 1) / (4 * q4_blocks(M));  // workgroups per K split
   // as for the bf16 split projections: the fewest splits that fill 80% of the CUs, at most one workgroup
   // per CU (72B: QKV 3, O and down 4 instead of 7-8 splits at two workgroups per CU; 72B int4 rollout +1%)
@@ -795,6 +847,23 @@ int gemm_splits_q4(int M, int N, int K, int max_splits) {
   s = std::max(1, std::min(s, max_splits));
   const int ks = kslice_q4(K, s);
   return (K + ks - 1) / ks;
+}
+
+// W: the packed matrix (its scales are read from there); Wi: its integers q - z (launch_dequant_q4)
+hipError_t launch_gemm_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, float* out, int M, int N,
+                               int K, int splits) {
+  if (M <= 0) return hipSuccess;
+  if (M <= kRingMaxRows || N % 16 || K % 128 || splits < 1) return hipErrorInvalidValue;
+  return launch_tile_q4<false>(s, (const bf16x8_t*)X, (const bf16x8_t*)Wi,
+                               (const floatx4_t*)((const char*)W + q4_code_bytes(N, K)), out, M, N, K, splits, nullptr);
+}
+
+hipError_t launch_gemm_swiglu_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, int M, int N, int K,
+                                      void* h) {
+  if (M <= 0) return hipSuccess;
+  if (M <= kRingMaxRows || N % 32 || K % 128) return hipErrorInvalidValue;
+  return launch_tile_q4<true>(s, (const bf16x8_t*)X, (const bf16x8_t*)Wi,
+                              (const floatx4_t*)((const char*)W + q4_code_bytes(N, K)), nullptr, M, N, K, 1, (uint16_t*)h);
 }
 
 hipError_t launch_gemm_q4(hipStream_t s, const void* X, const void* W, float* out, int M, int N, int K, int splits) {

@@ -72,8 +72,8 @@ size_t q4_code_bytes(int rows, int cols);
 size_t q4_sz_bytes(int rows, int cols);
 hipError_t launch_synth_q4(hipStream_t s, void* dst, const WeightDesc& w, uint64_t seed, double std_);
 hipError_t launch_export_q4(hipStream_t s, const void* src, const WeightDesc& w, int which, int rows, float* out);
-// bf16 MFMA-operand tiles hi = bf16(w), lo = bf16(w - hi) of an int4 matrix (each rows * cols bf16)
-hipError_t launch_dequant_q4(hipStream_t s, const void* src, int rows, int cols, void* dst_hi, void* dst_lo);
+// the integers q - z of an int4 matrix as bf16 fragments in the weight layout (rows * cols bf16)
+hipError_t launch_dequant_q4(hipStream_t s, const void* src, int rows, int cols, void* dst);
 hipError_t launch_export(hipStream_t s, const void* src, int dtype, const WeightDesc& w, int which, int rows,
                          float* out);
 
@@ -85,13 +85,18 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const v
 // Gate/up projection with SwiGLU applied to its own output (bf16, one K split;
 // the ring kernel up to 64 rows, the tile kernel above): W holds gate row i at
 // physical row 2i and up row i at 2i + 1; h[m][i] = silu(gate) * up in the down
-// projection's operand layout.  int4 weights: the int4 ring, M <= kSwigluMaxRows.
+// projection's operand layout.
 constexpr int kSwigluMaxRows = 64;
 hipError_t launch_gemm_swiglu(hipStream_t s, const void* X, const void* W, int M, int N, int K, void* h);
-// The same two GEMMs over an int4 weight matrix (M <= 64; K a multiple of 128; partial splits as above).
+// The same two GEMMs over an int4 weight matrix (K a multiple of 128; partial splits as above): the packed
+// matrix for M <= 64, above that with the matrix's integers Wi as launch_dequant_q4 leaves them.
 int gemm_splits_q4(int M, int N, int K, int max_splits);
 hipError_t launch_gemm_q4(hipStream_t s, const void* X, const void* W, float* out, int M, int N, int K, int splits);
 hipError_t launch_gemm_swiglu_q4(hipStream_t s, const void* X, const void* W, int M, int N, int K, void* h);
+hipError_t launch_gemm_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, float* out, int M, int N,
+                               int K, int splits);
+hipError_t launch_gemm_swiglu_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, int M, int N, int K,
+                                      void* h);
 
 hipError_t launch_embed(hipStream_t s, int dtype, const void* E, const int32_t* tokens, int tok_stride,
                         const int32_t* col, int M, int d, int V, float* x, int32_t* err);

@@ -124,11 +124,9 @@ int prefill_chunk_rows(int max_prompt_len) {
   return std::max(max_prompt_len, kPrefillRows / max_prompt_len * max_prompt_len);
 }
 
-// Split-K workspace: one whole output of the widest projection over all R rows (two for int4, whose larger
-// batches run two GEMMs).  Smaller batches and narrower projections split K as far as it goes.
-size_t max_part_elems(const Dims& D, int R) {
-  return (size_t)(D.wq4 ? 2 : 1) * R * std::max(std::max(D.nqkv, D.d), 2 * D.ff);
-}
+// Split-K workspace: one whole output of the widest projection over all R rows.  Smaller batches and narrower
+// projections split K as far as it goes.
+size_t max_part_elems(const Dims& D, int R) { return (size_t)R * std::max(std::max(D.nqkv, D.d), 2 * D.ff); }
 
 // Layout of weights and work buffers for S sequences in flight; the KV pool follows work_end.
 Layout make_layout(const Dims& D, int S, int max_prompt_len) {
@@ -188,9 +186,9 @@ Layout make_layout(const Dims& D, int S, int max_prompt_len) {
   Lo.err = take(64);
   Lo.cb = take((size_t)5 * S * 4);
   Lo.stopmap = take((size_t)(D.V + 31) / 32 * 4);
-  // int4: batches above the ring GEMM's rows multiply bf16 hi and lo copies of one projection at a time
+  // int4: batches above the ring GEMM's rows multiply the integers of one projection at a time, as bf16
   if (D.wq4)
-    Lo.wdq = take(std::max(std::max((size_t)D.nqkv * D.d, (size_t)D.d * D.qd), (size_t)2 * D.ff * D.d) * 4);
+    Lo.wdq = take(std::max(std::max((size_t)D.nqkv * D.d, (size_t)D.d * D.qd), (size_t)2 * D.ff * D.d) * 2);
   Lo.work_end = off;
   Lo.work_bytes = Lo.work_end - Lo.weights_end;
   Lo.kv_block_bytes = (size_t)D.L * D.nkv * 2 * D.blk * D.hd * eb;
@@ -341,7 +339,7 @@ rollout_status gemm(rollout_ctx* c, const void* X, const void* W, float* out, in
                     int* splits_out) {
   const Dims& D = c->D;
   // as many splits as the workspace holds (max_splits 1: the output is not the workspace)
-  if (max_splits > 1) max_splits = (int)std::min<size_t>(max_splits, c->Lo.part_elems / (D.wq4 ? 2 : 1) / ((size_t)M * N));
+  if (max_splits > 1) max_splits = (int)std::min<size_t>(max_splits, c->Lo.part_elems / ((size_t)M * N));
   if (max_splits < 1) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
   const int s = gemm_splits(D.dtype, M, N, K, max_splits);
   const double eb = (double)elem_bytes(D.dtype);
@@ -351,44 +349,47 @@ rollout_status gemm(rollout_ctx* c, const void* X, const void* W, float* out, in
   return ROLLOUT_OK;
 }
 
-// Gate/up GEMM with SwiGLU applied to its own output (bf16 weights: any M; int4: M <= kSwigluMaxRows).
+// int4 weights of a batch above the ring GEMM's rows: the matrix's integers into the work buffer
+rollout_status dequant(rollout_ctx* c, const void* W, int N, int K) {
+  Scope sc(c, 2, (double)(q4_code_bytes(N, K) + q4_sz_bytes(N, K)) + (double)N * K * 2, 0);
+  HIP_TRY(c, launch_dequant_q4(c->stream, W, N, K, c->at(c->Lo.wdq)), "dequantise");
+  return ROLLOUT_OK;
+}
+
+// Gate/up GEMM with SwiGLU applied to its own output.
 rollout_status gemm_swiglu(rollout_ctx* c, const void* X, const void* W, int M, int N, int K, void* h) {
   const double eb = (double)elem_bytes(c->D.dtype);
-  const double wb = c->D.wq4 ? (double)(q4_code_bytes(N, K) + q4_sz_bytes(N, K)) : (double)N * K * eb;
+  const bool tile_q4 = c->D.wq4 && M > kSwigluMaxRows;
+  rollout_status r;
+  if (tile_q4 && (r = dequant(c, W, N, K))) return r;
+  const double wb = c->D.wq4 && !tile_q4 ? (double)(q4_code_bytes(N, K) + q4_sz_bytes(N, K)) : (double)N * K * eb;
   Scope sc(c, 0, wb + (double)M * K * eb + (double)M * (N / 2) * eb, 2.0 * M * N * K);
-  if (c->D.wq4)
+  if (tile_q4)
+    HIP_TRY(c, launch_gemm_swiglu_q4_tile(c->stream, X, W, c->at(c->Lo.wdq), M, N, K, h), "gemm");
+  else if (c->D.wq4)
     HIP_TRY(c, launch_gemm_swiglu_q4(c->stream, X, W, M, N, K, h), "gemm");
   else
     HIP_TRY(c, launch_gemm_swiglu(c->stream, X, W, M, N, K, h), "gemm");
   return ROLLOUT_OK;
 }
 
-// A layer projection.  int4 matrices take the int4 ring GEMM for decode batches; larger batches
-// (prefill) dequantise the matrix into bf16 tiles first and take the bf16 GEMM.
+// A layer projection.  int4 matrices take the int4 ring GEMM for decode batches; larger batches write the
+// matrix's integers out first and take the tile GEMM on them.
 rollout_status proj(rollout_ctx* c, const void* X, const void* W, float* out, int M, int N, int K, int* splits_out) {
   if (!c->D.wq4) return gemm(c, X, W, out, M, N, K, kMaxSplits, splits_out);
-  const double wb = (double)(q4_code_bytes(N, K) + q4_sz_bytes(N, K));
-  if (M <= kSwigluMaxRows) {
-    const int s = gemm_splits_q4(M, N, K, kMaxSplits);
-    if ((size_t)s * M * N > c->Lo.part_elems) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
-    Scope sc(c, 0, wb + (double)M * K * 2 + (double)s * M * N * 4, 2.0 * M * N * K);
+  const bool tile = M > kSwigluMaxRows;
+  const int smax = (int)std::min<size_t>(kMaxSplits, c->Lo.part_elems / ((size_t)M * N));
+  if (smax < 1) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
+  rollout_status r;
+  if (tile && (r = dequant(c, W, N, K))) return r;
+  const int s = gemm_splits_q4(M, N, K, smax);
+  const double wb = tile ? (double)N * K * 2 : (double)(q4_code_bytes(N, K) + q4_sz_bytes(N, K));
+  Scope sc(c, 0, wb + (double)M * K * 2 + (double)s * M * N * 4, 2.0 * M * N * K);
+  if (tile)
+    HIP_TRY(c, launch_gemm_q4_tile(c->stream, X, W, c->at(c->Lo.wdq), out, M, N, K, s), "gemm");
+  else
     HIP_TRY(c, launch_gemm_q4(c->stream, X, W, out, M, N, K, s), "gemm");
-    *splits_out = s;
-    return ROLLOUT_OK;
-  }
-  // w = hi + lo with hi = bf16(w), lo = bf16(w - hi): two bf16 GEMMs into consecutive split slots
-  char* hi = c->at<char>(c->Lo.wdq);
-  char* lo = hi + (size_t)N * K * 2;
-  {
-    Scope sc(c, 2, wb + (double)N * K * 4, 0);
-    HIP_TRY(c, launch_dequant_q4(c->stream, W, N, K, hi, lo), "dequantise");
-  }
-  int s1 = 0, s2 = 0;
-  rollout_status r = gemm(c, X, hi, out, M, N, K, kMaxSplits / 2, &s1);
-  if (r) return r;
-  if ((size_t)2 * s1 * M * N > c->Lo.part_elems) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
-  if ((r = gemm(c, X, lo, out + (size_t)s1 * M * N, M, N, K, kMaxSplits / 2, &s2))) return r;
-  *splits_out = s1 + s2;
+  *splits_out = s;
   return ROLLOUT_OK;
 }
 
@@ -463,8 +464,8 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
       HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, part, s, M, D.d, x, c->at<float>(y.mlp_norm), D.eps, a),
               "residual norm");
     }
-    // SwiGLU in the gate/up GEMM's epilogue; int4 weights only up to the int4 ring's rows
-    if (D.dtype == ROLLOUT_DTYPE_BF16 && (!D.wq4 || M <= kSwigluMaxRows)) {
+    // SwiGLU in the gate/up GEMM's epilogue
+    if (D.dtype == ROLLOUT_DTYPE_BF16) {
       if ((r = gemm_swiglu(c, a, c->at(y.wgu), M, 2 * D.ff, D.d, h))) return r;
     } else {
       if ((r = proj(c, a, c->at(y.wgu), part, M, 2 * D.ff, D.d, &s))) return r;

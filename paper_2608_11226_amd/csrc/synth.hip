@@ -93,8 +93,7 @@ __global__ void k_synth(T* __restrict__ dst, WeightDesc w, uint64_t k0, uint64_t
 // Quantisation (fp32, round-half-even): lo, hi = group min, max;
 // s = (hi - lo) / 15 (a constant group: |hi|, or 1 when 0); z = clamp(rint(-lo/s), 0, 15);
 // q = clamp(rint(w/s) + z, 0, 15).  The dequantised weight is (q - z) * s; the GEMMs
-// never round it to bf16 (the decode GEMM scales each group's integer dot product,
-// prefill multiplies a bf16 pair hi + lo that holds it to 16 bits).
+// never round it to bf16 (they scale each group's integer dot product in fp32).
 __device__ __forceinline__ int q4_nibble(int e) { return (e >> 1) + 4 * (e & 1); }
 
 struct Q4Ptrs {
@@ -182,40 +181,31 @@ __global__ void k_export_q4(Q4Ptrs qp, WeightDesc w, int which, int rows, float*
   }
 }
 
-// int4 matrix -> two bf16 MFMA A-operand matrices in the weight fragment layout (wfrag), hi = bf16(w) and
-// lo = bf16(w - hi) (w - hi is exact in fp32), for the batches the tile GEMM takes.
-__global__ void k_dequant_q4(Q4Ptrs qp, int rows, int cols, uint4* __restrict__ hi, uint4* __restrict__ lo) {
-  const int kbt = cols / 32, gbt = cols / 128;
-  const size_t n = (size_t)(rows / 16) * kbt * 64;  // one fragment lane (8 values) per thread
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int lane = (int)(i & 63);
-    const size_t frag = i >> 6;
-    const int kb = (int)(frag % kbt);
-    const size_t nb = frag / kbt;
-    const size_t item = nb * gbt + (size_t)(kb >> 2);
-    const uint4 wd = qp.codes[item * 64 + lane];
-    const int j = kb & 3;
-    const uint32_t word = j == 0 ? wd.x : (j == 1 ? wd.y : (j == 2 ? wd.z : wd.w));
-    const size_t sr = item * 16 + (lane & 15);
-    const float sc = qp.s[sr], z = (float)qp.z[sr];
-    uint32_t oh[4], ol[4];
+// int4 matrix -> its integers q - z (exact in bf16, -15 .. 15) as MFMA A-operand fragments (wfrag), for the
+// batches that the tile GEMM takes; the scales stay where they are.  One thread per lane of a (block, group):
+// a 16-byte load of its 32 codes, four 16-byte stores that are whole fragments per wave.  Bound by the stores
+// (2 bytes a weight).
+__global__ __launch_bounds__(256) void k_dequant_q4(Q4Ptrs qp, int rows, int cols, uint4* __restrict__ out) {
+  const int kbt = cols / 32, gbt = cols / 128, nbt = rows / 16;
+  const size_t n = (size_t)nbt * gbt * 64;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int lane = (int)(i & 63);
+  const size_t item = i >> 6;
+  const int nb = (int)(item / gbt), gi = (int)(item % gbt);
+  const uint4 wd = qp.codes[i];
+  const float z = (float)qp.z[item * 16 + (lane & 15)];
+  const uint32_t word[4] = {wd.x, wd.y, wd.z, wd.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t o[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      uint32_t h2 = 0, l2 = 0;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float wv = ((float)((word >> (4 * q4_nibble(2 * t + u))) & 15u) - z) * sc;
-        const uint16_t bh = f32_to_bf16(wv);
-        const uint16_t bl = f32_to_bf16(wv - bf16_to_f32(bh));
-        h2 |= (uint32_t)bh << (16 * u);
-        l2 |= (uint32_t)bl << (16 * u);
-      }
-      oh[t] = h2;
-      ol[t] = l2;
+      const float a = (float)((word[j] >> (4 * q4_nibble(2 * t))) & 15u) - z;
+      const float b = (float)((word[j] >> (4 * q4_nibble(2 * t + 1))) & 15u) - z;
+      o[t] = (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xFFFF0000u);  // small integers: exact
     }
-    const size_t o = wfrag((int)nb, kb, rows / 16, kbt) * 64 + (size_t)lane;
-    hi[o] = make_uint4(oh[0], oh[1], oh[2], oh[3]);
-    lo[o] = make_uint4(ol[0], ol[1], ol[2], ol[3]);
+    out[wfrag(nb, 4 * gi + j, nbt, kbt) * 64 + (size_t)lane] = make_uint4(o[0], o[1], o[2], o[3]);
   }
 }
 
@@ -292,11 +282,11 @@ hipError_t launch_export_q4(hipStream_t s, const void* src, const WeightDesc& w,
   return hipGetLastError();
 }
 
-hipError_t launch_dequant_q4(hipStream_t s, const void* src, int rows, int cols, void* dst_hi, void* dst_lo) {
+hipError_t launch_dequant_q4(hipStream_t s, const void* src, int rows, int cols, void* dst) {
   if (rows % 16 || cols % 128) return hipErrorInvalidValue;
-  const size_t n = (size_t)(rows / 16) * (cols / 32) * 64;
-  hipLaunchKernelGGL(k_dequant_q4, dim3(grid_for(n, 256)), dim3(256), 0, s, q4_ptrs((void*)src, rows, cols), rows,
-                     cols, (uint4*)dst_hi, (uint4*)dst_lo);
+  const size_t n = (size_t)(rows / 16) * (cols / 128) * 64;
+  hipLaunchKernelGGL(k_dequant_q4, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                     q4_ptrs((void*)src, rows, cols), rows, cols, (uint4*)dst);
   return hipGetLastError();
 }
 

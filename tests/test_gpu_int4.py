@@ -3,8 +3,8 @@
 The library quantises the layer projections on the device from the same seeded fp32 weights; the exported
 dequantised values (q - z) * s in fp32 must equal the oracle's quantiser bit for bit, and logits must stay
 within the bf16 tolerance of the oracle run over the exact dequantised weights.  Decode batches up to 64
-rows take the group-scaled int4 ring GEMM, larger batches (prefill chunks, 256-row decode) dequantise into
-bf16 hi and lo tiles and take two bf16 GEMMs.
+rows take the group-scaled int4 ring GEMM, larger batches (prefill chunks, 256-row decode) write the integers
+q - z out as bf16 fragments and take the tile GEMM with the groups' scales.
 """
 import numpy as np
 import pytest
@@ -98,3 +98,23 @@ def test_int4_large_batch_decode_logits():
     err = _teacher_forced(INT4_SMALL, 32, 8, 24, N=3, seed=53)
     log(f"  max abs logit error per step: {[round(e, 5) for e in err]}")
     assert max(err) <= 3e-2
+
+
+# row counts around the tile choices of the group-scaled tile GEMM (one to three 128-row activation tiles, one
+# and two 256-row ones), weight blocks that leave partial tiles, one group per K slice and up to eleven
+@pytest.mark.parametrize("n_prompts,P", [(1, 65), (3, 43), (1, 256), (1, 257), (5, 77), (1, 513)])
+def test_int4_tile_gemm_rows(n_prompts, P):
+    shape = (1, 640, 10, 2, 64, 1408, 2064, 1e6)
+    log(f"int4 tile GEMM rows {n_prompts} x {P}")
+    cfg = R.model_config(shape, R.DTYPE_INT4, P, 2, n_prompts)
+    eng = R.Engine(cfg)
+    model = OracleModel(shape_of(cfg), mode="int4")
+    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=57)
+    want = np.stack([model.prefill(p)[1] for p in prompts])
+    logits = torch.empty((n_prompts, cfg.vocab), dtype=torch.float32, device="cuda:0")
+    R.rollout_prefill(eng.ctx, to_dev(prompts, torch), n_prompts, P, 1, logits)
+    eng.synchronize()
+    err = float(np.max(np.abs(logits.cpu().numpy() - want)))
+    log(f"  max abs logit error {err:.4g}")
+    assert err <= 3e-2  # the bf16 contract's bound, as above
+    eng.close()
