@@ -156,17 +156,21 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
     }
   };
   floatx4_t P[Q4 ? NB : 1][Q4 ? MBW : 1];
-  auto scale_group = [&](int slot) {  // acc += s * P with the scales of the group that k-step's slot belongs to
-    if constexpr (Q4) {
+  if constexpr (Q4) {  // the first k-step scales a group of zeros
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const floatx4_t sc = reinterpret_cast<const floatx4_t*>(&ls[slot][FR - 1][0])[(wn * NB + j) * 4 + (lane >> 4)];
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int i = 0; i < MBW; ++i)
+      for (int i = 0; i < MBW; ++i) P[j][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  floatx4_t sc[Q4 ? NB : 1];
+  auto read_scales = [&](int slot) {  // of the group that k-step's slot belongs to
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[j][i][r] = fmaf(sc[r], P[j][i][r], acc[j][i][r]);
-      }
-    }
+    for (int j = 0; j < NB; ++j)
+      sc[j] = reinterpret_cast<const floatx4_t*>(&ls[slot][FR - 1][0])[(wn * NB + j) * 4 + (lane >> 4)];
+  };
+  auto scale_tile = [&](int j, int i) {  // acc += s * P
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[j][i][r] = fmaf(sc[j][r], P[j][i][r], acc[j][i][r]);
   };
   if (nk > 0) {
     bf16x8_t wf[NB], xf[MBW];
@@ -184,19 +188,32 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
 #pragma unroll
           for (int i = 0; i < MBW; ++i) xf[i] = ls[u][TN + wm * MBW + i][lane];
           // the group that ended with step st - 1 (its slot is refilled after this step's multiply phase)
-          if (Q4 && u % 4 == 0 && st > 0) scale_group((u + NS - 1) % NS);
+          if (Q4 && u % 4 == 0) read_scales(u + (st > 0 ? NS - 1 : 0) - (u > 0 ? NS : 0));
           dma_wait_barrier<(NS - 3) * PER>();
           __builtin_amdgcn_s_setprio(1);
+          if constexpr (Q4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < MBW; ++i)
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
+              if (Q4 && u % 4 == 0) scale_tile(j, i);
               if constexpr (Q4)
                 P[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                     wf[j], xf[i], u % 4 == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : P[j][i], 0, 0, 0);
               else
                 acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[j][i], 0, 0, 0);
             }
+          if (Q4 && u % 4 == 0) {  // the last group's scaling stays between this step's MFMAs, four FMAs a tile
+#pragma unroll
+            for (int i = 0; i < MBW; ++i)
+#pragma unroll
+              for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[j][i]));
+#pragma unroll
+            for (int t = 0; t < NB * MBW; ++t) {
+              __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            }
+          }
           __builtin_amdgcn_s_setprio(0);
           __builtin_amdgcn_sched_barrier(0);  // the MFMAs stay in their phase
           phase_barrier();
@@ -205,7 +222,13 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
       }
     }
     if (wave < 4) phase_barrier();  // as many barriers as the second group
-    if constexpr (Q4) scale_group((nk - 1) % NS);  // the last group
+    if constexpr (Q4) {  // the last group
+      read_scales((nk - 1) % NS);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < MBW; ++i) scale_tile(j, i);
+    }
     dma_wait();                     // no transfer outlives the workgroup's LDS
   }
   // D layout of the 16x16 MFMA: lane holds rows 4*(lane/16)+r (weight rows n) of column lane%16 (row m of X)
