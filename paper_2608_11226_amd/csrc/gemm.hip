@@ -91,6 +91,9 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 //   14B head 424 -> 369;  128 rows: 14B gate/up 84 -> 62, 7B down 45 -> 38, 7B head 248 -> 234
 // All sums are bit-equal to the previous kernels' at equal splits (k order).
 //
+// rep: every output row is written rep times, to rows rep * m .. rep * m + rep - 1 (the LM head after a prefill: a
+// prompt's logits for each member of its group).
+//
 // Q4 (int4 weights): W holds the integers q - z, exact in bf16 (k_dequant_q4), and Ws the fp32 scale of every
 // (16-row block, 128-input group, row).  A group's four k-steps sum into P, and acc += s * P in fp32 while the
 // wave reads the next step's fragments, so the weights are never rounded and the vector work runs beside the
@@ -100,7 +103,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 template <int NB, int MBW, int WN, int WM, int NS, bool SWI, bool Q4>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, const floatx4_t* __restrict__ Ws,
-               float* __restrict__ out, int M, int N, int K, int kslice, int Nt, uint16_t* __restrict__ h) {
+               float* __restrict__ out, int M, int N, int K, int kslice, int Nt, uint16_t* __restrict__ h, int rep) {
   constexpr int TN = NB * WN, TM = MBW * WM, FR = TN + TM + (Q4 ? 1 : 0);
   constexpr int PER = (FR + 7) / 8;  // fragments a wave transfers per k-step (surplus ones repeat the last)
   static_assert(WN * WM == 8 && NS >= 3, "eight waves");
@@ -247,7 +250,8 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
         const float h0 = g0 / (1.0f + expf(-g0)) * u0, h1 = g1 / (1.0f + expf(-g1)) * u1;
         *reinterpret_cast<uint32_t*>(h + xoff(h, m, n >> 1, N >> 1, Mb)) = pack_bf16x2(h0, h1);
       } else {
-        *reinterpret_cast<float4*>(o + (size_t)m * N + n) = make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]);
+        const float4 v = make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]);
+        for (int c = 0; c < rep; ++c) *reinterpret_cast<float4*>(o + ((size_t)m * rep + c) * N + n) = v;
       }
     }
   }
@@ -263,7 +267,7 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
 template <int MB, int NBW, int D, bool SWI, int KW, bool BAL = false>
 __global__ __launch_bounds__(64 * KW) void k_gemm_ring(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W,
                                                        float* __restrict__ out, int M, int N, int K, int kslice,
-                                                       uint16_t* __restrict__ h) {
+                                                       uint16_t* __restrict__ h, int rep) {
   const int lane = threadIdx.x & 63;
   const int wave = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int nbt = N >> 4, kbt = K >> 5;
@@ -381,8 +385,8 @@ __global__ __launch_bounds__(64 * KW) void k_gemm_ring(const bf16x8_t* __restric
         *reinterpret_cast<uint32_t*>(h + xoff(h, m, n >> 1, N >> 1, MB)) = pack_bf16x2(h0, h1);
       } else {
         float* o = out + (size_t)blockIdx.y * M * N;
-        *reinterpret_cast<float4*>(o + (size_t)m * N + n) =
-            make_float4(acc[j][mb][0], acc[j][mb][1], acc[j][mb][2], acc[j][mb][3]);
+        const float4 v = make_float4(acc[j][mb][0], acc[j][mb][1], acc[j][mb][2], acc[j][mb][3]);
+        for (int c = 0; c < rep; ++c) *reinterpret_cast<float4*>(o + ((size_t)m * rep + c) * N + n) = v;
       }
     }
   }
@@ -546,7 +550,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ X, int ldx, const float* __restrict__ W,
-                                                  float* __restrict__ out, int M, int N, int K) {
+                                                  float* __restrict__ out, int M, int N, int K, int rep) {
   __shared__ float xs[16][33];
   __shared__ float ws[16][33];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
@@ -565,7 +569,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ X, i
     __syncthreads();
   }
   const int m = m0 + ty, n = n0 + tx;
-  if (m < M && n < N) out[(size_t)m * N + n] = acc;
+  if (m < M && n < N)
+    for (int c = 0; c < rep; ++c) out[((size_t)m * rep + c) * N + n] = acc;
 }
 
 int kslice_for(int K, int splits) {
@@ -659,25 +664,25 @@ TilePlan tile_plan(int M, int N, int K, int smin, int smax, bool q4 = false) {
 
 template <int NB, int MBW, int WN, int WM, int NS, bool SWI, bool Q4>
 void launch_pp(hipStream_t s, const TilePlan& p, const bf16x8_t* x, const bf16x8_t* w, const floatx4_t* ws, float* out,
-               int M, int N, int K, uint16_t* h) {
+               int M, int N, int K, uint16_t* h, int rep) {
   const int mt = ((M + 15) / 16 + MBW * WM - 1) / (MBW * WM);
   const dim3 grid((unsigned)(mt * p.nt + 7) / 8 * 8, p.splits);
   hipLaunchKernelGGL((k_gemm_pp<NB, MBW, WN, WM, NS, SWI, Q4>), grid, dim3(512), 0, s, x, w, ws, out, M, N, K,
-                     tile_kslice(K, p.splits, Q4), p.nt, h);
+                     tile_kslice(K, p.splits, Q4), p.nt, h, rep);
 }
 
 // LDS of a tile: NS x (TN + TM) KB (int4 one more fragment), at most 160
 template <bool SWI>
 hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K, int splits,
-                       uint16_t* h) {
+                       uint16_t* h, int rep) {
   const TilePlan p = tile_plan(M, N, K, splits, splits);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 6, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
-    case T_8x16: launch_pp<4, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
-    case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
-    default: launch_pp<5, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h); break;
+    case T_10x8: launch_pp<5, 2, 2, 4, 6, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_8x16: launch_pp<4, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    default: launch_pp<5, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
   }
   return hipGetLastError();
 }
@@ -687,10 +692,10 @@ hipError_t launch_tile_q4(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, c
                           int N, int K, int splits, uint16_t* h) {
   const TilePlan p = tile_plan(M, N, K, splits, splits, true);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
-    default: launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h); break;
+    case T_10x8: launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
+    default: launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
   }
   return hipGetLastError();
 }
@@ -741,14 +746,14 @@ int ring_waves_per_group(int N, int nbw, int splits) {
 
 template <int NBW, bool SWI, int KW>
 void launch_ring_kw(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
-                    int splits, uint16_t* h) {
+                    int splits, uint16_t* h, int rep) {
   const int kslice = kslice_for(K, splits);
   const dim3 grid(ring_groups(N, NBW), splits), block(64 * KW);
   switch ((M + 15) / 16) {
-    case 1: hipLaunchKernelGGL((k_gemm_ring<1, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
-    case 2: hipLaunchKernelGGL((k_gemm_ring<2, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
-    case 3: hipLaunchKernelGGL((k_gemm_ring<3, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
-    default: hipLaunchKernelGGL((k_gemm_ring<4, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
+    case 1: hipLaunchKernelGGL((k_gemm_ring<1, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
+    case 2: hipLaunchKernelGGL((k_gemm_ring<2, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
+    case 3: hipLaunchKernelGGL((k_gemm_ring<3, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
+    default: hipLaunchKernelGGL((k_gemm_ring<4, NBW, 2, SWI, KW>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
   }
 }
 
@@ -782,14 +787,14 @@ bool use_balanced_single(int M, int N, int splits) {
 
 template <bool SWI, int KW, int NBW = kBalNBW>
 hipError_t launch_ring_balanced(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
-                                int groups, uint16_t* h) {
+                                int groups, uint16_t* h, int rep) {
   const int kslice = kslice_for(K, 1);
   const dim3 grid(groups, 1), block(64 * KW);
   switch ((M + 15) / 16) {
-    case 1: hipLaunchKernelGGL((k_gemm_ring<1, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
-    case 2: hipLaunchKernelGGL((k_gemm_ring<2, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
-    case 3: hipLaunchKernelGGL((k_gemm_ring<3, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
-    default: hipLaunchKernelGGL((k_gemm_ring<4, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h); break;
+    case 1: hipLaunchKernelGGL((k_gemm_ring<1, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
+    case 2: hipLaunchKernelGGL((k_gemm_ring<2, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
+    case 3: hipLaunchKernelGGL((k_gemm_ring<3, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
+    default: hipLaunchKernelGGL((k_gemm_ring<4, NBW, 2, SWI, KW, true>), grid, block, 0, s, x, w, out, M, N, K, kslice, h, rep); break;
   }
   return hipGetLastError();
 }
@@ -798,25 +803,25 @@ template <int NBW, bool SWI>
 hipError_t launch_ring(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
                        int splits, uint16_t* h) {
   if (ring_waves_per_group(N, NBW, splits) == 2)
-    launch_ring_kw<NBW, SWI, 2>(s, x, w, out, M, N, K, splits, h);
+    launch_ring_kw<NBW, SWI, 2>(s, x, w, out, M, N, K, splits, h, 1);
   else
-    launch_ring_kw<NBW, SWI, 1>(s, x, w, out, M, N, K, splits, h);
+    launch_ring_kw<NBW, SWI, 1>(s, x, w, out, M, N, K, splits, h, 1);
   return hipGetLastError();
 }
 
 // A split projection (no SwiGLU) on the ring kernel, shaped by ring_four_blocks / ring_split_waves.  Any
 // shape gives the same partials; the split count is the caller's.
 hipError_t launch_ring_split(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, float* out, int M, int N, int K,
-                             int splits) {
+                             int splits, int rep) {
   if (ring_four_blocks(N, K, splits)) {
     if (ring_split_waves(N, K, 4, splits) == 4)
-      launch_ring_kw<4, false, 4>(s, x, w, out, M, N, K, splits, nullptr);
+      launch_ring_kw<4, false, 4>(s, x, w, out, M, N, K, splits, nullptr, rep);
     else
-      launch_ring_kw<4, false, 2>(s, x, w, out, M, N, K, splits, nullptr);
+      launch_ring_kw<4, false, 2>(s, x, w, out, M, N, K, splits, nullptr, rep);
   } else if (ring_split_waves(N, K, 8, splits) == 2) {
-    launch_ring_kw<8, false, 2>(s, x, w, out, M, N, K, splits, nullptr);
+    launch_ring_kw<8, false, 2>(s, x, w, out, M, N, K, splits, nullptr, rep);
   } else {
-    launch_ring_kw<8, false, 1>(s, x, w, out, M, N, K, splits, nullptr);
+    launch_ring_kw<8, false, 1>(s, x, w, out, M, N, K, splits, nullptr, rep);
   }
   return hipGetLastError();
 }
@@ -908,11 +913,12 @@ int gemm_splits(int dtype, int M, int N, int K, int max_splits) {
 }
 
 hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const void* W, float* out, int M, int N,
-                       int K, int splits) {
+                       int K, int splits, int rep) {
   if (M <= 0) return hipSuccess;
+  if (rep < 1 || (rep > 1 && splits > 1)) return hipErrorInvalidValue;
   if (dtype != ROLLOUT_DTYPE_BF16) {
     dim3 grid((N + 15) / 16, (M + 15) / 16);
-    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, (const float*)X, ldx, (const float*)W, out, M, N, K);
+    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, (const float*)X, ldx, (const float*)W, out, M, N, K, rep);
     return hipGetLastError();
   }
   if (N % 16 || K % 32) return hipErrorInvalidValue;
@@ -920,23 +926,23 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const v
   const bf16x8_t* w = (const bf16x8_t*)W;
   if (M <= kRingMaxRows) {
     if (use_balanced_single(M, N, splits))
-      return launch_ring_balanced<false, 1>(s, x, w, out, M, N, K, kBalWavesPerCU * device_cus(), nullptr);
-    return launch_ring_split(s, x, w, out, M, N, K, splits);
+      return launch_ring_balanced<false, 1>(s, x, w, out, M, N, K, kBalWavesPerCU * device_cus(), nullptr, rep);
+    return launch_ring_split(s, x, w, out, M, N, K, splits, rep);
   }
-  return launch_tile<false>(s, x, w, out, M, N, K, splits, nullptr);
+  return launch_tile<false>(s, x, w, out, M, N, K, splits, nullptr, rep);
 }
 
 hipError_t launch_gemm_swiglu(hipStream_t s, const void* X, const void* W, int M, int N, int K, void* h) {
   if (M <= 0) return hipSuccess;
   if (N % 32 || K % 32) return hipErrorInvalidValue;
   if (M > kRingMaxRows)  // larger batches: the same epilogue on k_gemm_pp, one K split
-    return launch_tile<true>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, 1, (uint16_t*)h);
+    return launch_tile<true>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, 1, (uint16_t*)h, 1);
   if (use_balanced_swiglu(M, N))
     return launch_ring_balanced<true, 2>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, device_cus(),
-                                         (uint16_t*)h);
+                                         (uint16_t*)h, 1);
   if (use_balanced_swiglu_wide(M, N))
     return launch_ring_balanced<true, 1, kBal2NBW>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K,
-                                                   2 * device_cus(), (uint16_t*)h);
+                                                   2 * device_cus(), (uint16_t*)h, 1);
   return launch_ring<4, true>(s, (const bf16x8_t*)X, (const bf16x8_t*)W, nullptr, M, N, K, 1, (uint16_t*)h);
 }
 

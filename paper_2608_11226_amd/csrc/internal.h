@@ -79,8 +79,9 @@ hipError_t launch_export(hipStream_t s, const void* src, int dtype, const Weight
 
 // out[split][m][n] = sum over the split's k range of X[m][k] * W[n][k] (fp32).
 int gemm_splits(int dtype, int M, int N, int K, int max_splits);
+// With rep > 1 (one split) every output row m is written rep times, to rows rep * m .. rep * m + rep - 1.
 hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const void* W, float* out, int M,
-                       int N, int K, int splits);
+                       int N, int K, int splits, int rep);
 
 // Gate/up projection with SwiGLU applied to its own output (bf16, one K split;
 // the ring kernel up to 64 rows, the tile kernel above): W holds gate row i at
@@ -136,8 +137,10 @@ hipError_t launch_attention_shared(hipStream_t s, const Dims& D, void* kv_pool, 
 // layer: all KV heads, K and V), for a sequence that starts from a copy of a shared partial block
 hipError_t launch_copy_kv_block(hipStream_t s, void* kv_pool, int n_blocks, int L, size_t bytes_per_layer, int src,
                                 int dst);
-hipError_t launch_gather_rows(hipStream_t s, int dtype, const void* src, int ld, int P, int G, int n_prompts,
-                              void* dst);
+// last position of each of n_prompts prompts (src: n_prompts * P rows), F copies each, into rows row0 .. of dst
+// (M_dst rows in all)
+hipError_t launch_gather_rows(hipStream_t s, int dtype, const void* src, int ld, int P, int F, int n_prompts, int row0,
+                              int M_dst, void* dst);
 hipError_t launch_advance(hipStream_t s, int32_t* ctx_len, int S, int32_t* cols);
 // Continuous batching (batching.hip): per-slot completion index, next token column, ended flag, the
 // slot's last draw and its staged uniform; all [S] in the arena.
@@ -252,6 +255,14 @@ __device__ __forceinline__ void st8(uint16_t* p, size_t i, const float* v) {
   u.z = (uint32_t)f32_to_bf16(v[4]) | ((uint32_t)f32_to_bf16(v[5]) << 16);
   u.w = (uint32_t)f32_to_bf16(v[6]) | ((uint32_t)f32_to_bf16(v[7]) << 16);
   *reinterpret_cast<uint4*>(p + i) = u;
+}
+// Four consecutive values at p (16-byte aligned for fp32, 8 for bf16).
+__device__ __forceinline__ void st4(float* p, const float* v) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void st4(uint16_t* p, const float* v) {
+  uint2 u;
+  u.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
+  u.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+  *reinterpret_cast<uint2*>(p) = u;
 }
 __device__ __forceinline__ void ld8(const float* p, size_t i, float* v) {
   const float4 a = reinterpret_cast<const float4*>(p + i)[0], b = reinterpret_cast<const float4*>(p + i)[1];

@@ -132,7 +132,8 @@ __device__ __forceinline__ void row_place(const RowMap& rm, int m, int* seq, int
   }
 }
 
-// One wave per (row, head slot): slots [0, nh) are query heads, [nh, nh+nkv)
+// Decode rows (fp32 path and head_dim 32; the bf16 decode attention forms q, k and v itself):
+// one wave per (row, head slot): slots [0, nh) are query heads, [nh, nh+nkv)
 // key heads, [nh+nkv, nh+2nkv) value heads; slot s owns columns [s*hd, s*hd+hd)
 // of the fused QKV output.  Query and key heads are rotated (rotate-half pairs
 // (i, i + hd/2), angles cos/sin[pos][i]); keys and values are appended to the
@@ -148,8 +149,6 @@ __global__ __launch_bounds__(64) void k_qkv_epilogue(Dims D, const float* __rest
   int seq, pos;
   row_place(rm, m, &seq, &pos);
   const int hd = D.hd, half = hd / 2;
-  // prefill rows in the last, partly filled prompt block go to every sequence of the group
-  const int copies = (rm.P > 0 && (pos / D.blk) * D.blk + D.blk > rm.P) ? rm.G : 1;
   const int n = D.nqkv;
   const size_t split_stride = (size_t)M * n;
   const float* pr = part + (size_t)m * n + (size_t)slot * hd;
@@ -170,26 +169,106 @@ __global__ __launch_bounds__(64) void k_qkv_epilogue(Dims D, const float* __rest
         stf(q_out, (size_t)m * D.qd + (size_t)slot * hd + i, o1);
         stf(q_out, (size_t)m * D.qd + (size_t)slot * hd + i + half, o2);
       } else {
-        for (int c = 0; c < copies; ++c) {
-          const int b = tables[(size_t)(seq + c) * max_blocks + pos / D.blk];
-          if (b < 0 || b >= n_blocks) { atomicOr(err, 2); continue; }
-          T* dst = kv + kv_offset(layer, b, kslot, n_blocks, D.nkv, 2 * blk_elems) + (size_t)(pos % D.blk) * hd;
-          stf(dst, i, o1);
-          stf(dst, i + half, o2);
-        }
+        const int b = tables[(size_t)seq * max_blocks + pos / D.blk];
+        if (b < 0 || b >= n_blocks) { atomicOr(err, 2); continue; }
+        T* dst = kv + kv_offset(layer, b, kslot, n_blocks, D.nkv, 2 * blk_elems) + (size_t)(pos % D.blk) * hd;
+        stf(dst, i, o1);
+        stf(dst, i + half, o2);
       }
     }
   } else {
     for (int i = tid; i < hd; i += 64) {
       float v = 0.f;
       for (int s = 0; s < splits; ++s) v += pr[s * split_stride + i];
-      for (int c = 0; c < copies; ++c) {
-        const int b = tables[(size_t)(seq + c) * max_blocks + pos / D.blk];
+      const int b = tables[(size_t)seq * max_blocks + pos / D.blk];
+      if (b < 0 || b >= n_blocks) { atomicOr(err, 2); continue; }
+      T* dst = kv + kv_offset(layer, b, vslot, n_blocks, D.nkv, 2 * blk_elems) + blk_elems + (size_t)i * D.blk +
+               (pos % D.blk);
+      stf(dst, 0, v);
+    }
+  }
+}
+
+// The same for prefill rows, 16 consecutive tokens of one prompt and one head slot per workgroup: every
+// access is whole 16-byte (fp32: up to 32-byte) pieces of rows -- the split partials by float4, queries and
+// keys in runs of four dimensions, and values turned in LDS so that a thread stores eight tokens of one
+// dimension at once (dimension-major blocks: one at a time these were 2-byte stores 2 * blk bytes apart).
+// Value groups that reach past the prompt store zeros there (their positions are written again before they
+// are read).  Bound by memory: 4,096 x 7,168 outputs 87 -> 33 us, 2,048 x 4,608 37 -> 15 us.
+constexpr int kQkvTokens = 16;
+template <typename T>
+__global__ __launch_bounds__(256) void k_qkv_prefill(Dims D, const float* __restrict__ part, int splits, int M, RowMap rm,
+                                                     const float* __restrict__ rcos, const float* __restrict__ rsin,
+                                                     T* __restrict__ q_out, T* __restrict__ kv, int n_blocks,
+                                                     const int32_t* __restrict__ tables, int max_blocks, int layer,
+                                                     int32_t* __restrict__ err) {
+  __shared__ float s_v[kQkvTokens][128 + 4];
+  const int P = rm.P, chunks = (P + kQkvTokens - 1) / kQkvTokens;
+  const int prompt = (int)(blockIdx.x / chunks), t0 = (int)(blockIdx.x % chunks) * kQkvTokens, slot = blockIdx.y;
+  const int tid = threadIdx.x, hd = D.hd, half = hd / 2, blk = D.blk;
+  const int seq = rm.seq0 + prompt * rm.G;
+  const size_t n = D.nqkv, split_stride = (size_t)M * n, blk_elems = (size_t)blk * hd;
+  const int kslot = slot - D.nh, vslot = slot - D.nh - D.nkv;
+  const int quads = half / 4;  // a thread takes dimensions 4 qd .. + 3 and their partners half further of one token
+  const int tl = tid / quads, qd = tid % quads, tok = t0 + tl;
+  float x1[4] = {0.f, 0.f, 0.f, 0.f}, x2[4] = {0.f, 0.f, 0.f, 0.f};
+  const bool act = tl < kQkvTokens && tok < P;
+  const size_t row = (size_t)prompt * P + (act ? tok : 0);
+  if (act) {
+    const float* pr = part + row * n + (size_t)slot * hd + 4 * qd;
+    for (int s = 0; s < splits; ++s) {
+      const float4 a = *reinterpret_cast<const float4*>(pr + s * split_stride);
+      const float4 b = *reinterpret_cast<const float4*>(pr + s * split_stride + half);
+      x1[0] += a.x; x1[1] += a.y; x1[2] += a.z; x1[3] += a.w;
+      x2[0] += b.x; x2[1] += b.y; x2[2] += b.z; x2[3] += b.w;
+    }
+  }
+  // tokens of the last, partly filled block go to every sequence of the group
+  const auto copies = [&](int t) { return (t / blk) * blk + blk > P ? rm.G : 1; };
+  if (vslot < 0) {
+    if (!act) return;
+    const float4 c4 = *reinterpret_cast<const float4*>(rcos + (size_t)tok * half + 4 * qd);
+    const float4 s4 = *reinterpret_cast<const float4*>(rsin + (size_t)tok * half + 4 * qd);
+    const float cs[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
+    float o1[4], o2[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o1[e] = x1[e] * cs[e] - x2[e] * sn[e];
+      o2[e] = x2[e] * cs[e] + x1[e] * sn[e];
+    }
+    if (kslot < 0) {
+      T* dst = q_out + row * D.qd + (size_t)slot * hd + 4 * qd;
+      st4(dst, o1);
+      st4(dst + half, o2);
+    } else {
+      for (int c = 0; c < copies(tok); ++c) {
+        const int b = tables[(size_t)(seq + c) * max_blocks + tok / blk];
         if (b < 0 || b >= n_blocks) { atomicOr(err, 2); continue; }
-        T* dst = kv + kv_offset(layer, b, vslot, n_blocks, D.nkv, 2 * blk_elems) + blk_elems + (size_t)i * D.blk +
-                 (pos % D.blk);
-        stf(dst, 0, v);
+        T* dst = kv + kv_offset(layer, b, kslot, n_blocks, D.nkv, 2 * blk_elems) + (size_t)(tok % blk) * hd + 4 * qd;
+        st4(dst, o1);
+        st4(dst + half, o2);
       }
+    }
+    return;
+  }
+  if (tl < kQkvTokens) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s_v[tl][4 * qd + e] = x1[e];
+      s_v[tl][4 * qd + half + e] = x2[e];
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < 2 * hd; i += 256) {
+    const int dim = i % hd, g8 = i / hd * 8, t8 = t0 + g8;  // tokens t8 .. t8 + 7: inside one block
+    if (t8 >= P) continue;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = s_v[g8 + e][dim];
+    for (int c = 0; c < copies(t8); ++c) {
+      const int b = tables[(size_t)(seq + c) * max_blocks + t8 / blk];
+      if (b < 0 || b >= n_blocks) { atomicOr(err, 2); continue; }
+      st8(kv, kv_offset(layer, b, vslot, n_blocks, D.nkv, 2 * blk_elems) + blk_elems + (size_t)dim * blk + t8 % blk, v);
     }
   }
 }
@@ -220,12 +299,12 @@ __global__ __launch_bounds__(256) void k_swiglu(const float* __restrict__ part, 
   st8(h, xoff(h, m, f, ff, (M + 15) >> 4), o);
 }
 
-// dst row p*G + g = src row p*P + P - 1 (last prompt position, replicated over the group), GEMM operand layout
+// dst row row0 + p*F + f = src row p*P + P - 1 (last prompt position, F copies), GEMM operand layout
 template <typename T>
-__global__ __launch_bounds__(256) void k_gather_rows(const T* __restrict__ src, int d, int P, int G, int M_src,
-                                                     int M_dst, T* __restrict__ dst) {
-  const int r = blockIdx.x;
-  const int sr = (r / G) * P + P - 1;
+__global__ __launch_bounds__(256) void k_gather_rows(const T* __restrict__ src, int d, int P, int F, int M_src,
+                                                     int row0, int M_dst, T* __restrict__ dst) {
+  const int r = row0 + blockIdx.x;
+  const int sr = (int)(blockIdx.x / F) * P + P - 1;
   const int mb_s = (M_src + 15) >> 4, mb_d = (M_dst + 15) >> 4;
   for (int g = threadIdx.x; g < (d >> 3); g += blockDim.x) {
     float v[8];
@@ -354,6 +433,17 @@ hipError_t launch_qkv_epilogue(hipStream_t s, const Dims& D, const float* part, 
                                const float* rope_cos, const float* rope_sin, void* q_out, void* kv_pool, int n_blocks,
                                const int32_t* tables, int max_blocks, int layer, int32_t* err) {
   if (M <= 0) return hipSuccess;
+  if (rm.P > 0) {  // whole prompts
+    if (M % rm.P || D.hd % 8 || D.hd > 128 || D.blk % 8) return hipErrorInvalidValue;
+    const dim3 pgrid(M / rm.P * ((rm.P + kQkvTokens - 1) / kQkvTokens), D.nh + 2 * D.nkv);
+    if (D.dtype == ROLLOUT_DTYPE_BF16)
+      hipLaunchKernelGGL(k_qkv_prefill<uint16_t>, pgrid, dim3(256), 0, s, D, part, splits, M, rm, rope_cos, rope_sin,
+                         (uint16_t*)q_out, (uint16_t*)kv_pool, n_blocks, tables, max_blocks, layer, err);
+    else
+      hipLaunchKernelGGL(k_qkv_prefill<float>, pgrid, dim3(256), 0, s, D, part, splits, M, rm, rope_cos, rope_sin,
+                         (float*)q_out, (float*)kv_pool, n_blocks, tables, max_blocks, layer, err);
+    return hipGetLastError();
+  }
   const dim3 grid(M, D.nh + 2 * D.nkv);
   if (D.dtype == ROLLOUT_DTYPE_BF16)
     hipLaunchKernelGGL(k_qkv_epilogue<uint16_t>, grid, dim3(64), 0, s, D, part, splits, M, rm, rope_cos, rope_sin,
@@ -392,16 +482,16 @@ hipError_t launch_copy_kv_block(hipStream_t s, void* kv_pool, int n_blocks, int 
   return hipGetLastError();
 }
 
-hipError_t launch_gather_rows(hipStream_t s, int dtype, const void* src, int d, int P, int G, int n_prompts,
-                              void* dst) {
-  if (n_prompts <= 0) return hipSuccess;
-  const int M_src = n_prompts * P, M_dst = n_prompts * G;
+hipError_t launch_gather_rows(hipStream_t s, int dtype, const void* src, int d, int P, int F, int n_prompts, int row0,
+                              int M_dst, void* dst) {
+  if (n_prompts <= 0 || F < 1) return hipSuccess;
+  const int M_src = n_prompts * P;
   if (dtype == ROLLOUT_DTYPE_BF16)
-    hipLaunchKernelGGL(k_gather_rows<uint16_t>, dim3(M_dst), dim3(256), 0, s, (const uint16_t*)src, d, P, G, M_src,
-                       M_dst, (uint16_t*)dst);
+    hipLaunchKernelGGL(k_gather_rows<uint16_t>, dim3(n_prompts * F), dim3(256), 0, s, (const uint16_t*)src, d, P, F,
+                       M_src, row0, M_dst, (uint16_t*)dst);
   else
-    hipLaunchKernelGGL(k_gather_rows<float>, dim3(M_dst), dim3(256), 0, s, (const float*)src, d, P, G, M_src, M_dst,
-                       (float*)dst);
+    hipLaunchKernelGGL(k_gather_rows<float>, dim3(n_prompts * F), dim3(256), 0, s, (const float*)src, d, P, F, M_src,
+                       row0, M_dst, (float*)dst);
   return hipGetLastError();
 }
 

@@ -336,15 +336,15 @@ struct Scope {
 };
 
 rollout_status gemm(rollout_ctx* c, const void* X, const void* W, float* out, int M, int N, int K, int max_splits,
-                    int* splits_out) {
+                    int* splits_out, int rep = 1) {
   const Dims& D = c->D;
   // as many splits as the workspace holds (max_splits 1: the output is not the workspace)
   if (max_splits > 1) max_splits = (int)std::min<size_t>(max_splits, c->Lo.part_elems / ((size_t)M * N));
   if (max_splits < 1) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
   const int s = gemm_splits(D.dtype, M, N, K, max_splits);
   const double eb = (double)elem_bytes(D.dtype);
-  Scope sc(c, 0, (double)N * K * eb + (double)M * K * eb + (double)M * N * 4, 2.0 * M * N * K);
-  HIP_TRY(c, launch_gemm(c->stream, D.dtype, X, K, W, out, M, N, K, s), "gemm");
+  Scope sc(c, 0, (double)N * K * eb + (double)M * K * eb + (double)M * rep * N * 4, 2.0 * M * N * K);
+  HIP_TRY(c, launch_gemm(c->stream, D.dtype, X, K, W, out, M, N, K, s, rep), "gemm");
   *splits_out = s;
   return ROLLOUT_OK;
 }
@@ -407,7 +407,7 @@ bool use_shared_prefix(const rollout_ctx* c, int M, const RowMap& rm) {
 
 // One transformer pass over M rows (prefill chunk or decode batch). On return
 // c->Lo.a holds the final-normed hidden states (cache dtype).
-// normed: the first layer's norm output is already in place (decode steps embed and normalise in one kernel)
+// normed: the first layer's norm output is already in place (embed_rows)
 rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max, double kv_tokens_read,
                               bool normed = false) {
   const Dims& D = c->D;
@@ -524,6 +524,22 @@ rollout_status upload_wave(rollout_ctx* c, int n_prompts, int P, int G) {
   return ROLLOUT_OK;
 }
 
+// Embedding of M rows, with the first layer's norm in the same kernel (*normed) unless the rows are too wide.
+rollout_status embed_rows(rollout_ctx* c, const int32_t* tokens, int tok_stride, const int32_t* col, int M, bool* normed) {
+  const Dims& D = c->D;
+  const Layout& Lo = c->Lo;
+  *normed = D.d % 8 == 0 && D.d / 8 <= 1024;
+  Scope sc(c, 2, (double)M * D.d * (4 + elem_bytes(D.dtype)), 0);
+  if (*normed)
+    HIP_TRY(c, launch_embed_norm(c->stream, D.dtype, c->at(Lo.embed), tokens, tok_stride, col, M, D.d, D.V,
+                                 c->at<float>(Lo.x), c->at<float>(Lo.layers[0].attn_norm), D.eps, c->at(Lo.a),
+                                 c->at<int32_t>(Lo.err)), "embed + norm");
+  else
+    HIP_TRY(c, launch_embed(c->stream, D.dtype, c->at(Lo.embed), tokens, tok_stride, col, M, D.d, D.V,
+                            c->at<float>(Lo.x), c->at<int32_t>(Lo.err)), "embed");
+  return ROLLOUT_OK;
+}
+
 // Prefill n_prompts prompts.  Prompt i writes its K/V through the block-table rows row0 + i * G_kv ..
 // + G_kv - 1 (tables already in place; the partial last prompt block goes to each of them); the last
 // position's logits, replicated G_out times, go to d_logits [n_prompts * G_out, V].
@@ -532,24 +548,27 @@ rollout_status prefill_rows(rollout_ctx* c, const int32_t* d_prompts, int n_prom
   const Dims& D = c->D;
   const Layout& Lo = c->Lo;
   const int per_chunk = std::max(1, Lo.T_chunk / P);
+  // The LM head runs once over the prompts' last positions.  Up to 64 rows it takes its weights' stream time
+  // whatever the rows (7B width 167 us at 8, 174 at 64, with the same logits written), so a group's rows are
+  // copied as far as that goes (F copies) and the head's stores make the rest (16 prompts, G = 16 at 14B width:
+  // 64 rows stored four times each, once, against 2 x 369 us for 128 rows a chunk).
+  int F = 1;
+  for (int f = 1; f <= G_out; ++f)
+    if (G_out % f == 0 && (int64_t)n_prompts * f <= 64) F = f;
   for (int p0 = 0; p0 < n_prompts; p0 += per_chunk) {
     const int np = std::min(per_chunk, n_prompts - p0);
     const int M = np * P;
-    {
-      Scope sc(c, 2, (double)M * D.d * (4 + elem_bytes(D.dtype)), 0);
-      HIP_TRY(c, launch_embed(c->stream, D.dtype, c->at(Lo.embed), d_prompts + (size_t)p0 * P, 1, nullptr, M, D.d, D.V,
-                              c->at<float>(Lo.x), c->at<int32_t>(Lo.err)), "embed");
-    }
+    bool normed;
+    rollout_status r = embed_rows(c, d_prompts + (size_t)p0 * P, 1, nullptr, M, &normed);
+    if (r) return r;
     RowMap rm{nullptr, P, G_kv, row0 + p0 * G_kv};
-    rollout_status r = forward_layers(c, M, rm, P, (double)np * P * (P + 1) / 2.0);
+    r = forward_layers(c, M, rm, P, (double)np * P * (P + 1) / 2.0, normed);
     if (r) return r;
-    HIP_TRY(c, launch_gather_rows(c->stream, D.dtype, c->at(Lo.a), D.d, P, G_out, np, c->at(Lo.a_last)), "gather");
-    int s;
-    r = gemm(c, c->at(Lo.a_last), c->at(Lo.lm_head), d_logits + (size_t)p0 * G_out * D.V, np * G_out, D.V, D.d, 1,
-             &s);
-    if (r) return r;
+    HIP_TRY(c, launch_gather_rows(c->stream, D.dtype, c->at(Lo.a), D.d, P, F, np, p0 * F, n_prompts * F, c->at(Lo.a_last)),
+            "gather");
   }
-  return ROLLOUT_OK;
+  int s;
+  return gemm(c, c->at(Lo.a_last), c->at(Lo.lm_head), d_logits, n_prompts * F, D.V, D.d, 1, &s, G_out / F);
 }
 
 rollout_status do_prefill(rollout_ctx* c, const int32_t* d_prompts, int n_prompts, int P, int G, float* d_logits) {
@@ -564,19 +583,11 @@ rollout_status enqueue_decode(rollout_ctx* c, const int32_t* tokens, int tok_str
   const Dims& D = c->D;
   const Layout& Lo = c->Lo;
   const int S = c->S;
-  const bool fused = D.d % 8 == 0 && D.d / 8 <= 1024;  // embedding and the first norm in one kernel
-  {
-    Scope sc(c, 2, (double)S * D.d * (4 + elem_bytes(D.dtype)), 0);
-    if (fused)
-      HIP_TRY(c, launch_embed_norm(c->stream, D.dtype, c->at(Lo.embed), tokens, tok_stride, col, S, D.d, D.V,
-                                   c->at<float>(Lo.x), c->at<float>(Lo.layers[0].attn_norm), D.eps, c->at(Lo.a),
-                                   c->at<int32_t>(Lo.err)), "embed + norm");
-    else
-      HIP_TRY(c, launch_embed(c->stream, D.dtype, c->at(Lo.embed), tokens, tok_stride, col, S, D.d, D.V,
-                              c->at<float>(Lo.x), c->at<int32_t>(Lo.err)), "embed");
-  }
+  bool normed;
+  rollout_status r = embed_rows(c, tokens, tok_stride, col, S, &normed);
+  if (r) return r;
   RowMap rm{c->at<int32_t>(Lo.ctx_len), 0, 1, 0};
-  rollout_status r = forward_layers(c, S, rm, ctx_max, (double)S * (c->cur_len + 1), fused);
+  r = forward_layers(c, S, rm, ctx_max, (double)S * (c->cur_len + 1), normed);
   if (r) return r;
   int s;
   r = gemm(c, c->at(Lo.a), c->at(Lo.lm_head), d_logits, S, D.V, D.d, 1, &s);
