@@ -27,6 +27,7 @@
 // log-sum-exp weights in split order.
 //
 // Cache layout: [layer][block][kv head][K: blk x hd | V: hd x blk] (kv_offset).
+#include <algorithm>
 #include <cstdlib>
 
 #include "internal.h"
@@ -250,15 +251,25 @@ struct AttnQKV {
   // rotated q is kept in q_keep, and the unnormalised softmax state goes to st_o / st_ml
   int t_begin;
   uint16_t* q_keep;
-  float* st_o;   // [row][head][HD]: sum of p * v relative to the state's max
-  float* st_ml;  // [row][head][2]: max, sum of p
+  float* st_o;   // [row][head][part][HD]: sum of p * v relative to the state's max
+  float* st_ml;  // [row][head][part][2]: max, sum of p
+  int parts;     // workgroups that share a row's context (kParts; else 1)
 };
+
+// What a workgroup of k_attn_mfma covers and leaves:
+//   kWhole: the row's whole context, normalised output;
+//   kSuffix: keys from t_begin on, state and rotated q left for k_attn_prefix;
+//   kParts: one of `parts` runs of 16-token tiles (shared out by the row's own position), state left for
+//     k_attn_merge.  Every part forms q again (from L2); the last one appends k and v and holds the current
+//     token.  For batches whose (row, KV head) pairs leave CUs idle (attn_parts).
+enum AttnMode { kWhole, kSuffix, kParts };
+constexpr int kMaxParts = 32;
 
 // ONE: every column group of the q/k/v formation fits one per thread ((nrep + 2) * HD / 4 <= NW * 64), so
 // the partials of a single group are held (fewer registers, more workgroups per CU); else up to 16 query
 // heads per KV head.  QBX: QKV split partials loaded with the block table (0: kQkvBatch, half for ONE); the
 // launch takes 4 when the QKV projection has at most 4 splits, so no loads are spent on surplus partials.
-template <int HD, int NW, int DR, bool SPLIT = false, bool ONE = false, int QBX = 0>
+template <int HD, int NW, int DR, int MODE = kWhole, bool ONE = false, int QBX = 0>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ONE && NW == 4 ? 3 : 1)))
 void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t* __restrict__ tables, int max_blocks,
                  RowMap rm, int R, int layer, AttnQKV Q, uint16_t* __restrict__ out, int32_t* __restrict__ err) {
@@ -277,8 +288,11 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   // XCD-aware order (workgroup b runs on XCD b % 8, and the grid is a multiple of 8): each XCD takes a
   // contiguous range of (row, KV head) items, so the rows of one group -- which read the same prompt KV
   // blocks -- fetch them into one L2 instead of all eight
-  const int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-  if (item >= R * D.nkv) return;
+  int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (item >= R * D.nkv * (MODE == kParts ? Q.parts : 1)) return;
+  const int part = MODE == kParts ? item % Q.parts : 0;
+  if constexpr (MODE == kParts) item /= Q.parts;
+  const bool last = MODE != kParts || part == Q.parts - 1;  // holds the current token
   const int kvh = item % D.nkv;
   const int r = item / D.nkv;
   int seq, pos;
@@ -292,7 +306,13 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   const size_t block_stride = (size_t)D.nkv * kv_head_stride;
   const int32_t* trow = tables + (size_t)seq * max_blocks;
   const float scale = 1.0f / sqrtf((float)HD);
-  const int t_end = pos;  // keys read from the cache
+  // keys read from the cache: t_begin .. t_end - 1
+  int t_begin = MODE == kSuffix ? Q.t_begin : 0, t_end = pos;
+  if constexpr (MODE == kParts) {
+    const int per = ((pos + 15) / 16 + Q.parts - 1) / Q.parts * 16;
+    t_begin = part * per;
+    t_end = min(pos, t_begin + per);
+  }
   // One round trip for the block table, the row's rotary factors and the first QB QKV split
   // partials of this thread's column groups (float4 groups; every load in flight at once).  The table
   // goes to LDS as soon as it arrives and the first K/V tiles go out before the partials are summed, so
@@ -336,7 +356,7 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   // registers: while one is attended, the next DR - 1 are loading.  The first
   // DR loads go out before q/k/v are rotated, so they overlap that work.
   constexpr int STRIDE = 16 * NW;
-  const int first = (SPLIT ? Q.t_begin : 0) + 16 * wave;
+  const int first = t_begin + 16 * wave;
   const int n_w = t_end > first ? (t_end - first + STRIDE - 1) / STRIDE : 0;
   bool bad = false;
   KVTile<HD> ring[DR];
@@ -388,7 +408,7 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   const float* cs = s_rope;
   const float* sn = s_rope + half;
   const int b = trow[pos / blk];
-  const bool bok = b >= 0 && b < n_blocks;
+  const bool bvalid = b >= 0 && b < n_blocks, bok = bvalid && last;
   uint16_t* kdst = kv + (size_t)(bok ? b : 0) * block_stride + layer_base;
   const int npair = (nrep + 1) * half;
   for (int it = tid; it < npair + HD; it += NT) {
@@ -400,7 +420,7 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
       if (h < nrep) {
         s_q[h][i] = b1;
         s_q[h][i + half] = b2;
-        if constexpr (SPLIT) {
+        if constexpr (MODE == kSuffix) {
           uint16_t* qk = Q.q_keep + (size_t)r * D.qd + (size_t)(kvh * nrep + h) * HD;
           qk[i] = b1;
           qk[i + half] = b2;
@@ -420,7 +440,7 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
       if (bok) kdst[blk_elems + (size_t)i * blk + pos % blk] = bv;
     }
   }
-  if (!bok && tid == 0) atomicOr(err, 2);
+  if (!bvalid && last && tid == 0) atomicOr(err, 2);
   for (int it = tid; it < (16 - nrep) * HD; it += NT) s_q[nrep + it / HD][it % HD] = 0;
   lds_barrier();  // LDS only: the tile loads and the cache stores stay in flight
 #pragma unroll
@@ -456,7 +476,7 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   const int Mb = (R + 15) >> 4;
   for (int item = tid; item < nrep * (HD / 8); item += NT) {
     const int h = item / (HD / 8), d0 = (item % (HD / 8)) * 8;
-    float mx = s_cur[h];
+    float mx = last ? s_cur[h] : -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w)
       if (s_l[w][h] > 0.f) mx = fmaxf(mx, s_m[w][h]);
@@ -470,12 +490,14 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
         for (int e = 0; e < 8; ++e) num[e] += wt * s_o[w][h][d0 + e];
       }
     }
-    const float wc = expf(s_cur[h] - mx);
-    den += wc;
+    if (last) {
+      const float wc = expf(s_cur[h] - mx);
+      den += wc;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) num[e] += wc * s_kv[1][d0 + e];
-    if constexpr (SPLIT) {
-      const size_t hr = (size_t)r * D.nh + kvh * nrep + h;
+      for (int e = 0; e < 8; ++e) num[e] += wc * s_kv[1][d0 + e];
+    }
+    if constexpr (MODE != kWhole) {
+      const size_t hr = ((size_t)r * D.nh + kvh * nrep + h) * Q.parts + part;
       float4* so = reinterpret_cast<float4*>(Q.st_o + hr * HD + d0);
       so[0] = make_float4(num[0], num[1], num[2], num[3]);
       so[1] = make_float4(num[4], num[5], num[6], num[7]);
@@ -812,6 +834,50 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(Dims D, const uint16_t*
     }
 }
 
+// The merge of a row's parts (kParts): one workgroup per (row, query head).  Every wave holds the parts'
+// (max, sum) one per lane, so the weights are a wave reduction and a shuffle away; a thread takes eight
+// dimensions of every (256 / (HD / 8))th part, all its loads in flight with the statistics', and the threads'
+// sums meet in LDS in thread order.  One round trip: 10.7 -> 4.6 us against k_attn_combine, whose threads walk the
+// parts one after the other (4 rows, 28 heads, 16 parts).
+template <int HD>
+__global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ st_o, const float* __restrict__ st_ml,
+                                                    int R, int nh, int parts, uint16_t* __restrict__ out) {
+  constexpr int G8 = HD / 8, PL = 256 / G8;       // dimension groups, part lanes
+  constexpr int NP = (kMaxParts + PL - 1) / PL;   // parts a thread takes at most
+  __shared__ float s_o[PL][HD + 4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const size_t rh = blockIdx.x;
+  const int r = (int)(rh / nh), h = (int)(rh % nh);
+  const int g = tid % G8, p0 = tid / G8;
+  const float2 st = *reinterpret_cast<const float2*>(st_ml + (rh * parts + min(lane, parts - 1)) * 2);
+  float v[NP][8];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) ld8(st_o, (rh * parts + min(p0 + i * PL, parts - 1)) * HD + 8 * g, v[i]);
+  const bool has = lane < parts && st.y > 0.f;
+  const float mx = wave_max(has ? st.x : -INFINITY);
+  const float w = has ? expf(st.x - mx) : 0.f;
+  const float den = wave_sum(has ? w * st.y : 0.f);
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int p = p0 + i * PL;
+    const float wp = __shfl(w, min(p, parts - 1), 64);
+    if (p < parts && wp > 0.f) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += wp * v[i][e];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s_o[p0][8 * g + e] = acc[e];
+  __syncthreads();
+  if (tid < HD) {
+    float o = 0.f;
+#pragma unroll
+    for (int i = 0; i < PL; ++i) o += s_o[i][tid];
+    stf(out, xoff(out, r, h * HD + tid, nh * HD, (R + 15) >> 4), den > 0.f ? o / den : 0.f);
+  }
+}
+
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void k_attn_valu(Dims D, const T* __restrict__ q, const T* __restrict__ kv,
                                                    int n_blocks, const int32_t* __restrict__ tables, int max_blocks,
@@ -969,8 +1035,22 @@ int attn_waves(int n_workgroups) {
   return n_workgroups >= 256 ? 4 : 8;
 }
 
-// k_attn_mfma grid: one workgroup per (row, KV head), rounded up to a multiple of the 8 XCDs
-static unsigned attn_grid(int R, const Dims& D) { return (unsigned)(R * D.nkv + 7) / 8 * 8; }
+// k_attn_mfma grid: one workgroup per (row, KV head) (and part), rounded up to a multiple of the 8 XCDs
+static unsigned attn_grid(int R, const Dims& D, int parts = 1) { return (unsigned)(R * D.nkv * parts + 7) / 8 * 8; }
+
+// Parts that a decode row's context is shared out to (1: none), from the batch's (row, KV head) pairs and the
+// longest context of the call.  A pair's workgroup takes 1.6 us per round of its eight waves' tiles, alone on
+// its CU; shared out, a pair costs the combine kernel (4 us) more.  So contexts of at least kPartMinTokens
+// (eight rounds) on at most half the CUs are shared out until the CUs are used, 64 tokens a part or more.
+// 4 rows of 7B width (16 pairs), context 3,000, 16 parts:
+// prefix and suffix pass 40 + 9.6 us a layer, in parts 11.4 + 4.6; whole decode steps at contexts of 1,100, 2,000
+// and 3,000 tokens gain 3, 9 and 13-25%, and lose 0-3% at 300 if shared out there.
+constexpr int kPartMinTokens = 1024;
+int attn_parts(const Dims& D, int R, int ctx_max) {
+  const int pairs = R * D.nkv;
+  if (!mfma_attention(D) || ctx_max < kPartMinTokens || pairs > 128) return 1;
+  return std::min(std::min(kMaxParts, 256 / pairs), ctx_max / 64);
+}
 
 bool attention_shares_prefix(const Dims& D) { return mfma_attention(D); }
 
@@ -982,7 +1062,7 @@ hipError_t launch_attention_shared(hipStream_t s, const Dims& D, void* kv_pool, 
   if (!mfma_attention(D) || rm.P != 0 || G < 1 || R % G || p_shared < D.blk || p_shared % D.blk ||
       qkv_splits < 1 || qkv_splits > kMaxQkvSplits || max_blocks > kMaxTableBlocks)
     return hipErrorInvalidValue;
-  const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, p_shared, (uint16_t*)q_keep, st_o, st_ml};
+  const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, p_shared, (uint16_t*)q_keep, st_o, st_ml, 1};
   uint16_t* kk = (uint16_t*)kv_pool;
   uint16_t* oo = (uint16_t*)out;
   // suffix: keys p_shared .. pos of every row, q/k/v formed, state kept
@@ -991,10 +1071,10 @@ hipError_t launch_attention_shared(hipStream_t s, const Dims& D, void* kv_pool, 
 #define ROLLOUT_SUFFIX(HD, NW)                                                                                       \
   do {                                                                                                               \
     if (one_group(D, NW))                                                                                            \
-      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, true, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,          \
+      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, kSuffix, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,          \
                          kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);      \
     else                                                                                                             \
-      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, true>), sgrid, dim3(NW * 64), tab_bytes, s, D,                \
+      hipLaunchKernelGGL((k_attn_mfma<HD, NW, 2, kSuffix>), sgrid, dim3(NW * 64), tab_bytes, s, D,                \
                          kk, n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);      \
   } while (0)
   const int nws = attn_waves(R * D.nkv);
@@ -1041,7 +1121,7 @@ bool attention_forms_qkv(const Dims& D) { return mfma_attention(D); }
 hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* kv_pool, int n_blocks,
                             const int32_t* tables, int max_blocks, RowMap rm, int R, int splits, int split_tokens,
                             int layer, float* opart, float* ml, void* out, int32_t* err, const float* qkv_part,
-                            int qkv_splits, const float* rope_cos, const float* rope_sin) {
+                            int qkv_splits, const float* rope_cos, const float* rope_sin, int parts) {
   if (R <= 0) return hipSuccess;
   if (qkv_part && (!mfma_attention(D) || rm.P != 0 || qkv_splits < 1 || qkv_splits > kMaxQkvSplits))
     return hipErrorInvalidValue;
@@ -1067,8 +1147,32 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
       const int d = v ? std::atoi(v) : 2;
       return d == 3 || d == 4 ? d : 2;
     }();
+    if (parts > 1) {
+      const AttnQKV Qp{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, opart, ml, parts};
+      const dim3 ggrid(attn_grid(R, D, parts));
+      const size_t tab = (size_t)max_blocks * 4;
+#define ROLLOUT_PARTS(HD)                                                                                            \
+  do {                                                                                                               \
+    if (one_group(D, 4))                                                                                             \
+      hipLaunchKernelGGL((k_attn_mfma<HD, 4, 2, kParts, true>), ggrid, dim3(256), tab, s, D, (uint16_t*)kv_pool,     \
+                         n_blocks, tables, max_blocks, rm, R, layer, Qp, (uint16_t*)out, err);                       \
+    else                                                                                                             \
+      hipLaunchKernelGGL((k_attn_mfma<HD, 4, 2, kParts, false, 4>), ggrid, dim3(256), tab, s, D, (uint16_t*)kv_pool, \
+                         n_blocks, tables, max_blocks, rm, R, layer, Qp, (uint16_t*)out, err);                       \
+  } while (0)
+      if (D.hd == 128) ROLLOUT_PARTS(128);
+      else ROLLOUT_PARTS(64);
+#undef ROLLOUT_PARTS
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      if (D.hd == 128)
+        hipLaunchKernelGGL(k_attn_merge<128>, dim3(R * D.nh), dim3(256), 0, s, opart, ml, R, D.nh, parts, (uint16_t*)out);
+      else
+        hipLaunchKernelGGL(k_attn_merge<64>, dim3(R * D.nh), dim3(256), 0, s, opart, ml, R, D.nh, parts, (uint16_t*)out);
+      return hipGetLastError();
+    }
     const dim3 grid(attn_grid(R, D));
-    const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, nullptr, nullptr};
+    const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, nullptr, nullptr, 1};
     uint16_t* kk = (uint16_t*)kv_pool;
     uint16_t* oo = (uint16_t*)out;
     const size_t tab_bytes = (size_t)max_blocks * 4;
@@ -1076,14 +1180,14 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
   do {                                                                                                                 \
     if constexpr (DR == 2) {                                                                                           \
       if (one_group(D, NW)) {                                                                                          \
-        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, false, true>), grid, dim3(NW * 64), tab_bytes, s, D, kk, n_blocks, \
+        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, kWhole, true>), grid, dim3(NW * 64), tab_bytes, s, D, kk, n_blocks, \
                            tables, max_blocks, rm, R, layer, Q, oo, err);                                              \
         break;                                                                                                         \
       }                                                                                                                \
     }                                                                                                                  \
     if constexpr (DR == 2 && NW == 4) {                                                                                \
       if (qkv_splits <= 4) {                                                                                           \
-        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, false, false, 4>), grid, dim3(NW * 64), tab_bytes, s, D, kk,       \
+        hipLaunchKernelGGL((k_attn_mfma<HD, NW, DR, kWhole, false, 4>), grid, dim3(NW * 64), tab_bytes, s, D, kk,       \
                            n_blocks, tables, max_blocks, rm, R, layer, Q, oo, err);                                    \
         break;                                                                                                         \
       }                                                                                                                \

@@ -123,7 +123,9 @@ bool attention_forms_qkv(const Dims& D);
 hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* kv_pool, int n_blocks,
                             const int32_t* tables, int max_blocks, RowMap rm, int R, int splits, int split_tokens,
                             int layer, float* opart, float* ml, void* out, int32_t* err, const float* qkv_part,
-                            int qkv_splits, const float* rope_cos, const float* rope_sin);
+                            int qkv_splits, const float* rope_cos, const float* rope_sin, int parts);
+// workgroups that share a decode row's context (launch_attention's parts; opart and ml hold R x n_heads x parts)
+int attn_parts(const Dims& D, int R, int ctx_max);
 // Decode attention with the group's shared prompt read once per group: a suffix pass over each row's own
 // keys (p_shared .. pos; q/k/v formed from the QKV split partials as above, rotated q kept in q_keep,
 // softmax state in st_o [R][nh][hd] / st_ml [R][nh][2]) and a prefix pass over the shared blocks that

@@ -395,14 +395,16 @@ rollout_status proj(rollout_ctx* c, const void* X, const void* W, float* out, in
 
 // Whether a decode batch takes the shared-prefix attention (whole groups of G >= 2 sequences whose prompt
 // fills at least one KV block).  By default only when G x shared prompt tokens >= 8192: below that the
-// group's redundant prompt reads are served by the caches and the extra pass costs more than it saves.
+// group's redundant prompt reads are served by the caches and the extra pass costs more than it saves.  Nor
+// when the rows' contexts are shared out (attn_parts): so few rows leave the prefix pass on a few CUs (one
+// group of 4, 3,000 tokens at 7B width: 16 workgroups, 40 us).
 // ROLLOUT_SHARED_PREFIX=0 never takes it, =2 always does (read per call).
-bool use_shared_prefix(const rollout_ctx* c, int M, const RowMap& rm) {
+bool use_shared_prefix(const rollout_ctx* c, int M, const RowMap& rm, int parts) {
   const char* v = std::getenv("ROLLOUT_SHARED_PREFIX");
   const int mode = v ? std::atoi(v) : 1;
   const int p_shared = c->P / c->D.blk * c->D.blk;
   if (mode == 0 || !c->wave || c->seq_refill || c->G < 2 || p_shared < c->D.blk || M % c->G || rm.seq0 % c->G) return false;
-  return mode == 2 || (int64_t)c->G * p_shared >= 8192;
+  return mode == 2 || (parts == 1 && (int64_t)c->G * p_shared >= 8192);
 }
 
 // One transformer pass over M rows (prefill chunk or decode batch). On return
@@ -431,8 +433,11 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
     HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, nullptr, 1, M, D.d, x, c->at<float>(Lo.layers[0].attn_norm),
                                     D.eps, a), "rmsnorm");
   }
-  // decode rows of whole groups read their group's shared prompt blocks once per group (shared-prefix attention)
-  const int p_shared = (rm.P == 0 && attention_shares_prefix(D) && use_shared_prefix(c, M, rm)) ? c->P / D.blk * D.blk : 0;
+  // decode rows: a few long contexts are shared out over the CUs (bounded by the state buffers)
+  int parts = rm.P == 0 ? attn_parts(D, M, attn_ctx_max) : 1;
+  parts = std::max(1, (int)std::min<int64_t>(parts, (int64_t)Lo.R * Lo.attn_splits_max / M));
+  // rows of whole groups read their group's shared prompt blocks once per group (shared-prefix attention)
+  const int p_shared = (rm.P == 0 && attention_shares_prefix(D) && use_shared_prefix(c, M, rm, parts)) ? c->P / D.blk * D.blk : 0;
   for (int l = 0; l < D.L; ++l) {
     const Layer& y = Lo.layers[l];
     int s;
@@ -455,7 +460,7 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
       else
         HIP_TRY(c, launch_attention(c->stream, D, q, kv, c->n_blocks, tables, Lo.max_blocks, rm, M, asplits, st_tok, l,
                                     opart, ml, o, err, attn_qkv ? part : nullptr, s, c->at<float>(Lo.rope_cos),
-                                    c->at<float>(Lo.rope_sin)), "attention");
+                                    c->at<float>(Lo.rope_sin), parts), "attention");
     }
     r = proj(c, o, c->at(y.wo), part, M, D.d, D.qd, &s);
     if (r) return r;

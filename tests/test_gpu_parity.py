@@ -362,6 +362,41 @@ def test_bf16_tile_gemm_rows(n_prompts, P):
     eng.close()
 
 
+# decode rows whose context is shared out over workgroups (calls that may reach 1,024 tokens on few rows): early
+# positions leave most parts empty, parts of one tile, several tiles a wave, one and seven column groups, 32 parts
+PARTS_ATTN = [
+    # (model shape, block size, prompts, G, prompt length)
+    ((1, 256, 14, 2, 128, 256, 2048, 1e6), 16, 1, 2, 5), ((1, 256, 14, 2, 128, 256, 2048, 1e6), 8, 3, 1, 513),
+    ((1, 256, 4, 1, 64, 256, 2048, 1e6), 32, 1, 3, 33), ((1, 256, 4, 1, 128, 256, 2048, 1e6), 16, 2, 2, 1027),
+]
+
+
+@pytest.mark.parametrize("shape,blk,n_prompts,G,P", PARTS_ATTN)
+def test_bf16_decode_attention_parts(shape, blk, n_prompts, G, P, monkeypatch):
+    set_attn_knobs(monkeypatch, "1", None)
+    log(f"bf16 decode attention in parts shape={shape} blk={blk} prompts={n_prompts} G={G} P={P}")
+    S, N = n_prompts * G, 4
+    cfg = R.model_config(shape, R.DTYPE_BF16, P, max(N, 1030 - P), S, kv_block_size=blk)
+    eng = R.Engine(cfg)
+    model = OracleModel(shape_of(cfg), mode="bf16")
+    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=61)
+    ref = rollout(model, prompts, G, N, 1.0, 1.0, W.uniforms(S, N, seed=62))
+    logits = torch.empty((S, cfg.vocab), dtype=torch.float32, device="cuda:0")
+    # stale values (NaN bit patterns) in the pool must not reach the outputs
+    eng.arena[eng.plan.arena_bytes - eng.plan.kv_bytes:].fill_(255)
+    torch.cuda.synchronize()
+    R.rollout_prefill(eng.ctx, to_dev(prompts, torch), n_prompts, P, G, logits)
+    eng.synchronize()
+    err = [float(np.max(np.abs(logits.cpu().numpy() - ref["logits"][0])))]
+    for t in range(1, N):
+        R.rollout_decode_step(eng.ctx, to_dev(ref["tokens"][:, t - 1], torch), logits)
+        eng.synchronize()
+        err.append(float(np.max(np.abs(logits.cpu().numpy() - ref["logits"][t]))))
+    log(f"  max abs logit error per step: {[round(e, 5) for e in err]}")
+    assert max(err) <= 3e-2  # the bf16 contract's bound, as in the tests above
+    eng.close()
+
+
 @pytest.mark.parametrize("shared", ["0", "2"])
 def test_bf16_gqa7_context_beyond_4096_tokens_teacher_forced(shared, monkeypatch):
     # A context of more than 256 blocks of 16 (4,096 tokens): the decode attention's workgroup of 256
