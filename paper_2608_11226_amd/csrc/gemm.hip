@@ -92,7 +92,9 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // All sums are bit-equal to the previous kernels' at equal splits (k order).
 //
 // rep: every output row is written rep times, to rows rep * m .. rep * m + rep - 1 (the LM head after a prefill: a
-// prompt's logits for each member of its group).
+// prompt's logits for each member of its group).  rep 0: the product is added to the output instead (O and down
+// projections of one split add to the residual stream: the norm that follows then reads the stream alone, not
+// the stream and a partial, with the same sums; 4,096 x 5,120: norm 70 -> 50 us, the GEMM 281 -> 294).
 //
 // Q4 (int4 weights): W holds the integers q - z, exact in bf16 (k_dequant_q4), and Ws the fp32 scale of every
 // (16-row block, 128-input group, row).  A group's four k-steps sum into P, and acc += s * P in fp32 while the
@@ -240,6 +242,20 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
   for (int j = 0; j < NB; ++j) {
     if (wn * NB + j >= wbc) continue;
     const int n = (wb0 + wn * NB + j) * 16 + 4 * (lane >> 4);
+    if (!SWI && rep == 0) {  // add to the output: a block's loads go out together
+      floatx4_t t[MBW];
+#pragma unroll
+      for (int i = 0; i < MBW; ++i) {
+        const int m = min((mb0 + wm * MBW + i) * 16 + (lane & 15), M - 1);
+        t[i] = *reinterpret_cast<const floatx4_t*>(o + (size_t)m * N + n);
+      }
+#pragma unroll
+      for (int i = 0; i < MBW; ++i) {
+        const int m = (mb0 + wm * MBW + i) * 16 + (lane & 15);
+        if (m < M) *reinterpret_cast<floatx4_t*>(o + (size_t)m * N + n) = t[i] + acc[j][i];
+      }
+      continue;
+    }
 #pragma unroll
     for (int i = 0; i < MBW; ++i) {
       const int m = (mb0 + wm * MBW + i) * 16 + (lane & 15);
@@ -689,13 +705,13 @@ hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, floa
 
 template <bool SWI>
 hipError_t launch_tile_q4(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, const floatx4_t* ws, float* out, int M,
-                          int N, int K, int splits, uint16_t* h) {
+                          int N, int K, int splits, uint16_t* h, int rep) {
   const TilePlan p = tile_plan(M, N, K, splits, splits, true);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
-    default: launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, 1); break;
+    case T_10x8: launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
+    default: launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
   }
   return hipGetLastError();
 }
@@ -879,11 +895,12 @@ int gemm_splits_q4(int M, int N, int K, int max_splits) {
 
 // W: the packed matrix (its scales are read from there); Wi: its integers q - z (launch_dequant_q4)
 hipError_t launch_gemm_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, float* out, int M, int N,
-                               int K, int splits) {
+                               int K, int splits, int rep) {
   if (M <= 0) return hipSuccess;
-  if (M <= kRingMaxRows || N % 16 || K % 128 || splits < 1) return hipErrorInvalidValue;
+  if (M <= kRingMaxRows || N % 16 || K % 128 || splits < 1 || rep < 0 || rep > 1 || (rep == 0 && splits > 1))
+    return hipErrorInvalidValue;
   return launch_tile_q4<false>(s, (const bf16x8_t*)X, (const bf16x8_t*)Wi,
-                               (const floatx4_t*)((const char*)W + q4_code_bytes(N, K)), out, M, N, K, splits, nullptr);
+                               (const floatx4_t*)((const char*)W + q4_code_bytes(N, K)), out, M, N, K, splits, nullptr, rep);
 }
 
 hipError_t launch_gemm_swiglu_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, int M, int N, int K,
@@ -891,7 +908,7 @@ hipError_t launch_gemm_swiglu_q4_tile(hipStream_t s, const void* X, const void* 
   if (M <= 0) return hipSuccess;
   if (M <= kRingMaxRows || N % 32 || K % 128) return hipErrorInvalidValue;
   return launch_tile_q4<true>(s, (const bf16x8_t*)X, (const bf16x8_t*)Wi,
-                              (const floatx4_t*)((const char*)W + q4_code_bytes(N, K)), nullptr, M, N, K, 1, (uint16_t*)h);
+                              (const floatx4_t*)((const char*)W + q4_code_bytes(N, K)), nullptr, M, N, K, 1, (uint16_t*)h, 1);
 }
 
 hipError_t launch_gemm_q4(hipStream_t s, const void* X, const void* W, float* out, int M, int N, int K, int splits) {
@@ -912,10 +929,15 @@ int gemm_splits(int dtype, int M, int N, int K, int max_splits) {
   return tile_plan(M, N, K, 1, std::max(1, std::min(max_splits, K / 256))).splits;
 }
 
+bool gemm_adds(int dtype, int M, int splits) {
+  return dtype == ROLLOUT_DTYPE_BF16 && M > kRingMaxRows && splits == 1;
+}
+
 hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const void* W, float* out, int M, int N,
                        int K, int splits, int rep) {
   if (M <= 0) return hipSuccess;
-  if (rep < 1 || (rep > 1 && splits > 1)) return hipErrorInvalidValue;
+  // adding is k_gemm_pp's only (see gemm_adds)
+  if (rep < 0 || (rep != 1 && splits > 1) || (rep == 0 && !gemm_adds(dtype, M, splits))) return hipErrorInvalidValue;
   if (dtype != ROLLOUT_DTYPE_BF16) {
     dim3 grid((N + 15) / 16, (M + 15) / 16);
     hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, (const float*)X, ldx, (const float*)W, out, M, N, K, rep);

@@ -79,7 +79,9 @@ hipError_t launch_export(hipStream_t s, const void* src, int dtype, const Weight
 
 // out[split][m][n] = sum over the split's k range of X[m][k] * W[n][k] (fp32).
 int gemm_splits(int dtype, int M, int N, int K, int max_splits);
-// With rep > 1 (one split) every output row m is written rep times, to rows rep * m .. rep * m + rep - 1.
+// With rep > 1 (one split) every output row m is written rep times, to rows rep * m .. rep * m + rep - 1; with rep 0
+// (where gemm_adds) the product is added to out.
+bool gemm_adds(int dtype, int M, int splits);
 hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const void* W, float* out, int M,
                        int N, int K, int splits, int rep);
 
@@ -95,7 +97,7 @@ int gemm_splits_q4(int M, int N, int K, int max_splits);
 hipError_t launch_gemm_q4(hipStream_t s, const void* X, const void* W, float* out, int M, int N, int K, int splits);
 hipError_t launch_gemm_swiglu_q4(hipStream_t s, const void* X, const void* W, int M, int N, int K, void* h);
 hipError_t launch_gemm_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, float* out, int M, int N,
-                               int K, int splits);
+                               int K, int splits, int rep);
 hipError_t launch_gemm_swiglu_q4_tile(hipStream_t s, const void* X, const void* W, const void* Wi, int M, int N, int K,
                                       void* h);
 

@@ -336,7 +336,7 @@ struct Scope {
 };
 
 rollout_status gemm(rollout_ctx* c, const void* X, const void* W, float* out, int M, int N, int K, int max_splits,
-                    int* splits_out, int rep = 1) {
+                    int* splits_out, int rep = 1, float* residual = nullptr) {
   const Dims& D = c->D;
   // as many splits as the workspace holds (max_splits 1: the output is not the workspace)
   if (max_splits > 1) max_splits = (int)std::min<size_t>(max_splits, c->Lo.part_elems / ((size_t)M * N));
@@ -344,8 +344,9 @@ rollout_status gemm(rollout_ctx* c, const void* X, const void* W, float* out, in
   const int s = gemm_splits(D.dtype, M, N, K, max_splits);
   const double eb = (double)elem_bytes(D.dtype);
   Scope sc(c, 0, (double)N * K * eb + (double)M * K * eb + (double)M * rep * N * 4, 2.0 * M * N * K);
-  HIP_TRY(c, launch_gemm(c->stream, D.dtype, X, K, W, out, M, N, K, s, rep), "gemm");
-  *splits_out = s;
+  const bool add = residual && rep == 1 && gemm_adds(D.dtype, M, s);
+  HIP_TRY(c, launch_gemm(c->stream, D.dtype, X, K, W, add ? residual : out, M, N, K, s, add ? 0 : rep), "gemm");
+  *splits_out = add ? 0 : s;
   return ROLLOUT_OK;
 }
 
@@ -375,8 +376,11 @@ rollout_status gemm_swiglu(rollout_ctx* c, const void* X, const void* W, int M, 
 
 // A layer projection.  int4 matrices take the int4 ring GEMM for decode batches; larger batches write the
 // matrix's integers out first and take the tile GEMM on them.
-rollout_status proj(rollout_ctx* c, const void* X, const void* W, float* out, int M, int N, int K, int* splits_out) {
-  if (!c->D.wq4) return gemm(c, X, W, out, M, N, K, kMaxSplits, splits_out);
+// With residual, a projection of one split (gemm_adds) adds its output there instead of writing a partial, and
+// *splits_out is 0.
+rollout_status proj(rollout_ctx* c, const void* X, const void* W, float* out, int M, int N, int K, int* splits_out,
+                    float* residual = nullptr) {
+  if (!c->D.wq4) return gemm(c, X, W, out, M, N, K, kMaxSplits, splits_out, 1, residual);
   const bool tile = M > kSwigluMaxRows;
   const int smax = (int)std::min<size_t>(kMaxSplits, c->Lo.part_elems / ((size_t)M * N));
   if (smax < 1) return fail(c, ROLLOUT_EINVAL, "internal: split-K workspace too small");
@@ -385,11 +389,13 @@ rollout_status proj(rollout_ctx* c, const void* X, const void* W, float* out, in
   const int s = gemm_splits_q4(M, N, K, smax);
   const double wb = tile ? (double)N * K * 2 : (double)(q4_code_bytes(N, K) + q4_sz_bytes(N, K));
   Scope sc(c, 0, wb + (double)M * K * 2 + (double)s * M * N * 4, 2.0 * M * N * K);
+  const bool add = tile && residual && gemm_adds(c->D.dtype, M, s);
   if (tile)
-    HIP_TRY(c, launch_gemm_q4_tile(c->stream, X, W, c->at(c->Lo.wdq), out, M, N, K, s), "gemm");
+    HIP_TRY(c, launch_gemm_q4_tile(c->stream, X, W, c->at(c->Lo.wdq), add ? residual : out, M, N, K, s, add ? 0 : 1),
+            "gemm");
   else
     HIP_TRY(c, launch_gemm_q4(c->stream, X, W, out, M, N, K, s), "gemm");
-  *splits_out = s;
+  *splits_out = add ? 0 : s;
   return ROLLOUT_OK;
 }
 
@@ -462,11 +468,11 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
                                     opart, ml, o, err, attn_qkv ? part : nullptr, s, c->at<float>(Lo.rope_cos),
                                     c->at<float>(Lo.rope_sin), parts), "attention");
     }
-    r = proj(c, o, c->at(y.wo), part, M, D.d, D.qd, &s);
+    r = proj(c, o, c->at(y.wo), part, M, D.d, D.qd, &s, x);
     if (r) return r;
     {
-      Scope sc(c, 2, (double)s * M * D.d * 4 + (double)M * D.d * (8 + eb), 0);
-      HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, part, s, M, D.d, x, c->at<float>(y.mlp_norm), D.eps, a),
+      Scope sc(c, 2, (double)s * M * D.d * 4 + (double)M * D.d * ((s ? 8 : 4) + eb), 0);
+      HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, s ? part : nullptr, s, M, D.d, x, c->at<float>(y.mlp_norm), D.eps, a),
               "residual norm");
     }
     // SwiGLU in the gate/up GEMM's epilogue
@@ -477,12 +483,12 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
       Scope sc(c, 2, (double)s * M * 2 * D.ff * 4 + (double)M * D.ff * eb, 0);
       HIP_TRY(c, launch_swiglu(c->stream, D.dtype, part, s, M, D.ff, h), "swiglu");
     }
-    r = proj(c, h, c->at(y.wdown), part, M, D.d, D.ff, &s);
+    r = proj(c, h, c->at(y.wdown), part, M, D.d, D.ff, &s, x);
     if (r) return r;
     {
       const float* next_gain = l + 1 < D.L ? c->at<float>(Lo.layers[l + 1].attn_norm) : c->at<float>(Lo.final_norm);
-      Scope sc(c, 2, (double)s * M * D.d * 4 + (double)M * D.d * (8 + eb), 0);
-      HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, part, s, M, D.d, x, next_gain, D.eps, a), "residual norm");
+      Scope sc(c, 2, (double)s * M * D.d * 4 + (double)M * D.d * ((s ? 8 : 4) + eb), 0);
+      HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, s ? part : nullptr, s, M, D.d, x, next_gain, D.eps, a), "residual norm");
     }
   }
   return ROLLOUT_OK;
