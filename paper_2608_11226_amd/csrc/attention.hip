@@ -882,8 +882,8 @@ template <typename T, int HD>
 __global__ __launch_bounds__(256) void k_attn_valu(Dims D, const T* __restrict__ q, const T* __restrict__ kv,
                                                    int n_blocks, const int32_t* __restrict__ tables, int max_blocks,
                                                    RowMap rm, int splits, int split_tokens, int layer,
-                                                   float* __restrict__ opart, float* __restrict__ ml,
-                                                   int32_t* __restrict__ err) {
+                                                   float* __restrict__ opart, float* __restrict__ ml, int R,
+                                                   T* __restrict__ out, int32_t* __restrict__ err) {
   constexpr int TT = 32;
   constexpr int NACC = 16 * HD / 256;
   __shared__ float qs[16][HD];
@@ -971,6 +971,16 @@ __global__ __launch_bounds__(256) void k_attn_valu(Dims D, const T* __restrict__
       }
     }
     __syncthreads();
+  }
+  if (splits == 1) {  // nothing to merge: the normalised output
+#pragma unroll
+    for (int j = 0; j < NACC; ++j) {
+      const int idx = tid + 256 * j;
+      const int h = idx / HD, dd = idx - h * HD;
+      if (h < nrep)
+        stf(out, xoff(out, r, (kvh * nrep + h) * HD + dd, D.qd, (R + 15) >> 4), l_s[h] > 0.f ? acc[j] / l_s[h] : 0.f);
+    }
+    return;
   }
 #pragma unroll
   for (int j = 0; j < NACC; ++j) {
@@ -1211,7 +1221,7 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
   const dim3 grid((unsigned)R * D.nkv * splits);
 #define ROLLOUT_ATTN(T, HD)                                                                                        \
   hipLaunchKernelGGL((k_attn_valu<T, HD>), grid, dim3(256), 0, s, D, (const T*)q, (const T*)kv_pool, n_blocks, tables, \
-                     max_blocks, rm, splits, split_tokens, layer, opart, ml, err)
+                     max_blocks, rm, splits, split_tokens, layer, opart, ml, R, (T*)out, err)
   if (D.dtype == ROLLOUT_DTYPE_BF16) {
     ROLLOUT_ATTN(uint16_t, 32);
   } else {
@@ -1221,7 +1231,7 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
   }
 #undef ROLLOUT_ATTN
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || splits == 1) return e;
   // merge the context splits into the output
   const dim3 cgrid(R, ((D.qd >> 3) + 63) / 64);
   if (D.dtype == ROLLOUT_DTYPE_BF16)

@@ -44,8 +44,8 @@
 // write a projection's integers q - z (exact in bf16) into fragments first and take k_gemm_pp on those,
 // which scales every group's sum in fp32.
 //
-// fp32 path: a plain LDS-tiled VALU GEMM over row-major X and W (the fp32
-// path exists for exact parity on small models, not for speed).
+// fp32 path: fp32 MFMAs over row-major X and W (the fp32 path exists for exact
+// parity on small models).
 #include <algorithm>
 #include <cmath>
 
@@ -565,28 +565,75 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 }
 
+// fp32 path, v_mfma_f32_16x16x4_f32 (fp32 products and sums): a workgroup of four waves owns MT x NT tiles of 16
+// rows x 16 outputs, and the waves share out K in runs of 16 (their sums meet in LDS in wave order).  Lane (r, g)
+// = (lane % 16, lane / 16) loads four consecutive k of row r at 4 g by one 16-byte load of each operand; four
+// MFMAs then take element e of both, i.e. k = 4 g + e of every lane group, so the loads need no rearranging and
+// nothing passes through LDS on the way in.  A wave's loads of U runs go out together (indices clamped, surplus
+// runs not multiplied): at the small fp32 models' sizes a launch is a few round trips, not bandwidth.  8 rows: 128
+// outputs over K = 512 12.1 -> 3.8 us, 1,024 over 128 5.9 -> 3.9 us against an LDS-tiled kernel of one output a thread
+// that waited for memory and two barriers every 32 k.
+template <int MT, int NT>
 __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ X, int ldx, const float* __restrict__ W,
                                                   float* __restrict__ out, int M, int N, int K, int rep) {
-  __shared__ float xs[16][33];
-  __shared__ float ws[16][33];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
-  float acc = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    for (int i = threadIdx.x; i < 512; i += 256) {
-      const int r = i >> 5, c = i & 31;
-      const int k = k0 + c;
-      xs[r][c] = (m0 + r < M && k < K) ? X[(size_t)(m0 + r) * ldx + k] : 0.f;
-      ws[r][c] = (n0 + r < N && k < K) ? W[(size_t)(n0 + r) * K + k] : 0.f;
-    }
-    __syncthreads();
+  constexpr int U = MT * NT > 1 ? 4 : 8;
+  __shared__ floatx4_t red[3][MT][NT][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
+  const int runs = K >> 4, per = (runs + 3) / 4;
+  const int c0 = wave * per, c1 = min(runs, c0 + per);
+  const float* wp[NT];
+  const float* xp[MT];
 #pragma unroll
-    for (int c = 0; c < 32; ++c) acc += xs[ty][c] * ws[tx][c];
-    __syncthreads();
+  for (int j = 0; j < NT; ++j) wp[j] = W + (size_t)min(n0 + 16 * j + r, N - 1) * K + 4 * g;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xp[i] = X + (size_t)min(m0 + 16 * i + r, M - 1) * ldx + 4 * g;
+  floatx4_t acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  for (int c = c0; c < c1; c += U) {
+    floatx4_t w[U][NT], x[U][MT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(c + u, c1 - 1) * 16;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) w[u][j] = *reinterpret_cast<const floatx4_t*>(wp[j] + k);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) x[u][i] = *reinterpret_cast<const floatx4_t*>(xp[i] + k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c + u < c1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][j][e], x[u][i][e], acc[i][j], 0, 0, 0);
+      }
   }
-  const int m = m0 + ty, n = n0 + tx;
-  if (m < M && n < N)
-    for (int c = 0; c < rep; ++c) out[((size_t)m * rep + c) * N + n] = acc;
+  if (wave > 0) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) red[wave - 1][i][j][lane] = acc[i][j];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  // D layout: lane holds outputs 4 g .. + 3 of row r
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const floatx4_t v = ((acc[i][j] + red[0][i][j][lane]) + red[1][i][j][lane]) + red[2][i][j][lane];
+      const int m = m0 + 16 * i + r, n = n0 + 16 * j + 4 * g;
+      if (m < M && n < N)
+        for (int c = 0; c < rep; ++c) *reinterpret_cast<floatx4_t*>(out + ((size_t)m * rep + c) * N + n) = v;
+    }
 }
 
 int kslice_for(int K, int splits) {
@@ -939,8 +986,15 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* X, int ldx, const v
   // adding is k_gemm_pp's only (see gemm_adds)
   if (rep < 0 || (rep != 1 && splits > 1) || (rep == 0 && !gemm_adds(dtype, M, splits))) return hipErrorInvalidValue;
   if (dtype != ROLLOUT_DTYPE_BF16) {
-    dim3 grid((N + 15) / 16, (M + 15) / 16);
-    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, (const float*)X, ldx, (const float*)W, out, M, N, K, rep);
+    if (N % 16 || K % 16 || ldx % 4) return hipErrorInvalidValue;
+    // four tiles a workgroup once that leaves two workgroups per CU: half the operand reads per product
+    const dim3 big((N + 31) / 32, (M + 31) / 32), small(N / 16, (M + 15) / 16);
+    if ((size_t)big.x * big.y >= 2 * (size_t)device_cus())
+      hipLaunchKernelGGL((k_gemm_f32<2, 2>), big, dim3(256), 0, s, (const float*)X, ldx, (const float*)W, out, M, N, K,
+                         rep);
+    else
+      hipLaunchKernelGGL((k_gemm_f32<1, 1>), small, dim3(256), 0, s, (const float*)X, ldx, (const float*)W, out, M, N,
+                         K, rep);
     return hipGetLastError();
   }
   if (N % 16 || K % 32) return hipErrorInvalidValue;
