@@ -30,8 +30,8 @@
 // masses, finds the chunk holding the crossing, and walks only that chunk:
 // one contiguous segment per wave, segment totals scanned across waves, then
 // the crossing wave scans its segment 64 ids at a time.  Per row (from 128
-// rows without top-p filtering, from 256 with it): one workgroup makes all of
-// these passes over its row.
+// rows without top-p filtering, from 256 with it, and for small vocabularies):
+// one workgroup makes all of these passes over its row.
 #include "internal.h"
 
 #include <climits>
@@ -807,15 +807,19 @@ __global__ __launch_bounds__(SR) void k_sample_row(const float* __restrict__ log
 // set by one workgroup's passes over its row, so it barely grows with S; the chunked kernels grow with S
 // and win below).  Measured at V = 152064, row / chunked: top-p 0.95: S = 64: 206 / 94 us, S = 128:
 // 210 / 147 us, S = 256: 245 / 258 us; top-p 1 (no digit passes): S = 64: 79 / 60 us, S = 128: 80 / 88 us,
-// S = 256: 90 / 152 us.  ROLLOUT_SAMPLE_PATH=row or =chunked forces a path (read per call; the row path
-// still needs V % 4 == 0 and V <= kRowMaxV).
-constexpr int kRowMinRows = 128, kRowMinRowsFiltered = 256;
-bool use_row_sampler(int S, int V, bool filter) {
-  if (V % 4 != 0 || V > kRowMaxV) return false;
+// S = 256: 90 / 152 us.  Small vocabularies take it at any row count: up to 8,192 ids a row is two rounds of one
+// workgroup's loads, and the chunked kernels are mostly their three or six launches.  Row / chunked, top-p 1 and
+// 0.95: 8 rows of 1,024 ids 9.5 / 16.6 and 18.8 / 30.0 us, 64 rows of 8,192 13.4 / 19.4 and 29.8 / 37.0, of 16,384
+// 16.9 / 19.6 and 37.2 / 36.9, of 32,768 24.5 / 20.6 and 58.1 / 40.0.
+// ROLLOUT_SAMPLE_PATH=row or =chunked forces a path (read per call; the row path still needs V % 4 == 0,
+// V <= kRowMaxV and logits aligned to its 16-byte loads).
+constexpr int kRowMinRows = 128, kRowMinRowsFiltered = 256, kRowSmallV = 8192;
+bool use_row_sampler(const float* logits, int S, int V, bool filter) {
+  if (V % 4 != 0 || V > kRowMaxV || (uintptr_t)logits % 16 != 0) return false;
   const char* v = std::getenv("ROLLOUT_SAMPLE_PATH");
   if (v && std::string(v) == "row") return true;
   if (v && std::string(v) == "chunked") return false;
-  return S >= (filter ? kRowMinRowsFiltered : kRowMinRows);
+  return V <= kRowSmallV || S >= (filter ? kRowMinRowsFiltered : kRowMinRows);
 }
 
 }  // namespace
@@ -875,7 +879,7 @@ hipError_t launch_sample(hipStream_t s, const float* logits, int S, int V, float
     return hipGetLastError();
   }
   const int filter = top_p < 1.0f;
-  if (use_row_sampler(S, V, filter)) {
+  if (use_row_sampler(logits, S, V, filter)) {
     hipLaunchKernelGGL(k_sample_row, dim3(S), dim3(SR), 0, s, logits, V, temperature, top_p, filter, escr, u, u_stride,
                        col, out, out_stride);
     return hipGetLastError();
