@@ -29,6 +29,7 @@
 // Cache layout: [layer][block][kv head][K: blk x hd | V: hd x blk] (kv_offset).
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -656,15 +657,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 // the prompt itself enters P V with weight 0.)
 //
 // Bound: the matrix pipe and the softmax's vector instructions side by side (48 MFMAs of 32 cycles against
-// about 1,400 vector cycles per wave and tile), two waves per SIMD.  Why tiles: one workgroup per token and
-// KV head read the whole prefix again for every token.  Per layer, before -> now: 7B width, one prompt of
-// 3,967 tokens 2,940 -> 224 us (0.75 PFLOP/s of MFMA work); 8 x 512 tokens at 14B width 797 -> 54 us; 8 x 256 at
-// 7B width 173 -> 20 us; 4 x 512 at 72B width 485 -> 45 us; one prompt of 203 tokens 23 -> 13 us.
+// about 1,500 vector cycles per wave and tile), two waves per SIMD; the pipe is busy half of the time.  Why tiles:
+// one workgroup per token and KV head read the whole prefix again for every token.  Per layer, before -> now: 7B
+// width, one prompt of 3,967 tokens 2,940 -> 196 us (0.88 PFLOP/s of MFMA work); 8 x 512 tokens at 14B width
+// 797 -> 53 us; 8 x 256 at 7B width 173 -> 20 us; 4 x 512 at 72B width 485 -> 44 us; one prompt of 203 tokens
+// 23 -> 13 us.  The lazy maximum (kPreGrow) and the block addresses kept by the wave took the first from 224 to 196;
+// the next tile's scores computed beside this tile's exponentials (K a tile ahead of V) gained nothing (199).
 constexpr int kPreCols = 128, kPreKeys = 64;
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 typedef float floatx2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+constexpr float kPreGrow = 8.f;
+
+// maximum over a lane and the lane 32 away
+__device__ __forceinline__ float half_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
 __device__ __forceinline__ int kv_perm(int a) { return (a & ~12) | ((a & 4) << 1) | ((a & 8) >> 1); }
 
@@ -716,25 +727,37 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(Dims D, const uint16_t*
   for (int c = 0; c < KS; ++c)
     qf[c] = *reinterpret_cast<const bf16x8_t*>(q + (size_t)row * D.qd + (size_t)head * HD + 16 * c + 8 * half);
 
-  auto load = [&](int buf, int tile) {
-    const int t0 = tile * kPreKeys;
-    // K: rows 16 wave .. + 15; an instruction covers 64 / CH rows, row chunk j stored at j ^ (kv_perm(row) % CH)
-    const uint16_t* src[HD / 32];
+  // K rows 16 wave .. + 15 of a tile: an instruction covers 64 / CH rows, row chunk j stored at j ^ (kv_perm(row) %
+  // CH).  V: fragments of key step `wave`; lane = dimension (permuted) + 32 * (eight-key half).  A tile starts at
+  // a multiple of 64, so a lane's place inside its block is the same in every tile; only the block id changes
+  // (past the prompt: its last block's, whose rows there are masked or zeroed).
+  const int ntab = (P + blk - 1) >> sh;
+  // The 64 / CH rows of one K instruction lie in one block: its base is the wave's, a lane adds its row and chunk.
+  constexpr int KR = 64 / CH;
+  const char* kbase = (const char*)(kv + layer_base);
+  uint32_t koff[HD / 32];
 #pragma unroll
-    for (int i = 0; i < HD / 32; ++i) {
-      const int r = 16 * wave + i * (64 / CH) + lane / CH;
-      const int t = min(t0 + r, P - 1);
-      const int ch = (lane % CH) ^ (kv_perm(r & 15) & (CH - 1));
-      src[i] = kv + (size_t)s_tab[t >> sh] * block_stride + layer_base + (size_t)(t & (blk - 1)) * HD + 8 * ch;
-    }
-    // V: fragments of key step `wave`; lane = dimension (permuted) + 32 * (eight-key half)
-    const int t8 = min(t0 + 16 * wave + 8 * half, (P - 1) & ~7);
-    const uint16_t* vb = kv + (size_t)s_tab[t8 >> sh] * block_stride + layer_base + blk_elems + (t8 & (blk - 1)) +
-                         (size_t)kv_perm(a) * blk;
+  for (int i = 0; i < HD / 32; ++i) {
+    const int r = 16 * wave + i * KR + lane / CH;
+    koff[i] = (uint32_t)((r & (blk - 1)) * HD + 8 * ((lane % CH) ^ (kv_perm(r & 15) & (CH - 1)))) * 2;
+  }
+  const int v8 = 16 * wave + 8 * half, vtab = v8 >> sh;
+  const char* vbase = (const char*)(kv + layer_base + blk_elems + (v8 & (blk - 1)) + (size_t)kv_perm(a) * blk);
+  const uint32_t stride = (uint32_t)(block_stride * 2);  // bytes of a block: KV heads x 2 x blk x HD x 2
+  auto block_at = [&](int tile, int i) { return (uint32_t)s_tab[min((tile * kPreKeys >> sh) + i, ntab - 1)]; };
+  auto load_k = [&](int buf, int tile) {
+    uint32_t b[HD / 32];
 #pragma unroll
-    for (int i = 0; i < HD / 32; ++i) dma_lds16(src[i], &s_k[buf][(16 * wave + i * (64 / CH)) * HD]);
+    for (int i = 0; i < HD / 32; ++i) b[i] = block_at(tile, (16 * wave + i * KR) >> sh);
 #pragma unroll
-    for (int d = 0; d < DT; ++d) dma_lds16(vb + (size_t)32 * d * blk, &s_v[buf][(wave * DT + d) * 512]);
+    for (int i = 0; i < HD / 32; ++i)
+      dma_lds16_at(kbase + (uint64_t)__builtin_amdgcn_readfirstlane(b[i]) * stride, koff[i],
+                   &s_k[buf][(16 * wave + i * KR) * HD]);
+  };
+  auto load_v = [&](int buf, int tile) {
+    const char* vb = vbase + (uint64_t)block_at(tile, vtab) * stride;
+#pragma unroll
+    for (int d = 0; d < DT; ++d) dma_lds16(vb + (size_t)64 * d * blk, &s_v[buf][(wave * DT + d) * 512]);
   };
 #pragma unroll
   for (int c = 0; c < KS; ++c) asm volatile("" : "+v"(qf[c]));  // q has arrived: no wait for it among the tiles
@@ -744,58 +767,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(Dims D, const uint16_t*
   for (int d = 0; d < DT; ++d)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[d][e] = 0.f;
-  // scores are kept in units of log 2: p = 2^(s c - m)
+  // scores are kept in units of log 2: p = 2^(s c2 - m)
   const float c2 = 1.44269504088896341f / sqrtf((float)HD);
   float m_run = -INFINITY, l_run = 0.f;
-
-  load(0, 0);
-  for (int it = 0; it < n_tiles; ++it) {
-    dma_wait_barrier();  // tile `it` is in LDS for every wave, and nobody reads the other buffer any more
-    if (it + 1 < n_tiles) load((it + 1) & 1, it + 1);
-    const int t0 = it * kPreKeys;
-    const uint16_t* kb = s_k[it & 1];
-    uint16_t* vb = s_v[it & 1];
-    if (t0 + kPreKeys > P) {  // the prompt's last tile: values past its end are zeroed
-      for (int i = tid; i < 4 * DT * 64; i += 256) {
-        const int ok = P - (t0 + 16 * (i / (DT * 64)) + 8 * ((i >> 5) & 1));  // values of this chunk inside the prompt
-        for (int e = max(ok, 0); e < 8; ++e) vb[8 * i + e] = 0;
-      }
-      lds_barrier();
-    }
-    if (t0 > w_last) continue;  // (wave-uniform) every key of the tile lies past the wave's tokens
-    floatx16_t s[2];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s[kt][e] = 0.f;
-      const int r = 32 * kt + kv_perm(a);
-#pragma unroll
-      for (int c = 0; c < KS; ++c) {
-        const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(kb + r * HD + 8 * ((2 * c + half) ^ (a & (CH - 1) & 15)));
-        s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], s[kt], 0, 0, 0);
-      }
-    }
-    if (t0 + kPreKeys - 1 > w_first) {  // causal limit inside the tile for some column
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (t0 + 32 * kt + 16 * (e >> 3) + 8 * half + (e & 7) > tok) s[kt][e] = -INFINITY;
-    }
-    float mx = s[0][0];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[kt][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
-    if (__any(mx > m_run)) {  // no column has a new maximum in most tiles after the first
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = exp2f(m_run - m_new);
-      m_run = m_new;
-      l_run *= alpha;
-#pragma unroll
-      for (int d = 0; d < DT; ++d) o[d] *= alpha;
-    }
+  auto qk_step = [&](const uint16_t* kb, int kt, int c, floatx16_t& s) {
+    const bf16x8_t kf =
+        *reinterpret_cast<const bf16x8_t*>(kb + (32 * kt + kv_perm(a)) * HD + 8 * ((2 * c + half) ^ (a & (CH - 1) & 15)));
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], s, 0, 0, 0);
+  };
+  // softmax and P V of a tile whose scores are in s
+  auto tile = [&](const floatx16_t* s, const uint16_t* vb) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       bf16x8_t ph, pl;
@@ -818,6 +799,57 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(Dims D, const uint16_t*
         o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl, o[d], 0, 0, 0);
       }
     }
+  };
+  load_k(0, 0);
+  load_v(0, 0);
+  for (int it = 0; it < n_tiles; ++it) {
+    dma_wait_barrier();  // tile `it` is in LDS for every wave, and nobody reads the other buffer any more
+    if (it + 1 < n_tiles) {
+      load_k((it + 1) & 1, it + 1);
+      load_v((it + 1) & 1, it + 1);
+    }
+    const int t0 = it * kPreKeys;
+    uint16_t* vb = s_v[it & 1];
+    if (t0 + kPreKeys > P) {  // the prompt's last tile: values past its end are zeroed
+      for (int i = tid; i < 4 * DT * 64; i += 256) {
+        const int ok = P - (t0 + 16 * (i / (DT * 64)) + 8 * ((i >> 5) & 1));  // values of this chunk inside the prompt
+        for (int e = max(ok, 0); e < 8; ++e) vb[8 * i + e] = 0;
+      }
+      lds_barrier();
+    }
+    if (t0 > w_last) continue;  // (wave-uniform) every key of the tile lies past the wave's tokens
+    floatx16_t s[2];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[kt][e] = 0.f;
+#pragma unroll
+      for (int c = 0; c < KS; ++c) qk_step(s_k[it & 1], kt, c, s[kt]);
+    }
+    if (t0 + kPreKeys - 1 > w_first) {  // causal limit inside the tile for some column
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (t0 + 32 * kt + 16 * (e >> 3) + 8 * half + (e & 7) > tok) s[kt][e] = -INFINITY;
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[kt][e]);
+    mx = half_max(mx) * c2;
+    // the running maximum follows only when a column outgrows it by 2^kPreGrow: until then its probabilities are
+    // that much above 1, which costs no precision (they are split and summed relative to their own size)
+    if (__any(mx > m_run + kPreGrow)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int d = 0; d < DT; ++d) o[d] *= alpha;
+    }
+    tile(s, vb);
   }
   if (col0 + a >= ncol) return;
   const float l = l_run + __shfl_xor(l_run, 32, 64);
