@@ -78,8 +78,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 //
 // Phases and slots: barrier b0 follows the prologue; group 0 multiplies step s between barriers 2 s + 1 and
 // 2 s + 2, group 1 between 2 s + 2 and 2 s + 3, and each reads step s from LDS in the phase before.  A wave
-// refills the slot of step s - 1 (with step s + NS - 1) after its multiply phase of step s: both groups have
-// read that slot by then.  Before the barrier that ends its reads of step s a wave waits until its own
+// refills the slot of step s - 1 (with step s + NS - 1) in the phase after its multiply phase of step s, behind its
+// reads of step s + 1: both groups have read that slot by then.  Before the barrier that ends its reads of step s a wave waits until its own
 // transfers of step s + 1 have landed, so the step is whole when group 0 comes to read it.
 //
 // Why: the previous kernels (a 256 x 128 tile of four waves with weights in a register ring; for 129..256 rows
@@ -149,15 +149,16 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
       fs[i] = 64;
     }
   }
-  auto transfer = [&](int slot, int st) {  // steps past the last repeat it into slots that are not read again
-    const size_t kk = (size_t)min(st, nk - 1);
+  // transfers of k-step st, called for 0, 1, 2, ... in turn (the addresses move on by themselves; steps past the
+  // last repeat it into slots that are not read again)
+  auto transfer = [&](int slot, int st) {
+    const bool on = st + 1 < nk;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int f = min(PER * wave + i, FR - 1);
-      if (Q4 && f == FR - 1)
-        dma_lds16_at(fb[i] + (kk >> 2) * fs[i], soff, &ls[slot][f][0]);
-      else
-        dma_lds16_at(fb[i] + kk * fs[i], lane * 16, &ls[slot][f][0]);
+      const bool scales = Q4 && f == FR - 1;
+      dma_lds16_at(fb[i], scales ? soff : lane * 16, &ls[slot][f][0]);
+      fb[i] += on && (!scales || (st & 3) == 3) ? fs[i] : 0;
     }
   };
   floatx4_t P[Q4 ? NB : 1][Q4 ? MBW : 1];
@@ -192,7 +193,9 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
           for (int j = 0; j < NB; ++j) wf[j] = ls[u][wn * NB + j][lane];
 #pragma unroll
           for (int i = 0; i < MBW; ++i) xf[i] = ls[u][TN + wm * MBW + i][lane];
-          // the group that ended with step st - 1 (its slot is refilled after this step's multiply phase)
+          // behind the reads: the slot of step st - 2 is free since the barrier, for step st + NS - 2
+          if (st > 0) transfer((u + NS - 2) % NS, st + NS - 2);
+          // the group that ended with step st - 1 (its slot is refilled in a later phase)
           if (Q4 && u % 4 == 0) read_scales(u + (st > 0 ? NS - 1 : 0) - (u > 0 ? NS : 0));
           dma_wait_barrier<(NS - 3) * PER>();
           __builtin_amdgcn_s_setprio(1);
@@ -222,7 +225,6 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
           __builtin_amdgcn_s_setprio(0);
           __builtin_amdgcn_sched_barrier(0);  // the MFMAs stay in their phase
           phase_barrier();
-          transfer((u + NS - 1) % NS, st + NS - 1);
         }
       }
     }
