@@ -77,10 +77,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // into a second register set during the MFMAs.
 //
 // Phases and slots: barrier b0 follows the prologue; group 0 multiplies step s between barriers 2 s + 1 and
-// 2 s + 2, group 1 between 2 s + 2 and 2 s + 3, and each reads step s from LDS in the phase before.  A wave
-// refills the slot of step s - 1 (with step s + NS - 1) in the phase after its multiply phase of step s, behind its
-// reads of step s + 1: both groups have read that slot by then.  Before the barrier that ends its reads of step s a wave waits until its own
-// transfers of step s + 1 have landed, so the step is whole when group 0 comes to read it.
+// 2 s + 2, group 1 between 2 s + 2 and 2 s + 3, and each reads step s from LDS in the phase before.  In that phase,
+// behind its reads, a wave refills the slot of step s - 1 (with step s + NS - 1): both groups' reads of step s - 1 ended
+// at a barrier before it.  Before the barrier that ends its reads of step s a wave waits until its own
+// transfers of step s + 1 have landed, so the step is whole when group 0 comes to read it.  (Refilling a phase
+// later leaves one step less in flight: 0.5% slower over two bf16 layers and 8 to 10% in int4 form, whose ring is
+// short for its k-steps; two k-steps a phase, with half the barriers, measured the same.)
 //
 // Why: the previous kernels (a 256 x 128 tile of four waves with weights in a register ring; for 129..256 rows
 // weights staged through registers and LDS by four waves) ran at the rate a CU fetches its operands or at
@@ -108,7 +110,7 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
                float* __restrict__ out, int M, int N, int K, int kslice, int Nt, uint16_t* __restrict__ h, int rep) {
   constexpr int TN = NB * WN, TM = MBW * WM, FR = TN + TM + (Q4 ? 1 : 0);
   constexpr int PER = (FR + 7) / 8;  // fragments a wave transfers per k-step (surplus ones repeat the last)
-  static_assert(WN * WM == 8 && NS >= 3, "eight waves");
+  static_assert(WN * WM == 8 && NS >= 3, "eight waves; a slot is read, one lands, one is refilled");
   static_assert(!Q4 || (NS % 4 == 0 && TN <= 16), "a group is four unrolled k-steps; its scales fit one fragment");
   __shared__ bf16x8_t ls[NS][FR][64];
   const int lane = threadIdx.x & 63;
@@ -169,6 +171,10 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
       for (int i = 0; i < MBW; ++i) P[j][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
   floatx4_t sc[Q4 ? NB : 1];
+  if constexpr (Q4) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) sc[j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
   auto read_scales = [&](int slot) {  // of the group that k-step's slot belongs to
 #pragma unroll
     for (int j = 0; j < NB; ++j)
@@ -193,11 +199,9 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
           for (int j = 0; j < NB; ++j) wf[j] = ls[u][wn * NB + j][lane];
 #pragma unroll
           for (int i = 0; i < MBW; ++i) xf[i] = ls[u][TN + wm * MBW + i][lane];
-          // behind the reads: the slot of step st - 2 is free since the barrier, for step st + NS - 2
-          if (st > 0) transfer((u + NS - 2) % NS, st + NS - 2);
-          // the group that ended with step st - 1 (its slot is refilled in a later phase)
-          if (Q4 && u % 4 == 0) read_scales(u + (st > 0 ? NS - 1 : 0) - (u > 0 ? NS : 0));
-          dma_wait_barrier<(NS - 3) * PER>();
+          transfer((u + NS - 1) % NS, st + NS - 1);  // behind the reads; the slot of step st - 1
+          if (Q4 && u % 4 == 3) read_scales(u);  // of the group that ends here, for the next step's FMAs
+          dma_wait_barrier<(NS - 2) * PER>();
           __builtin_amdgcn_s_setprio(1);
           if constexpr (Q4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -230,7 +234,6 @@ void k_gemm_pp(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W, 
     }
     if (wave < 4) phase_barrier();  // as many barriers as the second group
     if constexpr (Q4) {  // the last group
-      read_scales((nk - 1) % NS);
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
@@ -742,10 +745,10 @@ hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, floa
                        uint16_t* h, int rep) {
   const TilePlan p = tile_plan(M, N, K, splits, splits);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 6, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_8x16: launch_pp<4, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_10x8: launch_pp<5, 2, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_8x16: launch_pp<4, 4, 2, 4, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
     case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
     default: launch_pp<5, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
   }
