@@ -39,7 +39,7 @@
 // in groups of 128 inputs with an fp32 scale and a zero point per row and
 // group; the group's scale multiplies its integer dot product in fp32, so the
 // weights are never rounded.  The codes enter the MFMA as exact bf16 integers
-// (128 + q); a workgroup of four waves shares each group's activation
+// (128 + q); a workgroup of eight waves shares each group's activation
 // fragments and their sums through LDS.  Larger batches with int4 weights
 // write a projection's integers q - z (exact in bf16) into fragments first and take k_gemm_pp on those,
 // which scales every group's sum in fp32.
@@ -417,141 +417,223 @@ __global__ __launch_bounds__(64 * KW) void k_gemm_ring(const bf16x8_t* __restric
 // scales and uint8 zeros [N/16][K/128][16]), scaled per group: for a 128-input group g of row n,
 //   y[m] += s[n,g] * sum_k (q[n,k] - z[n,g]) x[m,k].
 // A code q enters the MFMA as the exact bf16 integer 128 + q (the nibble in the mantissa of 128: one
-// shift and one and-or per pair of codes), so a group's MFMA partial is P = sum_k (128 + q) x.  One
-// all-ones MFMA per group gives X = sum_k x[m,k], shared by the wave's weight blocks, and the group's
-// epilogue adds s * (P - (128 + z) * X) to the fp32 accumulator.  The weights are never rounded.
-// Ring over groups as in k_gemm_ring: per group and weight block one 16-byte code load, a 16-byte load
-// of the four scales of the lane's accumulator rows and a 4-byte load of their zeros.
-__device__ __forceinline__ bf16x8_t q4_operand(uint32_t w) {
+// shift and one and-or per pair of codes), so a group's MFMA partial is P = sum_k (128 + q) x.
+// All-ones MFMAs give X = sum_k x[m,k] once per workgroup, and the group's
+// scaling adds s * (P - (128 + z) * X) to the fp32 accumulator.  The weights are never rounded.
+__device__ __forceinline__ bf16x8_t q4_operand(uint32_t w, uint32_t magic) {  // magic: 0x43004300
   u32x4_t d;
-  d[0] = (w & 0x000F000Fu) | 0x43004300u;
-  d[1] = ((w >> 4) & 0x000F000Fu) | 0x43004300u;
-  d[2] = ((w >> 8) & 0x000F000Fu) | 0x43004300u;
-  d[3] = ((w >> 12) & 0x000F000Fu) | 0x43004300u;
+  d[0] = (w & 0x000F000Fu) | magic;
+  d[1] = ((w >> 4) & 0x000F000Fu) | magic;
+  d[2] = ((w >> 8) & 0x000F000Fu) | magic;
+  d[3] = ((w >> 12) & 0x000F000Fu) | magic;
   return __builtin_bit_cast(bf16x8_t, d);
 }
 
-// A workgroup of four waves shares the activation fragments of a group through LDS (double
-// buffered: wave w loads k-step w of group i + 1 for every 16-row block while all compute group i,
-// then stores it).  Wave w also forms that k-step's activation sums with MB all-ones MFMAs and
-// publishes them; a group's sums X are the four waves' partials added in k-step order.  Each wave
-// owns NBW weight blocks and keeps their codes, scales and zeros in a two-group register ring.
-// One barrier per group.
-template <int MB, int NBW, bool SWI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_q4(
+// A workgroup of eight waves owns 16 / KS weight blocks, two per wave: with KS = 2 the waves are two sets that
+// take the two halves of the workgroup's groups (their sums meet in LDS at the end).  A set's activation fragments,
+// codes, scales and zeros of a group come straight into LDS (dma_lds16_at) through a ring of NS groups, NS - 1
+// in flight, and one barrier per group; a wave forms one row block's activation sums (with KS = 1, of half the
+// k-steps).  A group is scaled between the first MFMAs of the next one, so that the vector work of the codes and of the
+// scaling runs beside MFMAs.
+//
+// Bound at 64 rows: LDS (sixteen activation fragments per wave and group) and the transfers, half of whose bytes are
+// activations out of L2: without any arithmetic the transfers alone take 60 of gate/up's 79 us.  Weights of four waves
+// in registers, activations through registers into LDS (the form before) -> now, us at 64 rows:
+//   72B (8,192 / 29,568) gate/up 91.6 -> 79.2, O and down 41.1 -> 30.5, QKV 25.6 -> 20.9
+// and per layer, all kernels: 72B 1 row 161 -> 142, 32 rows 197 -> 158; 14B 104 -> 75, 126 -> 91; 7B 86 -> 77, 105 -> 93.
+// Measured and not better: two halves of the waves that take turns at LDS and MFMAs (79 and 32 us), four waves of
+// four blocks each (111 us: half the LDS reads, but one wave a SIMD hides nothing).
+template <int MB, int KS, int NS, bool SWI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_q4(
     const bf16x8_t* __restrict__ XF, const u32x4_t* __restrict__ Wq, const floatx4_t* __restrict__ Ws,
     const uint32_t* __restrict__ Wz, float* __restrict__ out, int M, int N, int K, int kslice,
     uint16_t* __restrict__ h) {
-  constexpr int D = 2;
-  __shared__ bf16x8_t xl[2][4 * MB][64];
-  __shared__ float xsl[2][4][MB][16];
+  constexpr int WS = 8 / KS, TN = 2 * WS;   // waves and weight blocks of a set
+  constexpr int XFR = 4 * MB, FR = XFR + TN + 2;  // fragments of a group: activations, codes, scales, zeros
+  constexpr int SP = WS / 4;  // shares of the k-steps in the activation sums
+  constexpr int PX = (XFR + 2 + WS - 1) / WS, PER = PX + 2;  // transfers of a wave per group, its two blocks' codes last
+  __shared__ u32x4_t ls[NS][KS][FR][64];
+  __shared__ float xsl[2][KS][SP][MB][16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nb0 = (blockIdx.x * 4 + wave) * NBW;
+  const int set = wave / WS, w = wave % WS;
+  const int nb0 = blockIdx.x * TN + 2 * w;  // the wave's blocks
   const int nbt = N >> 4, gbt = K >> 7;
   const int kg0 = (int)blockIdx.y * (kslice >> 7);
   const int ng = min(gbt, kg0 + (kslice >> 7)) - kg0;
   if (ng <= 0) {  // an empty K split contributes zeros
     if constexpr (!SWI) {
-      for (int j = 0; j < NBW && nb0 + j < nbt; ++j)
-        for (int m = lane & 15; m < M; m += 16)
-          *reinterpret_cast<float4*>(out + ((size_t)blockIdx.y * M + m) * N + (nb0 + j) * 16 + 4 * (lane >> 4)) =
-              make_float4(0.f, 0.f, 0.f, 0.f);
+      if (set == 0)
+        for (int j = 0; j < 2 && nb0 + j < nbt; ++j)
+          for (int m = lane & 15; m < M; m += 16)
+            *reinterpret_cast<float4*>(out + ((size_t)blockIdx.y * M + m) * N + (nb0 + j) * 16 + 4 * (lane >> 4)) =
+                make_float4(0.f, 0.f, 0.f, 0.f);
     }
     return;
   }
+  const int steps = (ng + KS - 1) / KS;             // both sets take as many barriers
+  const int cnt = set ? ng - steps : steps;         // groups of this set, from g0 (a set without any loads group kg0's)
+  const int g0 = cnt > 0 ? kg0 + set * steps : kg0;
+  for (int i = tid; i < 2 * KS * SP * MB * 16; i += 512) (&xsl[0][0][0][0][0])[i] = 0.f;
+  const char* fb[PER];
+  uint32_t fo[PER], fs[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int f = min(PX * w + i, XFR + 1);
+    fo[i] = lane * 16;
+    if (i >= PX) {
+      fb[i] = (const char*)(Wq + ((size_t)min(nb0 + i - PX, nbt - 1) * gbt + g0) * 64);
+      fs[i] = 1024;
+    } else if (f < XFR) {
+      fb[i] = (const char*)(XF + ((size_t)g0 * XFR + f) * 64);
+      fs[i] = XFR * 1024;
+    } else {  // scales: 64 bytes a block, lane = 4 * block + four rows; zeros: 16 bytes a block, lane = block
+      const int left = nbt - 1 - (int)blockIdx.x * TN;  // the last block
+      const size_t it = (size_t)blockIdx.x * TN * gbt + g0;
+      const bool zero = f > XFR;
+      fb[i] = zero ? (const char*)Wz + it * 16 : (const char*)Ws + it * 64;
+      fs[i] = zero ? 16 : 64;
+      fo[i] = zero ? min(min(lane, TN - 1), left) * gbt * 16
+                   : min(min(lane >> 2, TN - 1), left) * gbt * 64 + (lane & 3) * 16;
+    }
+  }
+  // transfers of group st, called for 0, 1, 2, ... in turn (groups past the last repeat it, never read)
+  auto transfer = [&](int slot, int st) {
+    const bool on = st + 1 < cnt;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int f = i >= PX ? XFR + 2 * w + (i - PX) : min(PX * w + i, XFR + 1);
+      dma_lds16_at(fb[i], fo[i], &ls[slot][set][i < PX && f >= XFR ? f + TN : f][0]);
+      fb[i] += on ? fs[i] : 0;
+    }
+  };
   bf16x8_t ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = __builtin_bit_cast(__bf16, (uint16_t)0x3F80);
-  floatx4_t acc[NBW][MB];
+  uint32_t magic = 0x43004300u;
+  asm("" : "+v"(magic));  // in a vector register: an and-or may read only one scalar
+  const floatx4_t zf = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  floatx4_t acc[2][MB], P[2][MB], sc[2], of[2];
 #pragma unroll
-  for (int j = 0; j < NBW; ++j)
+  for (int j = 0; j < 2; ++j) {
+    sc[j] = of[j] = zf;  // the first group scales a group of zeros
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[j][mb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  {
-    // wave-uniform bases of each block's first group (blocks past N: clamped, never stored)
-    size_t item0[NBW];
+    for (int mb = 0; mb < MB; ++mb) acc[j][mb] = P[j][mb] = zf;
+  }
+  const int ws = min(w & 3, MB - 1);
+  float xs[MB];
+  auto scale_tile = [&](int j, int mb) {
 #pragma unroll
-    for (int j = 0; j < NBW; ++j) item0[j] = (size_t)min(nb0 + j, nbt - 1) * gbt + kg0;
-    const int wl = lane, sl = lane >> 4;
-    // k-step `wave` of a group, every 16-row block: fragments wave * MB .. + MB - 1 of the group's 4 MB
-    const bf16x8_t* xp = XF + (size_t)kg0 * 4 * MB * 64 + (size_t)wave * MB * 64;
-    u32x4_t cr[D][NBW];
-    floatx4_t sr[D][NBW];
-    uint32_t zr[D][NBW];
-    auto load_w = [&](int d, int gg) {
+    for (int r = 0; r < 4; ++r)
+      acc[j][mb][r] = fmaf(sc[j][r], fmaf(-of[j][r], xs[mb], P[j][mb][r]), acc[j][mb][r]);
+  };
+  auto read_sums = [&](int st) {
 #pragma unroll
-      for (int j = 0; j < NBW; ++j) {
-        const size_t it = item0[j] + (size_t)gg;
-        cr[d][j] = __builtin_nontemporal_load(Wq + it * 64 + wl);
-        sr[d][j] = Ws[it * 4 + sl];  // scales of rows 4 (lane / 16) .. + 3
-        zr[d][j] = Wz[it * 4 + sl];
-      }
-    };
-    bf16x8_t xst[MB];
-    auto load_x = [&](int gg) {
-#pragma unroll
-      for (int f = 0; f < MB; ++f) xst[f] = xp[((size_t)gg * 4 * MB + f) * 64 + lane];
-    };
-    auto store_x = [&](int buf) {
-#pragma unroll
-      for (int f = 0; f < MB; ++f) {
-        xl[buf][wave * MB + f][lane] = xst[f];
-        const floatx4_t p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, xst[f], floatx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        if (lane < 16) xsl[buf][wave][f][lane] = p[0];
-      }
-    };
-    load_x(0);
-    store_x(0);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      load_w(d, min(d, ng - 1));
-      __builtin_amdgcn_sched_barrier(0);
+    for (int mb = 0; mb < MB; ++mb) {
+      xs[mb] = xsl[st & 1][set][0][mb][lane & 15];
+      if (SP == 2) xs[mb] += xsl[st & 1][set][SP - 1][mb][lane & 15];
     }
-    __syncthreads();
-    for (int i = 0; i < ng; i += D) {
+  };
 #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const int g = i + d;                  // group computed now, from LDS buffer g & 1 and ring slot d
-        load_x(min(g + 1, ng - 1));           // next group's fragments (clamped past the end, never used)
-        if (g < ng) {
-          const int buf = g & 1;
-          float xs[MB];
+  for (int st = 0; st < NS - 1; ++st) transfer(st, st);
+  dma_wait_barrier<(NS - 2) * PER>();
+  for (int s0 = 0; s0 < steps; s0 += NS) {
 #pragma unroll
-          for (int mb = 0; mb < MB; ++mb) {
-            const int m16 = lane & 15;
-            xs[mb] = ((xsl[buf][0][mb][m16] + xsl[buf][1][mb][m16]) + xsl[buf][2][mb][m16]) + xsl[buf][3][mb][m16];
+    for (int u = 0; u < NS; ++u) {
+      const int st = s0 + u;
+      if (st < steps) {
+        if (st < cnt) {
+          const auto& l = ls[u][set];
+          u32x4_t c[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j) c[j] = l[XFR + 2 * w + j][lane];
+          bf16x8_t xf[4][MB];
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) xf[0][mb] = __builtin_bit_cast(bf16x8_t, l[mb][lane]);
+          read_sums(st + 1);  // of the group before
+#pragma unroll
+          for (int t = 1; t < 4; ++t)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) xf[t][mb] = __builtin_bit_cast(bf16x8_t, l[t * MB + mb][lane]);
+          // activation sums: a wave's row block (of those past the last the last again), its share of the k-steps
+          u32x4_t xq[4 / SP];
+#pragma unroll
+          for (int t = 0; t < 4 / SP; ++t) xq[t] = l[(SP * t + (w >> 2)) * MB + ws][lane];
+          transfer((u + NS - 1) % NS, st + NS - 1);  // the slot of the group before
+          __builtin_amdgcn_sched_barrier(0);  // the reads go out first
+          floatx4_t sum = zf;
+          bf16x8_t a[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j) a[j] = q4_operand(c[j][0], magic);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            bf16x8_t an[2] = {a[0], a[1]};
+            if (t < 3)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) an[j] = q4_operand(c[j][t + 1], magic);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                if (t == 0) {
+                  scale_tile(j, mb);
+                  asm volatile("" : "+v"(acc[j][mb]));  // here, not after the group's MFMAs
+                }
+                P[j][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], xf[t][mb], t ? P[j][mb] : zf, 0, 0, 0);
+              }
+            if (t >= 4 - 4 / SP || SP == 1)
+              sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  ones, __builtin_bit_cast(bf16x8_t, xq[SP == 1 ? t : t - 2]), sum, 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) a[j] = an[j];
+#pragma unroll
+            for (int i = 0; i < 2 * MB; ++i) {
+              if (t == 0) __builtin_amdgcn_sched_group_barrier(2, 10, 0);
+              __builtin_amdgcn_sched_group_barrier(8, 1, 0);
+              if (t) __builtin_amdgcn_sched_group_barrier(2, 2, 0);
+            }
           }
 #pragma unroll
-          for (int j = 0; j < NBW; ++j) {
-            floatx4_t pp[MB];
+          for (int j = 0; j < 2; ++j) {
+            sc[j] = __builtin_bit_cast(floatx4_t, l[XFR + TN][4 * (2 * w + j) + (lane >> 4)]);
+            const uint32_t z = reinterpret_cast<const uint32_t*>(&l[XFR + TN + 1][2 * w + j])[lane >> 4];
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) pp[mb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const bf16x8_t a = q4_operand(cr[d][j][t]);
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb)
-                pp[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, xl[buf][t * MB + mb][lane], pp[mb], 0, 0, 0);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float sc = sr[d][j][r];
-              const float off = __uint_as_float(0x43000000u | (((zr[d][j] >> (8 * r)) & 0xFFu) << 16));  // 128 + z
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb) acc[j][mb][r] = fmaf(sc, fmaf(-off, xs[mb], pp[mb][r]), acc[j][mb][r]);
-            }
+            for (int r = 0; r < 4; ++r)  // 128 + z: byte r of z in the mantissa of 128
+              of[j][r] = __uint_as_float(__builtin_amdgcn_perm(0x43u, z, 0x04000C0Cu | (uint32_t)r << 16));
           }
+          if (lane < 16) xsl[st & 1][set][w >> 2][ws][lane] = sum[0];
         }
-        load_w(d, min(g + D, ng - 1));
-        store_x((g + 1) & 1);  // buffer (g + 1) & 1 was last read for group g - 1, before the last barrier
-        __syncthreads();
+        dma_wait_barrier<(NS - 2) * PER>();
       }
     }
   }
+  read_sums(cnt + 1);  // the last group
 #pragma unroll
-  for (int j = 0; j < NBW; ++j) {
-    if (nb0 + j >= nbt) continue;
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) scale_tile(j, mb);
+  dma_wait();  // no transfer may still be on its way into LDS when it is used again or given back
+  if constexpr (KS == 2) {  // set i keeps its waves' block i and takes the other set's sums of it
+    floatx4_t(*red)[WS][MB][64] = reinterpret_cast<floatx4_t(*)[WS][MB][64]>(&ls[0][0][0][0]);
+    __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const floatx4_t a0 = acc[0][mb], a1 = acc[1][mb];
+      red[set][w][mb][lane] = set ? a0 : a1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const floatx4_t o = red[1 - set][w][mb][lane];
+      if (set)
+        acc[1][mb] = o + acc[1][mb];
+      else
+        acc[0][mb] += o;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (nb0 + j >= nbt || (KS == 2 && j != set)) continue;
     const int n = (nb0 + j) * 16 + 4 * (lane >> 4);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -900,30 +982,40 @@ int kslice_q4(int K, int splits) {
   return (per + 127) / 128 * 128;
 }
 
-template <int MB, int NBW, bool SWI>
+template <int MB, int KS, int NS, bool SWI>
 void launch_q4_mb(hipStream_t s, const bf16x8_t* x, const void* w, float* out, int M, int N, int K, int splits,
                   uint16_t* h) {
   const int kslice = kslice_q4(K, splits);
-  const dim3 grid((N / 16 + 4 * NBW - 1) / (4 * NBW), splits);
+  const dim3 grid((N / 16 + 16 / KS - 1) / (16 / KS), splits);
   const char* base = (const char*)w;
   const u32x4_t* wq = (const u32x4_t*)base;
   const floatx4_t* ws = (const floatx4_t*)(base + q4_code_bytes(N, K));
   const uint32_t* wz = (const uint32_t*)(base + q4_code_bytes(N, K) + (size_t)N * (K / 128) * 4);
-  hipLaunchKernelGGL((k_gemm_q4<MB, NBW, SWI>), grid, dim3(256), 0, s, x, wq, ws, wz, out, M, N, K, kslice, h);
+  hipLaunchKernelGGL((k_gemm_q4<MB, KS, NS, SWI>), grid, dim3(512), 0, s, x, wq, ws, wz, out, M, N, K, kslice, h);
 }
 
-// Weight blocks per wave: 4 for up to two 16-row activation blocks, 2 above (registers: both fit two
-// waves per SIMD).
-constexpr int q4_blocks(int M) { return M <= 32 ? 4 : 2; }
-
+// One set of waves where the gate/up matrix has the blocks for 80% of the CUs at 16 each (72B: 231 workgroups in one
+// wave of the grid, against 462 of two sets); two sets below that and for the split projections, which need the
+// workgroups.  LDS: NS x KS x (4 MB + 16 / KS + 2) KB and the sums, at most 160.
 template <bool SWI>
 hipError_t launch_q4(hipStream_t s, const bf16x8_t* x, const void* w, float* out, int M, int N, int K, int splits,
                      uint16_t* h) {
+  if constexpr (SWI) {
+    if (5 * ((N / 16 + 15) / 16) >= 4 * device_cus()) {
+      switch ((M + 15) / 16) {
+        case 1: launch_q4_mb<1, 1, 6, SWI>(s, x, w, out, M, N, K, splits, h); break;
+        case 2: launch_q4_mb<2, 1, 5, SWI>(s, x, w, out, M, N, K, splits, h); break;
+        case 3: launch_q4_mb<3, 1, 5, SWI>(s, x, w, out, M, N, K, splits, h); break;
+        default: launch_q4_mb<4, 1, 4, SWI>(s, x, w, out, M, N, K, splits, h); break;
+      }
+      return hipGetLastError();
+    }
+  }
   switch ((M + 15) / 16) {
-    case 1: launch_q4_mb<1, q4_blocks(16), SWI>(s, x, w, out, M, N, K, splits, h); break;
-    case 2: launch_q4_mb<2, q4_blocks(32), SWI>(s, x, w, out, M, N, K, splits, h); break;
-    case 3: launch_q4_mb<3, q4_blocks(48), SWI>(s, x, w, out, M, N, K, splits, h); break;
-    default: launch_q4_mb<4, q4_blocks(64), SWI>(s, x, w, out, M, N, K, splits, h); break;
+    case 1: launch_q4_mb<1, 2, 5, SWI>(s, x, w, out, M, N, K, splits, h); break;
+    case 2: launch_q4_mb<2, 2, 4, SWI>(s, x, w, out, M, N, K, splits, h); break;
+    case 3: launch_q4_mb<3, 2, 3, SWI>(s, x, w, out, M, N, K, splits, h); break;
+    default: launch_q4_mb<4, 2, 3, SWI>(s, x, w, out, M, N, K, splits, h); break;
   }
   return hipGetLastError();
 }
@@ -933,7 +1025,7 @@ hipError_t launch_q4(hipStream_t s, const bf16x8_t* x, const void* w, float* out
 int gemm_splits_q4(int M, int N, int K, int max_splits) {
   if (max_splits <= 1) return 1;
   if (M > kRingMaxRows) return tile_plan(M, N, K, 1, std::max(1, std::min(max_splits, K / 256)), true).splits;
-  const int groups = (N / 16 + 4 * q4_blocks(M) - 1) / (4 * q4_blocks(M));  // workgroups per K split
+  const int groups = (N / 16 + 7) / 8;  // workgroups per K split
   // as for the bf16 split projections: the fewest splits that fill 80% of the CUs, at most one workgroup
   // per CU (72B: QKV 3, O and down 4 instead of 7-8 splits at two workgroups per CU; 72B int4 rollout +1%)
   const int cus = device_cus();

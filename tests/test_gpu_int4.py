@@ -118,3 +118,25 @@ def test_int4_tile_gemm_rows(n_prompts, P):
     log(f"  max abs logit error {err:.4g}")
     assert err <= 3e-2  # the bf16 contract's bound, as above
     eng.close()
+
+
+# the ring GEMM at one to four 16-row blocks: one group (a set of waves without any), five (an odd share) and
+# eleven over K splits; 26368 gate/up features are enough blocks for the form whose waves all share a group
+@pytest.mark.parametrize("d,d_ff", [(128, 384), (640, 1408), (640, 26368)])
+def test_int4_ring_gemm_rows(d, d_ff):
+    heads = d // 64 if d > 128 else 2
+    shape = (1, d, heads, 2, 64, d_ff, 2064, 1e6)
+    cfg = R.model_config(shape, R.DTYPE_INT4, 64, 2, 1)
+    eng = R.Engine(cfg)
+    model = OracleModel(shape_of(cfg), mode="int4")
+    logits = torch.empty((1, cfg.vocab), dtype=torch.float32, device="cuda:0")
+    for P in (1, 16, 17, 33, 64):
+        log(f"int4 ring GEMM d={d} d_ff={d_ff} rows {P}")
+        prompts = W.prompts(1, P, cfg.vocab, seed=59)
+        want = model.prefill(prompts[0])[1]
+        R.rollout_prefill(eng.ctx, to_dev(prompts, torch), 1, P, 1, logits)
+        eng.synchronize()
+        err = float(np.max(np.abs(logits.cpu().numpy()[0] - want)))
+        log(f"  max abs logit error {err:.4g}")
+        assert err <= 3e-2  # the bf16 contract's bound, as above
+    eng.close()
