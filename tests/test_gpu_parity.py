@@ -156,6 +156,36 @@ def test_sampler_row_kernel_equals_chunked_kernels(V, temperature, top_p, monkey
     eng.close()
 
 
+@pytest.mark.parametrize("V", [1024, 2064, 20016])
+@pytest.mark.parametrize("top_p", [1.0, 0.95])
+def test_sampler_chunked_loads_by_alignment(V, top_p, monkeypatch):
+    """The chunked kernels draw the same tokens by 16-byte loads (aligned logits) and by 4-byte loads (logits
+    one float further on), with masked ids (-inf) in the rows."""
+    log(f"sampler chunked loads V={V} top_p={top_p}")
+    S = 16
+    rng = np.random.default_rng(V)
+    z = (rng.standard_normal((S, V)) * 2.0).astype(np.float32)
+    z[:4, V // 2:] = -np.inf
+    buf = torch.empty((S * V + 1,), dtype=torch.float32, device="cuda:0")
+    du = to_dev(W.uniforms(S, 1, seed=13)[:, 0], torch)
+    cfg = R.model_config("tiny", R.DTYPE_FP32, 16, 8, 4)
+    cfg.vocab = V
+    eng = R.Engine(cfg)
+    monkeypatch.setenv("ROLLOUT_SAMPLE_PATH", "chunked")
+    got = []
+    for off in (0, 1):
+        dz = buf[off:off + S * V].view(S, V)
+        dz.copy_(to_dev(z, torch))
+        torch.cuda.synchronize()
+        out = torch.full((S,), -1, dtype=torch.int32, device="cuda:0")
+        R.rollout_sample(eng.ctx, dz, S, 0.9, top_p, du, out)
+        eng.synchronize()
+        got.append(out.cpu().numpy())
+    assert (got[0] >= 0).all() and (got[0] < V).all() and (got[0][:4] < V // 2).all()
+    assert np.array_equal(got[0], got[1])
+    eng.close()
+
+
 # ---------------------------------------------------------------------------
 # tiny fp32 model: the whole rollout
 # ---------------------------------------------------------------------------
