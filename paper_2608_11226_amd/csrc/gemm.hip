@@ -87,10 +87,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // Why: the previous kernels (a 256 x 128 tile of four waves with weights in a register ring; for 129..256 rows
 // weights staged through registers and LDS by four waves) ran at the rate a CU fetches its operands or at
 // one wave's latency per k-step.  us before -> now (sum of its partials' reads included), PFLOP/s now:
-//   2,048 rows: 7B gate/up 479-553 -> 416-440 (1.3), 7B QKV 119 -> 70, O 75 -> 57, down 258 -> 214
-//   4,096 rows: 14B gate/up 1,000 -> 840 (1.38), 14B O 235 -> 172, down 566 -> 415, 72B gate/up 3,150 -> 2,690 (1.48)
+//   2,048 rows: 7B gate/up 479-553 -> 405-414 (1.36), 7B QKV 119 -> 61, O 75 -> 57, down 258 -> 210
+//   4,096 rows: 14B gate/up 1,000 -> 819-829 (1.41), 14B O 235 -> 181, down 566 -> 413, 72B gate/up 3,150 -> 2,690 (1.48)
 //   512 rows:   7B QKV 64 -> 31, down 95 -> 73, gate/up 147 -> 102;  256 rows: 7B gate/up 109 -> 71,
-//   14B head 424 -> 369;  128 rows: 14B gate/up 84 -> 62, 7B down 45 -> 38, 7B head 248 -> 234
+//   14B gate/up 88 -> 85, head 424 -> 367;  128 rows: 14B gate/up 84 -> 62, 7B down 45 -> 38, 7B head 248 -> 234
 // All sums are bit-equal to the previous kernels' at equal splits (k order).
 //
 // rep: every output row is written rep times, to rows rep * m .. rep * m + rep - 1 (the LM head after a prefill: a
