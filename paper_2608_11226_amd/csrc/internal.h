@@ -108,9 +108,14 @@ hipError_t launch_embed(hipStream_t s, int dtype, const void* E, const int32_t* 
 hipError_t launch_embed_norm(hipStream_t s, int dtype, const void* E, const int32_t* tokens, int tok_stride,
                              const int32_t* col, int M, int d, int V, float* x, const float* gain, float eps, void* out,
                              int32_t* err);
+// What a decode step's last norm moves on: ctx_len[m] of its rows (NULL: nothing) and cols[0], cols[1] (may be NULL).
+struct Advance {
+  int32_t* ctx_len = nullptr;
+  int32_t* cols = nullptr;
+};
 // x[m] += sum_s part[s][m] (part may be NULL); out[m] = rmsnorm(x[m]) * gain in the cache dtype.
 hipError_t launch_residual_norm(hipStream_t s, int dtype, const float* part, int splits, int M, int d, float* x,
-                                const float* gain, float eps, void* out);
+                                const float* gain, float eps, void* out, Advance adv = {});
 hipError_t launch_qkv_epilogue(hipStream_t s, const Dims& D, const float* part, int splits, int M, RowMap rm,
                                const float* rope_cos, const float* rope_sin, void* q_out, void* kv_pool,
                                int n_blocks, const int32_t* tables, int max_blocks, int layer, int32_t* err);
@@ -145,7 +150,6 @@ hipError_t launch_copy_kv_block(hipStream_t s, void* kv_pool, int n_blocks, int 
 // (M_dst rows in all)
 hipError_t launch_gather_rows(hipStream_t s, int dtype, const void* src, int ld, int P, int F, int n_prompts, int row0,
                               int M_dst, void* dst);
-hipError_t launch_advance(hipStream_t s, int32_t* ctx_len, int S, int32_t* cols);
 // Continuous batching (batching.hip): per-slot completion index, next token column, ended flag, the
 // slot's last draw and its staged uniform; all [S] in the arena.
 struct CbState {

@@ -417,7 +417,7 @@ bool use_shared_prefix(const rollout_ctx* c, int M, const RowMap& rm, int parts)
 // c->Lo.a holds the final-normed hidden states (cache dtype).
 // normed: the first layer's norm output is already in place (embed_rows)
 rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max, double kv_tokens_read,
-                              bool normed = false) {
+                              bool normed = false, Advance adv = {}) {
   const Dims& D = c->D;
   const Layout& Lo = c->Lo;
   float* x = c->at<float>(Lo.x);
@@ -488,7 +488,8 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
     {
       const float* next_gain = l + 1 < D.L ? c->at<float>(Lo.layers[l + 1].attn_norm) : c->at<float>(Lo.final_norm);
       Scope sc(c, 2, (double)s * M * D.d * 4 + (double)M * D.d * ((s ? 8 : 4) + eb), 0);
-      HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, s ? part : nullptr, s, M, D.d, x, next_gain, D.eps, a), "residual norm");
+      HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, s ? part : nullptr, s, M, D.d, x, next_gain, D.eps, a,
+                                      l + 1 < D.L ? Advance{} : adv), "residual norm");
     }
   }
   return ROLLOUT_OK;
@@ -590,7 +591,7 @@ rollout_status do_prefill(rollout_ctx* c, const int32_t* d_prompts, int n_prompt
 
 // Enqueue one decode step of the current wave (no host-side state change).
 rollout_status enqueue_decode(rollout_ctx* c, const int32_t* tokens, int tok_stride, const int32_t* col,
-                              float* d_logits, int ctx_max, bool advance = true) {
+                              float* d_logits, int ctx_max, Advance adv) {
   const Dims& D = c->D;
   const Layout& Lo = c->Lo;
   const int S = c->S;
@@ -598,12 +599,11 @@ rollout_status enqueue_decode(rollout_ctx* c, const int32_t* tokens, int tok_str
   rollout_status r = embed_rows(c, tokens, tok_stride, col, S, &normed);
   if (r) return r;
   RowMap rm{c->at<int32_t>(Lo.ctx_len), 0, 1, 0};
-  r = forward_layers(c, S, rm, ctx_max, (double)S * (c->cur_len + 1), normed);
+  r = forward_layers(c, S, rm, ctx_max, (double)S * (c->cur_len + 1), normed, adv);
   if (r) return r;
   int s;
   r = gemm(c, c->at(Lo.a), c->at(Lo.lm_head), d_logits, S, D.V, D.d, 1, &s);
   if (r) return r;
-  if (advance) HIP_TRY(c, launch_advance(c->stream, c->at<int32_t>(Lo.ctx_len), S, nullptr), "advance");
   return ROLLOUT_OK;
 }
 
@@ -793,7 +793,8 @@ rollout_status rollout_decode_step(rollout_ctx* ctx, const int32_t* d_tokens, fl
   if (!ctx->wave) return fail(ctx, ROLLOUT_ESTATE, "decode before prefill");
   if (ctx->cur_len + 1 > ctx->P + ctx->cfg.max_new_tokens)
     return fail(ctx, ROLLOUT_ESTATE, "context full (max_prompt_len + max_new_tokens reached)");
-  rollout_status r = enqueue_decode(ctx, d_tokens, 1, nullptr, d_logits, ctx->P + ctx->cfg.max_new_tokens);
+  rollout_status r = enqueue_decode(ctx, d_tokens, 1, nullptr, d_logits, ctx->P + ctx->cfg.max_new_tokens,
+                                    Advance{ctx->at<int32_t>(ctx->Lo.ctx_len), nullptr});
   if (r) return r;
   ctx->cur_len += 1;
   return ROLLOUT_OK;
@@ -868,16 +869,16 @@ rollout_status rollout_generate(rollout_ctx* ctx, const int32_t* d_prompts, int3
     HIP_TRY(ctx, launch_sample(ctx->stream, logits, Sw, D.V, temperature, top_p, uu, N, nullptr, tok, N,
                                ctx->at(ctx->Lo.samp)), "sample");
     if (N == 1) continue;
-    HIP_TRY(ctx, launch_set_cols(ctx->stream, cols, 0, 1), "set cols");
+    HIP_TRY(ctx, launch_set_cols(ctx->stream, cols, 0, 0), "set cols");
     const bool use_graph = !ctx->prof.on;
-    // cols[0] = column of the token fed in, cols[1] = column drawn; both move on after the draw
-    // the sequences' positions and the token columns move on together, in one launch after the draw
+    // cols[0] = column of the token fed in (read by the embedding), cols[1] = column drawn (read by the draw); both and
+    // the sequences' positions move on in between, with the step's last norm
     auto step = [&]() -> rollout_status {
-      rollout_status rr = enqueue_decode(ctx, tok, N, cols, logits, prompt_len + N, false);
+      rollout_status rr = enqueue_decode(ctx, tok, N, cols, logits, prompt_len + N,
+                                         Advance{ctx->at<int32_t>(ctx->Lo.ctx_len), cols});
       if (rr) return rr;
       HIP_TRY(ctx, launch_sample(ctx->stream, logits, Sw, D.V, temperature, top_p, uu, N, cols + 1, tok, N,
                                  ctx->at(ctx->Lo.samp)), "sample");
-      HIP_TRY(ctx, launch_advance(ctx->stream, ctx->at<int32_t>(ctx->Lo.ctx_len), ctx->S, cols), "advance");
       return ROLLOUT_OK;
     };
     if (!use_graph) {
@@ -1058,7 +1059,7 @@ rollout_status rollout_generate_eos(rollout_ctx* ctx, const int32_t* d_prompts, 
   };
   // one decode step over all slots: feed each slot's last draw, draw with its staged uniform, file the draws
   auto step = [&]() -> rollout_status {
-    rollout_status rr = enqueue_decode(ctx, cb.draw, 1, nullptr, logits, P + N, false);
+    rollout_status rr = enqueue_decode(ctx, cb.draw, 1, nullptr, logits, P + N, Advance{});
     if (rr) return rr;
     HIP_TRY(ctx, launch_sample(ctx->stream, logits, S, D.V, temperature, top_p, cb.u_slot, 1, nullptr, cb.draw, 1,
                                samp), "sample");
