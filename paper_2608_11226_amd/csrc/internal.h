@@ -294,17 +294,17 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // 16 bytes per lane from global memory straight into LDS: lane i's bytes land at dst + 16 i (dst is the same
 // for the whole wave; src is each lane's own).  Counted like a global load (vmcnt).  Written as asm because
 // the compiler otherwise waits for every transfer in flight before the next LDS read of any buffer; the
-// kernel waits itself (dma_wait_barrier) before it reads what a transfer wrote.  M0 is set here and used by
-// nothing else in kernels that call this.
+// kernel waits itself (dma_wait_barrier) before it reads what a transfer wrote.  The LDS address is handed over in M0;
+// a load that reads it needs one wait state behind the scalar write (the s_nop: the compiler adds none inside asm).
 __device__ __forceinline__ void dma_lds16(const void* src, void* dst) {
   const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)dst);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(lds) : "memory");
 }
 
 // The same with a wave-uniform base (src) and each lane's byte offset.
 __device__ __forceinline__ void dma_lds16_at(const void* src, uint32_t offset, void* dst) {
   const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)dst);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(src), "s"(lds) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(src), "{m0}"(lds) : "memory");
 }
 
 // All but the wave's latest N transfers into LDS and all its LDS accesses are complete, then every wave has arrived.
