@@ -28,6 +28,7 @@
 //
 // Cache layout: [layer][block][kv head][K: blk x hd | V: hd x blk] (kv_offset).
 #include <algorithm>
+#include <climits>
 #include <cstdlib>
 #include <type_traits>
 
@@ -254,17 +255,27 @@ struct AttnQKV {
   uint16_t* q_keep;
   float* st_o;   // [row][head][part][HD]: sum of p * v relative to the state's max
   float* st_ml;  // [row][head][part][2]: max, sum of p
-  int parts;     // workgroups that share a row's context (kParts; else 1)
+  int parts;     // workgroups that may share a row's context (kParts; else 1)
+  // the launch's rows: those at positions lo .. hi - 1 (the others' workgroups leave at once)
+  int lo, hi;
 };
 
 // What a workgroup of k_attn_mfma covers and leaves:
 //   kWhole: the row's whole context, normalised output;
 //   kSuffix: keys from t_begin on, state and rotated q left for k_attn_prefix;
-//   kParts: one of `parts` runs of 16-token tiles (shared out by the row's own position), state left for
-//     k_attn_merge.  Every part forms q again (from L2); the last one appends k and v and holds the current
-//     token.  For batches whose (row, KV head) pairs leave CUs idle (attn_parts).
+//   kParts: one of row_parts runs of 16-token tiles, state left for k_attn_merge.  Every part forms q again (from
+//     L2); the last one appends k and v and holds the current token.  For long rows of batches whose (row, KV head)
+//     pairs leave CUs idle (attn_parts).
 enum AttnMode { kWhole, kSuffix, kParts };
 constexpr int kMaxParts = 32;
+
+// Parts of a row at position pos (64 tokens each or more).  It follows from the row's own position and the batch
+// alone, so a row's sums do not depend on the capacity of its context or on the call that decodes it; the grid's
+// parts do not bound it (attn_parts).
+__host__ __device__ __forceinline__ int row_parts(int pos, int parts) {
+  const int most = pos >> 6;
+  return most < 1 ? 1 : (most < parts ? most : parts);
+}
 
 // ONE: every column group of the q/k/v formation fits one per thread ((nrep + 2) * HD / 4 <= NW * 64), so
 // the partials of a single group are held (fewer registers, more workgroups per CU); else up to 16 query
@@ -293,11 +304,14 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   if (item >= R * D.nkv * (MODE == kParts ? Q.parts : 1)) return;
   const int part = MODE == kParts ? item % Q.parts : 0;
   if constexpr (MODE == kParts) item /= Q.parts;
-  const bool last = MODE != kParts || part == Q.parts - 1;  // holds the current token
   const int kvh = item % D.nkv;
   const int r = item / D.nkv;
   int seq, pos;
   row_place(rm, r, &seq, &pos);
+  if (MODE != kSuffix && (pos < Q.lo || pos >= Q.hi)) return;
+  const int parts = MODE == kParts ? row_parts(pos, Q.parts) : 1;
+  if (part >= parts) return;
+  const bool last = part == parts - 1;  // holds the current token
   const int nrep = D.nh / D.nkv;
   const int hh = lane & 15, g = lane >> 4;
   const int blk = D.blk;
@@ -310,7 +324,7 @@ void k_attn_mfma(Dims D, uint16_t* __restrict__ kv, int n_blocks, const int32_t*
   // keys read from the cache: t_begin .. t_end - 1
   int t_begin = MODE == kSuffix ? Q.t_begin : 0, t_end = pos;
   if constexpr (MODE == kParts) {
-    const int per = ((pos + 15) / 16 + Q.parts - 1) / Q.parts * 16;
+    const int per = ((pos + 15) / 16 + parts - 1) / parts * 16;
     t_begin = part * per;
     t_end = min(pos, t_begin + per);
   }
@@ -873,7 +887,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(Dims D, const uint16_t*
 // parts one after the other (4 rows, 28 heads, 16 parts).
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ st_o, const float* __restrict__ st_ml,
-                                                    int R, int nh, int parts, uint16_t* __restrict__ out) {
+                                                    const int32_t* __restrict__ ctx_len, int lo, int R, int nh,
+                                                    int stride, uint16_t* __restrict__ out) {
   constexpr int G8 = HD / 8, PL = 256 / G8;       // dimension groups, part lanes
   constexpr int NP = (kMaxParts + PL - 1) / PL;   // parts a thread takes at most
   __shared__ float s_o[PL][HD + 4];
@@ -881,10 +896,14 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ st
   const size_t rh = blockIdx.x;
   const int r = (int)(rh / nh), h = (int)(rh % nh);
   const int g = tid % G8, p0 = tid / G8;
-  const float2 st = *reinterpret_cast<const float2*>(st_ml + (rh * parts + min(lane, parts - 1)) * 2);
+  // stride: the grid's parts; states of parts that the row does not have are loaded and not used
+  const int pos = ctx_len[r];
+  const float2 st = *reinterpret_cast<const float2*>(st_ml + (rh * stride + min(lane, stride - 1)) * 2);
   float v[NP][8];
 #pragma unroll
-  for (int i = 0; i < NP; ++i) ld8(st_o, (rh * parts + min(p0 + i * PL, parts - 1)) * HD + 8 * g, v[i]);
+  for (int i = 0; i < NP; ++i) ld8(st_o, (rh * stride + min(p0 + i * PL, stride - 1)) * HD + 8 * g, v[i]);
+  if (pos < lo) return;  // k_attn_mfma's whole-context form has written this row
+  const int parts = row_parts(pos, stride);
   const bool has = lane < parts && st.y > 0.f;
   const float mx = wave_max(has ? st.x : -INFINITY);
   const float w = has ? expf(st.x - mx) : 0.f;
@@ -1066,7 +1085,7 @@ bool mfma_attention(const Dims& D) { return D.dtype == ROLLOUT_DTYPE_BF16 && (D.
 
 }  // namespace
 
-// Waves per decode-attention workgroup: four once there is a workgroup per CU.  With that many
+// Waves per decode-attention workgroup (a row's parts always take four): four once there is a workgroup per CU.  With that many
 // workgroups the KV stream runs near the HBM rate either way, and four waves halve the merge of the
 // waves' softmax states (7B, 256 workgroups: decode +1.6% over eight).  Eight for smaller grids, which
 // need the loads of more waves in flight.  ROLLOUT_ATTN_WAVES=4 or 8 forces the choice (read per call).
@@ -1080,18 +1099,18 @@ int attn_waves(int n_workgroups) {
 // k_attn_mfma grid: one workgroup per (row, KV head) (and part), rounded up to a multiple of the 8 XCDs
 static unsigned attn_grid(int R, const Dims& D, int parts = 1) { return (unsigned)(R * D.nkv * parts + 7) / 8 * 8; }
 
-// Parts that a decode row's context is shared out to (1: none), from the batch's (row, KV head) pairs and the
-// longest context of the call.  A pair's workgroup takes 1.6 us per round of its eight waves' tiles, alone on
-// its CU; shared out, a pair costs the combine kernel (4 us) more.  So contexts of at least kPartMinTokens
-// (eight rounds) on at most half the CUs are shared out until the CUs are used, 64 tokens a part or more.
+// Workgroups that a decode row's context may be shared out to (1: none), rows at positions up to last.
+// A pair's workgroup takes 1.6 us per round of its eight waves' tiles, alone on its CU; shared out, a pair costs the
+// merge kernel (4.6 us) more.  So rows at kAttnPartTokens (eight rounds) or more, in batches whose (row, KV head)
+// pairs leave half of the CUs idle, are shared out until the CUs are used.
 // 4 rows of 7B width (16 pairs), context 3,000, 16 parts:
 // prefix and suffix pass 40 + 9.6 us a layer, in parts 11.4 + 4.6; whole decode steps at contexts of 1,100, 2,000
-// and 3,000 tokens gain 3, 9 and 13-25%, and lose 0-3% at 300 if shared out there.
-constexpr int kPartMinTokens = 1024;
-int attn_parts(const Dims& D, int R, int ctx_max) {
-  const int pairs = R * D.nkv;
-  if (!mfma_attention(D) || ctx_max < kPartMinTokens || pairs > 128) return 1;
-  return std::min(std::min(kMaxParts, 256 / pairs), ctx_max / 64);
+// and 3,000 tokens gain 3, 9 and 13-25%; at 300 the two forms are within 1 to 3% of each other either way.  (Parts of
+// eight waves: 14.3 us.)
+bool attn_few_rows(const Dims& D, int R) { return mfma_attention(D) && (int64_t)R * D.nkv <= 128; }
+int attn_parts(const Dims& D, int R, int last) {
+  if (!attn_few_rows(D, R) || last < kAttnPartTokens) return 1;
+  return std::min(std::min(kMaxParts, 256 / (R * D.nkv)), last / 64);  // the last as far as row_parts uses it
 }
 
 bool attention_shares_prefix(const Dims& D) { return mfma_attention(D); }
@@ -1104,7 +1123,7 @@ hipError_t launch_attention_shared(hipStream_t s, const Dims& D, void* kv_pool, 
   if (!mfma_attention(D) || rm.P != 0 || G < 1 || R % G || p_shared < D.blk || p_shared % D.blk ||
       qkv_splits < 1 || qkv_splits > kMaxQkvSplits || max_blocks > kMaxTableBlocks)
     return hipErrorInvalidValue;
-  const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, p_shared, (uint16_t*)q_keep, st_o, st_ml, 1};
+  const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, p_shared, (uint16_t*)q_keep, st_o, st_ml, 1, 0, INT_MAX};
   uint16_t* kk = (uint16_t*)kv_pool;
   uint16_t* oo = (uint16_t*)out;
   // suffix: keys p_shared .. pos of every row, q/k/v formed, state kept
@@ -1163,7 +1182,7 @@ bool attention_forms_qkv(const Dims& D) { return mfma_attention(D); }
 hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* kv_pool, int n_blocks,
                             const int32_t* tables, int max_blocks, RowMap rm, int R, int splits, int split_tokens,
                             int layer, float* opart, float* ml, void* out, int32_t* err, const float* qkv_part,
-                            int qkv_splits, const float* rope_cos, const float* rope_sin, int parts) {
+                            int qkv_splits, const float* rope_cos, const float* rope_sin, PosSpan pos) {
   if (R <= 0) return hipSuccess;
   if (qkv_part && (!mfma_attention(D) || rm.P != 0 || qkv_splits < 1 || qkv_splits > kMaxQkvSplits))
     return hipErrorInvalidValue;
@@ -1183,6 +1202,7 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
                            (const uint16_t*)kv_pool, n_blocks, tables, max_blocks, rm, R, layer, (uint16_t*)out, err);
       return hipGetLastError();
     }
+    const int parts = attn_parts(D, R, pos.hi);
     const int nw = attn_waves(R * D.nkv);
     static const int dr = [] {
       const char* v = std::getenv("ROLLOUT_ATTN_RING");
@@ -1190,7 +1210,8 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
       return d == 3 || d == 4 ? d : 2;
     }();
     if (parts > 1) {
-      const AttnQKV Qp{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, opart, ml, parts};
+      const int lo = pos.lo < kAttnPartTokens ? kAttnPartTokens : 0;
+      const AttnQKV Qp{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, opart, ml, parts, lo, INT_MAX};
       const dim3 ggrid(attn_grid(R, D, parts));
       const size_t tab = (size_t)max_blocks * 4;
 #define ROLLOUT_PARTS(HD)                                                                                            \
@@ -1208,13 +1229,18 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       if (D.hd == 128)
-        hipLaunchKernelGGL(k_attn_merge<128>, dim3(R * D.nh), dim3(256), 0, s, opart, ml, R, D.nh, parts, (uint16_t*)out);
+        hipLaunchKernelGGL(k_attn_merge<128>, dim3(R * D.nh), dim3(256), 0, s, opart, ml, rm.ctx_len, lo, R, D.nh, parts,
+                           (uint16_t*)out);
       else
-        hipLaunchKernelGGL(k_attn_merge<64>, dim3(R * D.nh), dim3(256), 0, s, opart, ml, R, D.nh, parts, (uint16_t*)out);
-      return hipGetLastError();
+        hipLaunchKernelGGL(k_attn_merge<64>, dim3(R * D.nh), dim3(256), 0, s, opart, ml, rm.ctx_len, lo, R, D.nh, parts,
+                           (uint16_t*)out);
+      e = hipGetLastError();
+      if (e != hipSuccess || lo == 0) return e;
     }
     const dim3 grid(attn_grid(R, D));
-    const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, nullptr, nullptr, 1};
+    // beside rows in parts: the rows below kAttnPartTokens
+    const AttnQKV Q{qkv_part, qkv_splits, rope_cos, rope_sin, 0, nullptr, nullptr, nullptr, 1, 0,
+                    parts > 1 ? kAttnPartTokens : INT_MAX};
     uint16_t* kk = (uint16_t*)kv_pool;
     uint16_t* oo = (uint16_t*)out;
     const size_t tab_bytes = (size_t)max_blocks * 4;

@@ -60,6 +60,12 @@ struct RowMap {
   int P, G, seq0;
 };
 
+// The positions of a decode call's rows, as far as the host knows them: lo .. hi.  They choose the attention's
+// launches; rows outside them are decoded all the same.
+struct PosSpan {
+  int lo, hi;
+};
+
 // ---------------------------------------------------------------------------
 // Launchers (each enqueues on the given stream and returns hipGetLastError()).
 // ---------------------------------------------------------------------------
@@ -130,9 +136,13 @@ bool attention_forms_qkv(const Dims& D);
 hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* kv_pool, int n_blocks,
                             const int32_t* tables, int max_blocks, RowMap rm, int R, int splits, int split_tokens,
                             int layer, float* opart, float* ml, void* out, int32_t* err, const float* qkv_part,
-                            int qkv_splits, const float* rope_cos, const float* rope_sin, int parts);
-// workgroups that share a decode row's context (launch_attention's parts; opart and ml hold R x n_heads x parts)
-int attn_parts(const Dims& D, int R, int ctx_max);
+                            int qkv_splits, const float* rope_cos, const float* rope_sin, PosSpan pos);
+// Rows of small decode batches (attn_few_rows) at positions of kAttnPartTokens or more have their context shared out
+// over up to attn_parts workgroups, for rows at positions up to last (opart and ml hold R x n_heads x parts).  How a
+// row is decoded depends on its own position and on the batch only.
+constexpr int kAttnPartTokens = 1024;
+bool attn_few_rows(const Dims& D, int R);
+int attn_parts(const Dims& D, int R, int last);
 // Decode attention with the group's shared prompt read once per group: a suffix pass over each row's own
 // keys (p_shared .. pos; q/k/v formed from the QKV split partials as above, rotated q kept in q_keep,
 // softmax state in st_o [R][nh][hd] / st_ml [R][nh][2]) and a prefix pass over the shared blocks that

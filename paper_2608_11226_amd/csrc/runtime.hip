@@ -402,22 +402,23 @@ rollout_status proj(rollout_ctx* c, const void* X, const void* W, float* out, in
 // Whether a decode batch takes the shared-prefix attention (whole groups of G >= 2 sequences whose prompt
 // fills at least one KV block).  By default only when G x shared prompt tokens >= 8192: below that the
 // group's redundant prompt reads are served by the caches and the extra pass costs more than it saves.  Nor
-// when the rows' contexts are shared out (attn_parts): so few rows leave the prefix pass on a few CUs (one
-// group of 4, 3,000 tokens at 7B width: 16 workgroups, 40 us).
-// ROLLOUT_SHARED_PREFIX=0 never takes it, =2 always does (read per call).
-bool use_shared_prefix(const rollout_ctx* c, int M, const RowMap& rm, int parts) {
+// for the few rows that attn_few_rows names: they leave the prefix pass on a few CUs (one group of 4, 3,000 tokens at
+// 7B width: 16 workgroups, 40 us; two-layer steps of one group of 16 at 600 tokens 399 us without it, 412 with it, of
+// 32 at 1,000 tokens 422 and 436).  ROLLOUT_SHARED_PREFIX=0 never takes it, =2 always does (read per call).
+bool use_shared_prefix(const rollout_ctx* c, int M, const RowMap& rm) {
   const char* v = std::getenv("ROLLOUT_SHARED_PREFIX");
   const int mode = v ? std::atoi(v) : 1;
   const int p_shared = c->P / c->D.blk * c->D.blk;
   if (mode == 0 || !c->wave || c->seq_refill || c->G < 2 || p_shared < c->D.blk || M % c->G || rm.seq0 % c->G) return false;
-  return mode == 2 || (parts == 1 && (int64_t)c->G * p_shared >= 8192);
+  return mode == 2 || ((int64_t)c->G * p_shared >= 8192 && !attn_few_rows(c->D, M));
 }
 
 // One transformer pass over M rows (prefill chunk or decode batch). On return
 // c->Lo.a holds the final-normed hidden states (cache dtype).
 // normed: the first layer's norm output is already in place (embed_rows)
+// pos: positions of decode rows
 rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max, double kv_tokens_read,
-                              bool normed = false, Advance adv = {}) {
+                              bool normed = false, Advance adv = {}, PosSpan pos = {0, 0}) {
   const Dims& D = c->D;
   const Layout& Lo = c->Lo;
   float* x = c->at<float>(Lo.x);
@@ -439,11 +440,11 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
     HIP_TRY(c, launch_residual_norm(c->stream, D.dtype, nullptr, 1, M, D.d, x, c->at<float>(Lo.layers[0].attn_norm),
                                     D.eps, a), "rmsnorm");
   }
-  // decode rows: a few long contexts are shared out over the CUs (bounded by the state buffers)
-  int parts = rm.P == 0 ? attn_parts(D, M, attn_ctx_max) : 1;
-  parts = std::max(1, (int)std::min<int64_t>(parts, (int64_t)Lo.R * Lo.attn_splits_max / M));
+  // the states of decode rows in parts (M x parts <= 256)
+  if (rm.P == 0 && (int64_t)M * attn_parts(D, M, pos.hi) > (int64_t)Lo.R * Lo.attn_splits_max)
+    return fail(c, ROLLOUT_EINVAL, "internal: attention state workspace too small");
   // rows of whole groups read their group's shared prompt blocks once per group (shared-prefix attention)
-  const int p_shared = (rm.P == 0 && attention_shares_prefix(D) && use_shared_prefix(c, M, rm, parts)) ? c->P / D.blk * D.blk : 0;
+  const int p_shared = (rm.P == 0 && attention_shares_prefix(D) && use_shared_prefix(c, M, rm)) ? c->P / D.blk * D.blk : 0;
   for (int l = 0; l < D.L; ++l) {
     const Layer& y = Lo.layers[l];
     int s;
@@ -466,7 +467,7 @@ rollout_status forward_layers(rollout_ctx* c, int M, RowMap rm, int attn_ctx_max
       else
         HIP_TRY(c, launch_attention(c->stream, D, q, kv, c->n_blocks, tables, Lo.max_blocks, rm, M, asplits, st_tok, l,
                                     opart, ml, o, err, attn_qkv ? part : nullptr, s, c->at<float>(Lo.rope_cos),
-                                    c->at<float>(Lo.rope_sin), parts), "attention");
+                                    c->at<float>(Lo.rope_sin), pos), "attention");
     }
     r = proj(c, o, c->at(y.wo), part, M, D.d, D.qd, &s, x);
     if (r) return r;
@@ -591,7 +592,7 @@ rollout_status do_prefill(rollout_ctx* c, const int32_t* d_prompts, int n_prompt
 
 // Enqueue one decode step of the current wave (no host-side state change).
 rollout_status enqueue_decode(rollout_ctx* c, const int32_t* tokens, int tok_stride, const int32_t* col,
-                              float* d_logits, int ctx_max, Advance adv) {
+                              float* d_logits, int ctx_max, PosSpan pos, Advance adv) {
   const Dims& D = c->D;
   const Layout& Lo = c->Lo;
   const int S = c->S;
@@ -599,11 +600,29 @@ rollout_status enqueue_decode(rollout_ctx* c, const int32_t* tokens, int tok_str
   rollout_status r = embed_rows(c, tokens, tok_stride, col, S, &normed);
   if (r) return r;
   RowMap rm{c->at<int32_t>(Lo.ctx_len), 0, 1, 0};
-  r = forward_layers(c, S, rm, ctx_max, (double)S * (c->cur_len + 1), normed, adv);
+  r = forward_layers(c, S, rm, ctx_max, (double)S * (c->cur_len + 1), normed, adv, pos);
   if (r) return r;
   int s;
   r = gemm(c, c->at(Lo.a), c->at(Lo.lm_head), d_logits, S, D.V, D.d, 1, &s);
   if (r) return r;
+  return ROLLOUT_OK;
+}
+
+// The launches of step() as an executable graph.
+template <typename Step>
+rollout_status capture_graph(rollout_ctx* c, Step&& step, hipGraphExec_t* exec) {
+  hipGraph_t graph = nullptr;
+  HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal), "begin capture");
+  rollout_status r = step();
+  hipError_t ce = hipStreamEndCapture(c->stream, &graph);
+  if (r) {
+    if (graph) hipGraphDestroy(graph);
+    return r;
+  }
+  if (ce != hipSuccess) return hip_fail(c, ce, "end capture");
+  hipError_t ie = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+  hipGraphDestroy(graph);
+  if (ie != hipSuccess) return hip_fail(c, ie, "graph instantiate");
   return ROLLOUT_OK;
 }
 
@@ -794,7 +813,7 @@ rollout_status rollout_decode_step(rollout_ctx* ctx, const int32_t* d_tokens, fl
   if (ctx->cur_len + 1 > ctx->P + ctx->cfg.max_new_tokens)
     return fail(ctx, ROLLOUT_ESTATE, "context full (max_prompt_len + max_new_tokens reached)");
   rollout_status r = enqueue_decode(ctx, d_tokens, 1, nullptr, d_logits, ctx->P + ctx->cfg.max_new_tokens,
-                                    Advance{ctx->at<int32_t>(ctx->Lo.ctx_len), nullptr});
+                                    PosSpan{ctx->cur_len, ctx->cur_len}, Advance{ctx->at<int32_t>(ctx->Lo.ctx_len), nullptr});
   if (r) return r;
   ctx->cur_len += 1;
   return ROLLOUT_OK;
@@ -873,8 +892,8 @@ rollout_status rollout_generate(rollout_ctx* ctx, const int32_t* d_prompts, int3
     const bool use_graph = !ctx->prof.on;
     // cols[0] = column of the token fed in (read by the embedding), cols[1] = column drawn (read by the draw); both and
     // the sequences' positions move on in between, with the step's last norm
-    auto step = [&]() -> rollout_status {
-      rollout_status rr = enqueue_decode(ctx, tok, N, cols, logits, prompt_len + N,
+    auto step = [&](PosSpan pos) -> rollout_status {
+      rollout_status rr = enqueue_decode(ctx, tok, N, cols, logits, prompt_len + N, pos,
                                          Advance{ctx->at<int32_t>(ctx->Lo.ctx_len), cols});
       if (rr) return rr;
       HIP_TRY(ctx, launch_sample(ctx->stream, logits, Sw, D.V, temperature, top_p, uu, N, cols + 1, tok, N,
@@ -883,48 +902,43 @@ rollout_status rollout_generate(rollout_ctx* ctx, const int32_t* d_prompts, int3
     };
     if (!use_graph) {
       for (int t = 1; t < N; ++t) {
-        r = step();
+        r = step(PosSpan{ctx->cur_len, ctx->cur_len});
         if (r) return r;
         ctx->cur_len += 1;
       }
       continue;
     }
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    HIP_TRY(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal), "begin capture");
-    r = step();
-    hipError_t ce = hipStreamEndCapture(ctx->stream, &graph);
-    if (r) {
-      if (graph) hipGraphDestroy(graph);
-      return r;
-    }
-    if (ce != hipSuccess) return hip_fail(ctx, ce, "end capture");
-    hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    hipGraphDestroy(graph);
-    if (ie != hipSuccess) return hip_fail(ctx, ie, "graph instantiate");
-    {
-      Range replay("rollout_generate: decode steps (graph replay)");
-      for (int t = 1; t < N; ++t) {
-        hipError_t le = hipGraphLaunch(exec, ctx->stream);
-        if (le != hipSuccess) {
-          hipStreamSynchronize(ctx->stream);
-          hipGraphExecDestroy(exec);
-          return hip_fail(ctx, le, "graph launch");
+    // one graph for all steps, or two where a few rows' attention changes its launches on the way (kAttnPartTokens)
+    for (int t0 = 1, t1; t0 < N; t0 = t1) {
+      const int at = prompt_len + t0 - 1;  // the rows' position at step t0
+      t1 = attn_few_rows(D, Sw) && at < kAttnPartTokens ? std::min(N, t0 + kAttnPartTokens - at) : N;
+      hipGraphExec_t exec = nullptr;
+      r = capture_graph(ctx, [&] { return step(PosSpan{at, prompt_len + t1 - 2}); }, &exec);
+      if (r) return r;
+      {
+        Range replay("rollout_generate: decode steps (graph replay)");
+        for (int t = t0; t < t1; ++t) {
+          hipError_t le = hipGraphLaunch(exec, ctx->stream);
+          if (le != hipSuccess) {
+            hipStreamSynchronize(ctx->stream);
+            hipGraphExecDestroy(exec);
+            return hip_fail(ctx, le, "graph launch");
+          }
+          ctx->cur_len += 1;
         }
-        ctx->cur_len += 1;
       }
+      // the replays run on after the call returns: the executable is destroyed once they have finished
+      hipEvent_t done = nullptr;
+      hipError_t ee = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+      if (ee == hipSuccess) ee = hipEventRecord(done, ctx->stream);
+      if (ee != hipSuccess) {
+        hipStreamSynchronize(ctx->stream);
+        hipGraphExecDestroy(exec);
+        if (done) hipEventDestroy(done);
+        return hip_fail(ctx, ee, "wave event");
+      }
+      ctx->retired.emplace_back(exec, done);
     }
-    // the replays run on after the call returns: the executable is destroyed once they have finished
-    hipEvent_t done = nullptr;
-    hipError_t ee = hipEventCreateWithFlags(&done, hipEventDisableTiming);
-    if (ee == hipSuccess) ee = hipEventRecord(done, ctx->stream);
-    if (ee != hipSuccess) {
-      hipStreamSynchronize(ctx->stream);
-      hipGraphExecDestroy(exec);
-      if (done) hipEventDestroy(done);
-      return hip_fail(ctx, ee, "wave event");
-    }
-    ctx->retired.emplace_back(exec, done);
   }
   return ROLLOUT_OK;
 }
@@ -1058,8 +1072,8 @@ rollout_status rollout_generate_eos(rollout_ctx* ctx, const int32_t* d_prompts, 
     return ROLLOUT_OK;
   };
   // one decode step over all slots: feed each slot's last draw, draw with its staged uniform, file the draws
-  auto step = [&]() -> rollout_status {
-    rollout_status rr = enqueue_decode(ctx, cb.draw, 1, nullptr, logits, P + N, Advance{});
+  auto step = [&](PosSpan pos) -> rollout_status {
+    rollout_status rr = enqueue_decode(ctx, cb.draw, 1, nullptr, logits, P + N, pos, Advance{});
     if (rr) return rr;
     HIP_TRY(ctx, launch_sample(ctx->stream, logits, S, D.V, temperature, top_p, cb.u_slot, 1, nullptr, cb.draw, 1,
                                samp), "sample");
@@ -1074,9 +1088,12 @@ rollout_status rollout_generate_eos(rollout_ctx* ctx, const int32_t* d_prompts, 
     for (int i = 0; i < S && !r; ++i) r = admit_seq(i, 0);
   }
   if (r) return r;
-  hipGraphExec_t exec = nullptr;
+  // Graphs of a step, captured when first needed: of a few rows short of kAttnPartTokens, on both sides of it, and past
+  // it (their attention's launches); all other batches only the first.
+  hipGraphExec_t execs[3] = {nullptr, nullptr, nullptr};
   auto finish = [&](rollout_status st) {
-    if (exec) {
+    for (hipGraphExec_t& exec : execs) {
+      if (!exec) continue;
       hipStreamSynchronize(ctx->stream);
       hipGraphExecDestroy(exec);
       exec = nullptr;
@@ -1084,32 +1101,35 @@ rollout_status rollout_generate_eos(rollout_ctx* ctx, const int32_t* d_prompts, 
     ctx->wave = false;  // the slots' state is not a wave that rollout_decode_step may continue
     return st;
   };
-  if (!ctx->prof.on) {
-    hipGraph_t graph = nullptr;
-    HIP_TRY(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal), "begin capture");
-    r = step();
-    hipError_t ce = hipStreamEndCapture(ctx->stream, &graph);
-    if (r) {
-      if (graph) hipGraphDestroy(graph);
-      return finish(r);
-    }
-    if (ce != hipSuccess) return finish(hip_fail(ctx, ce, "end capture"));
-    hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    hipGraphDestroy(graph);
-    if (ie != hipSuccess) return finish(hip_fail(ctx, ie, "graph instantiate"));
-  }
   int steps = 0;
+  const int last = P + std::max(N - 2, 0);  // the last position a token is fed at
+  // positions of the live slots over the next refill_interval steps
+  auto positions = [&]() {
+    int64_t lo = last, hi = P;
+    for (int i = 0; i < S; ++i) {
+      if (slot_seq[i] < 0) continue;
+      const int64_t at = (int64_t)P + steps - admit_step[slot_seq[i]];
+      lo = std::min(lo, at);
+      hi = std::max(hi, at + refill_interval - 1);
+    }
+    return PosSpan{(int)lo, (int)std::min<int64_t>(hi, last)};
+  };
   auto live = [&]() {
     for (int i = 0; i < S; ++i)
       if (slot_seq[i] >= 0) return true;
     return false;
   };
   while (live()) {
+    PosSpan pos = positions();
+    const int form = !attn_few_rows(D, S) || pos.hi < kAttnPartTokens ? 0 : (pos.lo < kAttnPartTokens ? 1 : 2);
+    if (form > 0) pos = PosSpan{form == 1 ? P : std::max(P, kAttnPartTokens), last};  // of every step that has this form
+    if (!ctx->prof.on && !execs[form] && (r = capture_graph(ctx, [&] { return step(pos); }, &execs[form])))
+      return finish(r);
     for (int i = 0; i < refill_interval; ++i) {
-      if (exec) {
-        hipError_t le = hipGraphLaunch(exec, ctx->stream);
+      if (execs[form]) {
+        hipError_t le = hipGraphLaunch(execs[form], ctx->stream);
         if (le != hipSuccess) return finish(hip_fail(ctx, le, "graph launch"));
-      } else if ((r = step())) {
+      } else if ((r = step(pos))) {
         return finish(r);
       }
     }

@@ -97,6 +97,65 @@ def test_small_bf16_generate_equals_the_eager_chain(seqs, shared, waves, monkeyp
     eng.close()
 
 
+# contexts that stay below 1,024 tokens, that cross them (where the decode attention of a few rows begins to share
+# a row out), and a group whose prompt is long enough for the shared-prefix pass
+@pytest.mark.parametrize("P,G", [(40, 4), (1010, 4), (600, 16)])
+def test_decode_does_not_depend_on_the_capacity_of_the_context(P, G, monkeypatch):
+    _set_knobs(monkeypatch, None, None)
+    N, T, top_p = 24, 0.9, 0.95
+    log(f"bf16 decode in contexts of two capacities: P={P}, G={G}, N={N}")
+    prompts = W.prompts(1, P, SMALL_BF16[6], seed=45)
+    u = W.uniforms(G, N, seed=46)
+    chain = None
+    for spare in (1, 2000):
+        cfg = R.model_config(SMALL_BF16, R.DTYPE_BF16, P, N + spare, G)
+        eng = R.Engine(cfg, group_size=G)
+        tokens = _graph(eng, prompts, G, G, N, T, top_p, u)
+        last = torch.empty((G, cfg.vocab), dtype=torch.float32, device="cuda:0")
+        R.rollout_decode_step(eng.ctx, to_dev(np.ascontiguousarray(tokens[:, -1]), torch), last)
+        eng.synchronize()
+        steps = []
+        logits = torch.empty_like(last)
+        R.rollout_prefill(eng.ctx, to_dev(prompts, torch), 1, P, G, logits)
+        for t in range(N):
+            R.rollout_decode_step(eng.ctx, to_dev(np.ascontiguousarray(tokens[:, t]), torch), logits)
+            eng.synchronize()
+            steps.append(logits.cpu().numpy())
+        eng.close()
+        assert np.array_equal(last.cpu().numpy(), steps[-1]), "logits after a graph rollout and after the eager chain"
+        if chain is None:
+            chain = tokens, steps
+        assert np.array_equal(tokens, chain[0])
+        bad = [t for t in range(N) if not np.array_equal(steps[t], chain[1][t])]
+        assert not bad, f"steps whose logits depend on the context's capacity: {bad}"
+
+
+def test_rows_on_both_sides_of_the_shared_out_attention(monkeypatch):
+    """Slots that hold completions of different lengths, some short of 1,024 tokens and some past them: every
+    completion has the tokens of rollout_generate, cut at its stop token."""
+    _set_knobs(monkeypatch, None, None)
+    n_prompts, P, G, N, T, top_p = 3, 1010, 4, 24, 0.9, 0.95
+    log(f"bf16 continuous batching across 1,024 tokens: {n_prompts} prompts x {P}, G={G}, N={N}")
+    cfg = R.model_config(SMALL_BF16, R.DTYPE_BF16, P, N, G + 1)
+    eng = R.Engine(cfg)
+    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=47)
+    u = W.uniforms(n_prompts * G, N, seed=48)
+    want = _graph(eng, prompts, G, G, N, T, top_p, u)
+    stop = np.arange(cfg.vocab // 16, dtype=np.int32)
+    ends = [int(np.argmax(np.append(row[:-1] < len(stop), True))) + 1 for row in want]
+    assert len(set(ends)) > 3 and max(ends) > 16  # slots are refilled apart, and some rows pass 1,024 tokens
+    got = torch.full((n_prompts * G, N), -7, dtype=torch.int32, device="cuda:0")
+    lengths = torch.zeros(n_prompts * G, dtype=torch.int32, device="cuda:0")
+    R.rollout_generate_eos(eng.ctx, to_dev(prompts, torch), n_prompts, P, G, G, N, T, top_p, to_dev(u, torch),
+                           to_dev(stop, torch), len(stop), 2, False, got, lengths, None)
+    eng.synchronize()
+    eng.close()
+    got = got.cpu().numpy()
+    assert lengths.cpu().tolist() == ends
+    for s, n in enumerate(ends):
+        assert np.array_equal(got[s, :n], want[s, :n]) and np.all(got[s, n:] == -1), f"completion {s}"
+
+
 # name: (shape, prompts, prompt length, G, sequences in flight, new tokens, temperature, top-p)
 LAUNCH = {
     "7b": ("7b", 8, 256, 8, 64, 16, 0.9, 0.95),
