@@ -770,7 +770,7 @@ int tile_kslice(int K, int splits, bool q4) { return q4 ? (kslice_for(K, splits)
 TilePlan tile_plan(int M, int N, int K, int smin, int smax, bool q4 = false) {
   const int nbt = N / 16, mb = (M + 15) / 16, cus = device_cus(), per_xcd = std::max(1, cus / 8);
   const bool single = smax == 1;
-  TilePlan best{T_8x16, 1, 1};
+  TilePlan best{T_8x16, 1, 0};  // no candidate: refused by launch_pp
   float best_cost = 3e38f;
   for (int t = 0; t < kTiles; ++t) {
     bool look;
@@ -813,12 +813,15 @@ TilePlan tile_plan(int M, int N, int K, int smin, int smax, bool q4 = false) {
 }
 
 template <int NB, int MBW, int WN, int WM, int NS, bool SWI, bool Q4>
-void launch_pp(hipStream_t s, const TilePlan& p, const bf16x8_t* x, const bf16x8_t* w, const floatx4_t* ws, float* out,
-               int M, int N, int K, uint16_t* h, int rep) {
+hipError_t launch_pp(hipStream_t s, const TilePlan& p, const bf16x8_t* x, const bf16x8_t* w, const floatx4_t* ws,
+                     float* out, int M, int N, int K, uint16_t* h, int rep) {
+  // every N tile has a block and holds all of its blocks
+  if (p.nt < 1 || p.nt > N / 16 || (N / 16 + p.nt - 1) / p.nt > NB * WN) return hipErrorInvalidValue;
   const int mt = ((M + 15) / 16 + MBW * WM - 1) / (MBW * WM);
   const dim3 grid((unsigned)(mt * p.nt + 7) / 8 * 8, p.splits);
   hipLaunchKernelGGL((k_gemm_pp<NB, MBW, WN, WM, NS, SWI, Q4>), grid, dim3(512), 0, s, x, w, ws, out, M, N, K,
                      tile_kslice(K, p.splits, Q4), p.nt, h, rep);
+  return hipGetLastError();
 }
 
 // LDS of a tile: NS x (TN + TM) KB (int4 one more fragment), at most 160
@@ -827,14 +830,13 @@ hipError_t launch_tile(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, floa
                        uint16_t* h, int rep) {
   const TilePlan p = tile_plan(M, N, K, splits, splits);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_8x16: launch_pp<4, 4, 2, 4, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    case T_16x16: launch_pp<4, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
-    default: launch_pp<5, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep); break;
+    case T_10x8: return launch_pp<5, 2, 2, 4, 5, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep);
+    case T_16x8: return launch_pp<4, 4, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep);
+    case T_8x16: return launch_pp<4, 4, 2, 4, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep);
+    case T_10x16: return launch_pp<5, 4, 2, 4, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep);
+    case T_16x16: return launch_pp<4, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep);
+    default: return launch_pp<5, 8, 4, 2, 4, SWI, false>(s, p, x, w, nullptr, out, M, N, K, h, rep);
   }
-  return hipGetLastError();
 }
 
 template <bool SWI>
@@ -842,12 +844,11 @@ hipError_t launch_tile_q4(hipStream_t s, const bf16x8_t* x, const bf16x8_t* w, c
                           int N, int K, int splits, uint16_t* h, int rep) {
   const TilePlan p = tile_plan(M, N, K, splits, splits, true);
   switch (p.tile) {
-    case T_10x8: launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
-    case T_16x8: launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
-    case T_10x16: launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
-    default: launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep); break;
+    case T_10x8: return launch_pp<5, 2, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep);
+    case T_16x8: return launch_pp<4, 4, 4, 2, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep);
+    case T_10x16: return launch_pp<5, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep);
+    default: return launch_pp<4, 4, 2, 4, 4, SWI, true>(s, p, x, w, ws, out, M, N, K, h, rep);
   }
-  return hipGetLastError();
 }
 
 // Ring kernel shape of the split projections (QKV, O, down at M <= 64).  Workgroups of 4 or 8 weight
