@@ -11,7 +11,7 @@ import pytest
 
 import paper_2608_11226_amd as R
 import workload as W
-from gpu_helpers import log, shape_of, to_dev
+from gpu_helpers import TILE_ROWS, check_rows, log, one_token_logits, shape_of, to_dev
 from oracle import OracleModel, bf16_round, rollout
 from oracle.quant import dequantize_int4, quantize_int4
 
@@ -77,6 +77,22 @@ def _teacher_forced(shape, n_prompts, G, P, N, blk=16, seed=51):
     return err
 
 
+def _one_token_rows(what, shape, rows):
+    """Prompts of one token, so that every row of every GEMM has logits of its own to compare."""
+    cfg = R.model_config(shape, R.DTYPE_INT4, 1, 1, max(rows))
+    eng = R.Engine(cfg)
+    model = OracleModel(shape_of(cfg), mode="int4")
+    tokens = W.prompts(max(rows), 1, cfg.vocab, seed=57)
+    want = one_token_logits(model, tokens[:, 0])
+    for n in rows:
+        log(f"{what}: {n} rows")
+        logits = torch.empty((n, cfg.vocab), dtype=torch.float32, device="cuda:0")
+        R.rollout_prefill(eng.ctx, to_dev(tokens[:n], torch), n, 1, 1, logits)
+        eng.synchronize()
+        check_rows(logits.cpu().numpy(), want[:n])
+    eng.close()
+
+
 # prefill rows n_prompts x P above or below 64 (dequantise + tile GEMM, or the int4 ring), decode rows S
 @pytest.mark.parametrize("shape,n_prompts,G,P", [
     (INT4_SMALL, 3, 4, 32),     # prefill 96 rows (tile), decode 12 rows (ring, one 16-row block)
@@ -93,31 +109,17 @@ def test_int4_teacher_forced_logits(shape, n_prompts, G, P):
 
 
 def test_int4_large_batch_decode_logits():
-    # 256 decode rows: every decode step dequantises into bf16 tiles and takes the tile GEMM
+    # 256 decode rows: every projection of a decode step writes its integers q - z out and takes the tile GEMM
     log("int4 teacher forced, 32 prompts x G=8, P=24 (256-row decode)")
     err = _teacher_forced(INT4_SMALL, 32, 8, 24, N=3, seed=53)
     log(f"  max abs logit error per step: {[round(e, 5) for e in err]}")
     assert max(err) <= 3e-2
 
 
-# row counts around the tile choices of the group-scaled tile GEMM (one to three 128-row activation tiles, one
-# and two 256-row ones), weight blocks that leave partial tiles, one group per K slice and up to eleven
-@pytest.mark.parametrize("n_prompts,P", [(1, 65), (3, 43), (1, 256), (1, 257), (5, 77), (1, 513)])
-def test_int4_tile_gemm_rows(n_prompts, P):
-    shape = (1, 640, 10, 2, 64, 1408, 2064, 1e6)
-    log(f"int4 tile GEMM rows {n_prompts} x {P}")
-    cfg = R.model_config(shape, R.DTYPE_INT4, P, 2, n_prompts)
-    eng = R.Engine(cfg)
-    model = OracleModel(shape_of(cfg), mode="int4")
-    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=57)
-    want = np.stack([model.prefill(p)[1] for p in prompts])
-    logits = torch.empty((n_prompts, cfg.vocab), dtype=torch.float32, device="cuda:0")
-    R.rollout_prefill(eng.ctx, to_dev(prompts, torch), n_prompts, P, 1, logits)
-    eng.synchronize()
-    err = float(np.max(np.abs(logits.cpu().numpy() - want)))
-    log(f"  max abs logit error {err:.4g}")
-    assert err <= 3e-2  # the bf16 contract's bound, as above
-    eng.close()
+@pytest.mark.parametrize("name", [n for n, t in TILE_ROWS.items() if t[1]])
+def test_int4_tile_gemm_rows(name):
+    _, rows, shape = TILE_ROWS[name]
+    _one_token_rows(f"int4 tile GEMM, {name}", shape, rows)
 
 
 # the ring GEMM at one to four 16-row blocks: one group (a set of waves without any), five (an odd share) and
@@ -125,18 +127,4 @@ def test_int4_tile_gemm_rows(n_prompts, P):
 @pytest.mark.parametrize("d,d_ff", [(128, 384), (640, 1408), (640, 26368)])
 def test_int4_ring_gemm_rows(d, d_ff):
     heads = d // 64 if d > 128 else 2
-    shape = (1, d, heads, 2, 64, d_ff, 2064, 1e6)
-    cfg = R.model_config(shape, R.DTYPE_INT4, 64, 2, 1)
-    eng = R.Engine(cfg)
-    model = OracleModel(shape_of(cfg), mode="int4")
-    logits = torch.empty((1, cfg.vocab), dtype=torch.float32, device="cuda:0")
-    for P in (1, 16, 17, 33, 64):
-        log(f"int4 ring GEMM d={d} d_ff={d_ff} rows {P}")
-        prompts = W.prompts(1, P, cfg.vocab, seed=59)
-        want = model.prefill(prompts[0])[1]
-        R.rollout_prefill(eng.ctx, to_dev(prompts, torch), 1, P, 1, logits)
-        eng.synchronize()
-        err = float(np.max(np.abs(logits.cpu().numpy()[0] - want)))
-        log(f"  max abs logit error {err:.4g}")
-        assert err <= 3e-2  # the bf16 contract's bound, as above
-    eng.close()
+    _one_token_rows(f"int4 ring GEMM d={d} d_ff={d_ff}", (1, d, heads, 2, 64, d_ff, 2064, 1e6), (1, 16, 17, 33, 64))
