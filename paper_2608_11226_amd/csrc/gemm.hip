@@ -289,6 +289,7 @@ template <int MB, int NBW, int D, bool SWI, int KW, bool BAL = false>
 __global__ __launch_bounds__(64 * KW) void k_gemm_ring(const bf16x8_t* __restrict__ XF, const bf16x8_t* __restrict__ W,
                                                        float* __restrict__ out, int M, int N, int K, int kslice,
                                                        uint16_t* __restrict__ h, int rep) {
+  if constexpr (!SWI) asm volatile("" ::"s"(rep));  // here, with the other arguments, and not behind the sums
   const int lane = threadIdx.x & 63;
   const int wave = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int nbt = N >> 4, kbt = K >> 5;
@@ -391,26 +392,31 @@ __global__ __launch_bounds__(64 * KW) void k_gemm_ring(const bf16x8_t* __restric
     }
   }
   // D layout of the 16x16 MFMA: lane holds rows 4*(lane/16)+r (weight rows n) of column lane%16 (row m of X)
+  // The copies (rep) outside, one run of stores each: with a loop over them behind every store, and rep loaded there,
+  // launches that write one took longer (64 rows, 768 outputs over 256 inputs 7.2 -> 6.75 us, 256 over 256 6.4 -> 5.95).
+  int c = 0;
+  do {
 #pragma unroll
-  for (int j = 0; j < NBW; ++j) {
-    if (j % KW != wave || j >= nbc) continue;
-    const int n = (nb0 + j) * 16 + 4 * (lane >> 4);
+    for (int j = 0; j < NBW; ++j) {
+      if (j % KW != wave || j >= nbc) continue;
+      const int n = (nb0 + j) * 16 + 4 * (lane >> 4);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int m = mb * 16 + (lane & 15);
-      if (m >= M) continue;
-      if constexpr (SWI) {
-        // rows n, n+1 are (gate, up) of output f = n/2; rows n+2, n+3 of output f + 1
-        const float g0 = acc[j][mb][0], u0 = acc[j][mb][1], g1 = acc[j][mb][2], u1 = acc[j][mb][3];
-        const float h0 = g0 / (1.0f + expf(-g0)) * u0, h1 = g1 / (1.0f + expf(-g1)) * u1;
-        *reinterpret_cast<uint32_t*>(h + xoff(h, m, n >> 1, N >> 1, MB)) = pack_bf16x2(h0, h1);
-      } else {
-        float* o = out + (size_t)blockIdx.y * M * N;
-        const float4 v = make_float4(acc[j][mb][0], acc[j][mb][1], acc[j][mb][2], acc[j][mb][3]);
-        for (int c = 0; c < rep; ++c) *reinterpret_cast<float4*>(o + ((size_t)m * rep + c) * N + n) = v;
+      for (int mb = 0; mb < MB; ++mb) {
+        const int m = mb * 16 + (lane & 15);
+        if (m >= M) continue;
+        if constexpr (SWI) {
+          // rows n, n+1 are (gate, up) of output f = n/2; rows n+2, n+3 of output f + 1
+          const float g0 = acc[j][mb][0], u0 = acc[j][mb][1], g1 = acc[j][mb][2], u1 = acc[j][mb][3];
+          const float h0 = g0 / (1.0f + expf(-g0)) * u0, h1 = g1 / (1.0f + expf(-g1)) * u1;
+          *reinterpret_cast<uint32_t*>(h + xoff(h, m, n >> 1, N >> 1, MB)) = pack_bf16x2(h0, h1);
+        } else {
+          float* o = out + (size_t)blockIdx.y * M * N;
+          *reinterpret_cast<float4*>(o + ((size_t)m * rep + c) * N + n) =
+              make_float4(acc[j][mb][0], acc[j][mb][1], acc[j][mb][2], acc[j][mb][3]);
+        }
       }
     }
-  }
+  } while (!SWI && ++c < rep);
 }
 
 // int4 weights (format in synth.hip: codes [N/16][K/128][64][4 words] in AWQ nibble order, then fp32
