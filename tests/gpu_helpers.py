@@ -55,7 +55,7 @@ TILE_ROWS = {
     "one split": ((65, 129, 257, 385), (65, 129, 257), (1, 640, 6, 2, 64, 384, 2064, 1e6)),
     "wide": ((65, 129, 257, 513), (65, 129, 257, 385), (1, 640, 6, 2, 64, 26368, 52736, 1e6)),
     "half as wide": ((385, 513), (513,), (1, 640, 6, 2, 64, 6656, 20480, 1e6)),
-    "wide residual": ((513,), (513,), (1, 13312, 6, 2, 64, 384, 2064, 1e6)),
+    "wide residual": ((385, 513), (129, 513), (1, 26624, 6, 2, 64, 384, 2064, 1e6)),
 }
 
 

@@ -61,7 +61,15 @@ def test_the_row_tests_reach_every_tile(routes, q4):
         assert (tile, "", True) in seen or (tile, ADD, True) in seen, tile
         assert (tile, SWIGLU, True) in seen, tile
     # the product added to the residual stream, at 128- and 256-row activation tiles
-    assert {t for t, what, ragged in seen if what == ADD and ragged} >= {"10x8", "16x8", "10x16"}
+    assert {t for t, what, ragged in seen if what == ADD and ragged} >= {"10x8", "16x8", "8x16", "10x16" if q4 else "20x16"}
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(256, 768, 256, "10x8"), (129, 1024, 256, "10x8"),
+                                        (256, 37888, 3584, "10x16"), (256, 27648, 5120, "8x16")])
+def test_short_k_takes_small_tiles(routes, M, N, K, tile):
+    assert routes.project(0, M, N, K, 1, 1, 0) == 1
+    t = re.search(r"k_gemm_ppILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", routes.last_kernel().decode())
+    assert TILE[",".join(t.groups())] == tile
 
 
 def test_a_plan_that_cannot_hold_the_matrix_is_refused(routes):
