@@ -312,7 +312,9 @@ rollout_status rollout_profile_decode_step(rollout_ctx* ctx, const int32_t* d_to
  * wave, in the launch mode the rollout uses: the step's projection launches
  * (per layer QKV, O, gate/up with SwiGLU, down; then the LM head, into
  * d_logits, fp32 [n_seqs, vocab]) are captured as one HIP graph and replayed
- * reps times between two HIP events on the context's stream.  Only the
+ * reps times between two HIP events on the context's stream.  (Where the
+ * rollout's O and down add to the residual stream, above 64 rows, they write
+ * to the workspace here.)  Only the
  * split-K workspace, the SwiGLU output and d_logits are written (the wave's
  * KV cache, residual stream and positions are untouched).  out: launches per
  * step, average microseconds per launch, algorithmic bytes (weights once,

@@ -672,11 +672,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 //
 // Bound: the matrix pipe and the softmax's vector instructions side by side (48 MFMAs of 32 cycles against
 // about 1,500 vector cycles per wave and tile), two waves per SIMD; the pipe is busy half of the time.  Why tiles:
-// one workgroup per token and KV head read the whole prefix again for every token.  Per layer, before -> now: 7B
-// width, one prompt of 3,967 tokens 2,940 -> 196 us (0.88 PFLOP/s of MFMA work); 8 x 512 tokens at 14B width
-// 797 -> 53 us; 8 x 256 at 7B width 173 -> 20 us; 4 x 512 at 72B width 485 -> 44 us; one prompt of 203 tokens
-// 23 -> 13 us.  The lazy maximum (kPreGrow) and the block addresses kept by the wave took the first from 224 to 196;
-// the next tile's scores computed beside this tile's exponentials (K a tile ahead of V) gained nothing (199).
+// one workgroup per token and KV head read the whole prefix again for every token.  Per layer, before -> now, in runs
+// long enough for the clock to have risen: 7B width, one prompt of 3,967 tokens 2,908 -> 171 us (1.0 PFLOP/s of MFMA
+// work); 8 x 512 tokens at 14B width 789 -> 52 us; 8 x 256 at 7B width 134 -> 17 us; 4 x 512 at 72B width 477 -> 42
+// us; one prompt of 203 tokens 22 -> 13 us.  (In a first few passes 196 to 201, 53 to 55, 20 and 44 to 47 us.)  The lazy
+// maximum (kPreGrow) and the block addresses kept by the wave took the first from 224 to 196 in such passes; the next
+// tile's scores computed beside this tile's exponentials (K a tile ahead of V) gained nothing (199).
 constexpr int kPreCols = 128, kPreKeys = 64;
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
