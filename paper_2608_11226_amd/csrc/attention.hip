@@ -1102,12 +1102,15 @@ static unsigned attn_grid(int R, const Dims& D, int parts = 1) { return (unsigne
 
 // Workgroups that a decode row's context may be shared out to (1: none), rows at positions up to last.
 // A pair's workgroup takes 1.6 us per round of its eight waves' tiles, alone on its CU; shared out, a pair costs the
-// merge kernel (4.6 us) more.  So rows at kAttnPartTokens (eight rounds) or more, in batches whose (row, KV head)
-// pairs leave half of the CUs idle, are shared out until the CUs are used.
-// 4 rows of 7B width (16 pairs), context 3,000, 16 parts:
-// prefix and suffix pass 40 + 9.6 us a layer, in parts 11.4 + 4.6; whole decode steps at contexts of 1,100, 2,000
-// and 3,000 tokens gain 3, 9 and 13-25%; at 300 the two forms are within 1 to 3% of each other either way.  (Parts of
-// eight waves: 14.3 us.)
+// merge kernel (4.6 us) more.  So rows at kAttnPartTokens or more, in batches whose (row, KV head)
+// pairs leave half of the CUs idle, are shared out until the CUs are used.  Steps of six layers, whole / in parts, us:
+//   7B width, 1 row     at 272 tokens 816 / 809, 400 831 / 812, 528 838 / 815, 784 853 / 811, 990 865 / 812
+//            16 rows                  859 / 861,     875 / 863,     889 / 873,     910 / 882,     923 / 889
+//            32 rows                  905 / 914,     920 / 922,     928 / 921,     965 / 951,     982 / 975
+//   14B width, 4 rows                 961 / 950,     972 / 950,     977 / 956,     999 / 962,   1,018 / 964
+//             16 rows                 987 / 994,   1,000 / 1,000, 1,010 / 1,014, 1,049 / 1,047, 1,072 / 1,057
+// Parts of 32 and 16 tokens take the same within 1%.  4 rows of 7B width (16 pairs) at 3,000 tokens, 16 parts: prefix
+// and suffix pass 40 + 9.6 us a layer, in parts 11.4 + 4.6 (parts of eight waves: 14.3 in place of 11.4).
 bool attn_few_rows(const Dims& D, int R) { return mfma_attention(D) && (int64_t)R * D.nkv <= 128; }
 int attn_parts(const Dims& D, int R, int last) {
   if (!attn_few_rows(D, R) || last < kAttnPartTokens) return 1;

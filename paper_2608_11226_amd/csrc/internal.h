@@ -140,7 +140,7 @@ hipError_t launch_attention(hipStream_t s, const Dims& D, const void* q, void* k
 // Rows of small decode batches (attn_few_rows) at positions of kAttnPartTokens or more have their context shared out
 // over up to attn_parts workgroups, for rows at positions up to last (opart and ml hold R x n_heads x parts).  How a
 // row is decoded depends on its own position and on the batch only.
-constexpr int kAttnPartTokens = 1024;
+constexpr int kAttnPartTokens = 384;
 bool attn_few_rows(const Dims& D, int R);
 int attn_parts(const Dims& D, int R, int last);
 // Decode attention with the group's shared prompt read once per group: a suffix pass over each row's own

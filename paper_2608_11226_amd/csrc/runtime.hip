@@ -908,20 +908,35 @@ rollout_status rollout_generate(rollout_ctx* ctx, const int32_t* d_prompts, int3
       }
       continue;
     }
-    // one graph for all steps, or two where a few rows' attention changes its launches on the way (kAttnPartTokens)
+    // One graph for all steps, or two where a few rows' attention changes its launches on the way (kAttnPartTokens).
+    // Both are captured here, while the prefill runs.
+    struct Replay {
+      hipGraphExec_t exec;
+      int steps;
+    };
+    std::vector<Replay> replays;
+    auto drop_from = [&](size_t i) {  // the executables not handed to ctx->retired
+      hipStreamSynchronize(ctx->stream);
+      for (; i < replays.size(); ++i) hipGraphExecDestroy(replays[i].exec);
+    };
     for (int t0 = 1, t1; t0 < N; t0 = t1) {
       const int at = prompt_len + t0 - 1;  // the rows' position at step t0
       t1 = attn_few_rows(D, Sw) && at < kAttnPartTokens ? std::min(N, t0 + kAttnPartTokens - at) : N;
       hipGraphExec_t exec = nullptr;
       r = capture_graph(ctx, [&] { return step(PosSpan{at, prompt_len + t1 - 2}); }, &exec);
-      if (r) return r;
+      if (r) {
+        drop_from(0);
+        return r;
+      }
+      replays.push_back({exec, t1 - t0});
+    }
+    for (size_t i = 0; i < replays.size(); ++i) {
       {
         Range replay("rollout_generate: decode steps (graph replay)");
-        for (int t = t0; t < t1; ++t) {
-          hipError_t le = hipGraphLaunch(exec, ctx->stream);
+        for (int t = 0; t < replays[i].steps; ++t) {
+          hipError_t le = hipGraphLaunch(replays[i].exec, ctx->stream);
           if (le != hipSuccess) {
-            hipStreamSynchronize(ctx->stream);
-            hipGraphExecDestroy(exec);
+            drop_from(i);
             return hip_fail(ctx, le, "graph launch");
           }
           ctx->cur_len += 1;
@@ -932,12 +947,11 @@ rollout_status rollout_generate(rollout_ctx* ctx, const int32_t* d_prompts, int3
       hipError_t ee = hipEventCreateWithFlags(&done, hipEventDisableTiming);
       if (ee == hipSuccess) ee = hipEventRecord(done, ctx->stream);
       if (ee != hipSuccess) {
-        hipStreamSynchronize(ctx->stream);
-        hipGraphExecDestroy(exec);
+        drop_from(i);
         if (done) hipEventDestroy(done);
         return hip_fail(ctx, ee, "wave event");
       }
-      ctx->retired.emplace_back(exec, done);
+      ctx->retired.emplace_back(replays[i].exec, done);
     }
   }
   return ROLLOUT_OK;
@@ -1088,8 +1102,8 @@ rollout_status rollout_generate_eos(rollout_ctx* ctx, const int32_t* d_prompts, 
     for (int i = 0; i < S && !r; ++i) r = admit_seq(i, 0);
   }
   if (r) return r;
-  // Graphs of a step, captured when first needed: of a few rows short of kAttnPartTokens, on both sides of it, and past
-  // it (their attention's launches); all other batches only the first.
+  // Graphs of a step: of a few rows short of kAttnPartTokens, on both sides of it, and past it (their attention's
+  // launches); all other batches only the first.
   hipGraphExec_t execs[3] = {nullptr, nullptr, nullptr};
   auto finish = [&](rollout_status st) {
     for (hipGraphExec_t& exec : execs) {
@@ -1114,22 +1128,30 @@ rollout_status rollout_generate_eos(rollout_ctx* ctx, const int32_t* d_prompts, 
     }
     return PosSpan{(int)lo, (int)std::min<int64_t>(hi, last)};
   };
+  auto form_of = [&](PosSpan pos) {
+    return !attn_few_rows(D, S) || pos.hi < kAttnPartTokens ? 0 : (pos.lo < kAttnPartTokens ? 1 : 2);
+  };
+  // the widest positions of a form in this call
+  const PosSpan spans[3] = {{P, attn_few_rows(D, S) ? std::min(last, kAttnPartTokens - 1) : last},
+                            {P, last},
+                            {std::max(P, kAttnPartTokens), last}};
+  if (!ctx->prof.on)  // those that can occur, while the first prefills run
+    for (int f = 0; f < 3; ++f)
+      if (spans[f].lo <= spans[f].hi && form_of(spans[f]) == f &&
+          (r = capture_graph(ctx, [&] { return step(spans[f]); }, &execs[f])))
+        return finish(r);
   auto live = [&]() {
     for (int i = 0; i < S; ++i)
       if (slot_seq[i] >= 0) return true;
     return false;
   };
   while (live()) {
-    PosSpan pos = positions();
-    const int form = !attn_few_rows(D, S) || pos.hi < kAttnPartTokens ? 0 : (pos.lo < kAttnPartTokens ? 1 : 2);
-    if (form > 0) pos = PosSpan{form == 1 ? P : std::max(P, kAttnPartTokens), last};  // of every step that has this form
-    if (!ctx->prof.on && !execs[form] && (r = capture_graph(ctx, [&] { return step(pos); }, &execs[form])))
-      return finish(r);
+    const int form = form_of(positions());
     for (int i = 0; i < refill_interval; ++i) {
       if (execs[form]) {
         hipError_t le = hipGraphLaunch(execs[form], ctx->stream);
         if (le != hipSuccess) return finish(hip_fail(ctx, le, "graph launch"));
-      } else if ((r = step(pos))) {
+      } else if ((r = step(spans[form]))) {
         return finish(r);
       }
     }

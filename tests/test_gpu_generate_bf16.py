@@ -97,9 +97,9 @@ def test_small_bf16_generate_equals_the_eager_chain(seqs, shared, waves, monkeyp
     eng.close()
 
 
-# contexts that stay below 1,024 tokens, that cross them (where the decode attention of a few rows begins to share
+# contexts that stay below 384 tokens, that cross them (where the decode attention of a few rows begins to share
 # a row out), and a group whose prompt is long enough for the shared-prefix pass
-@pytest.mark.parametrize("P,G", [(40, 4), (1010, 4), (600, 16)])
+@pytest.mark.parametrize("P,G", [(40, 4), (370, 4), (600, 16)])
 def test_decode_does_not_depend_on_the_capacity_of_the_context(P, G, monkeypatch):
     _set_knobs(monkeypatch, None, None)
     N, T, top_p = 24, 0.9, 0.95
@@ -131,11 +131,11 @@ def test_decode_does_not_depend_on_the_capacity_of_the_context(P, G, monkeypatch
 
 
 def test_rows_on_both_sides_of_the_shared_out_attention(monkeypatch):
-    """Slots that hold completions of different lengths, some short of 1,024 tokens and some past them: every
+    """Slots that hold completions of different lengths, some short of 384 tokens and some past them: every
     completion has the tokens of rollout_generate, cut at its stop token."""
     _set_knobs(monkeypatch, None, None)
-    n_prompts, P, G, N, T, top_p = 3, 1010, 4, 24, 0.9, 0.95
-    log(f"bf16 continuous batching across 1,024 tokens: {n_prompts} prompts x {P}, G={G}, N={N}")
+    n_prompts, P, G, N, T, top_p = 3, 370, 4, 24, 0.9, 0.95
+    log(f"bf16 continuous batching across 384 tokens: {n_prompts} prompts x {P}, G={G}, N={N}")
     cfg = R.model_config(SMALL_BF16, R.DTYPE_BF16, P, N, G + 1)
     eng = R.Engine(cfg)
     prompts = W.prompts(n_prompts, P, cfg.vocab, seed=47)
@@ -143,7 +143,7 @@ def test_rows_on_both_sides_of_the_shared_out_attention(monkeypatch):
     want = _graph(eng, prompts, G, G, N, T, top_p, u)
     stop = np.arange(cfg.vocab // 16, dtype=np.int32)
     ends = [int(np.argmax(np.append(row[:-1] < len(stop), True))) + 1 for row in want]
-    assert len(set(ends)) > 3 and max(ends) > 16  # slots are refilled apart, and some rows pass 1,024 tokens
+    assert len(set(ends)) > 3 and max(ends) > 16  # slots are refilled apart, and some rows pass 384 tokens
     got = torch.full((n_prompts * G, N), -7, dtype=torch.int32, device="cuda:0")
     lengths = torch.zeros(n_prompts * G, dtype=torch.int32, device="cuda:0")
     R.rollout_generate_eos(eng.ctx, to_dev(prompts, torch), n_prompts, P, G, G, N, T, top_p, to_dev(u, torch),

@@ -420,12 +420,12 @@ def test_bf16_tile_gemm_rows(name):
     eng.close()
 
 
-# decode rows whose context is shared out over workgroups (calls that may reach 1,024 tokens on few rows): early
-# positions leave most parts empty, parts of one tile, several tiles a wave, one and seven column groups, 32 parts
+# decode rows whose context is shared out over workgroups (from position 384 on in small batches): the step that
+# begins to, a last part of one token, 5 to 16 parts of one tile a wave and more, one and seven column groups
 PARTS_ATTN = [
     # (model shape, block size, prompts, G, prompt length)
-    ((1, 256, 14, 2, 128, 256, 2048, 1e6), 16, 1, 2, 5), ((1, 256, 14, 2, 128, 256, 2048, 1e6), 8, 3, 1, 513),
-    ((1, 256, 4, 1, 64, 256, 2048, 1e6), 32, 1, 3, 33), ((1, 256, 4, 1, 128, 256, 2048, 1e6), 16, 2, 2, 1027),
+    ((1, 256, 14, 2, 128, 256, 2048, 1e6), 16, 1, 2, 382), ((1, 256, 14, 2, 128, 256, 2048, 1e6), 8, 3, 1, 513),
+    ((1, 256, 4, 1, 64, 256, 2048, 1e6), 32, 1, 3, 385), ((1, 256, 4, 1, 128, 256, 2048, 1e6), 16, 2, 2, 1027),
 ]
 
 
@@ -434,7 +434,7 @@ def test_bf16_decode_attention_parts(shape, blk, n_prompts, G, P, monkeypatch):
     set_attn_knobs(monkeypatch, "1", None)
     log(f"bf16 decode attention in parts shape={shape} blk={blk} prompts={n_prompts} G={G} P={P}")
     S, N = n_prompts * G, 4
-    cfg = R.model_config(shape, R.DTYPE_BF16, P, max(N, 1030 - P), S, kv_block_size=blk)
+    cfg = R.model_config(shape, R.DTYPE_BF16, P, N, S, kv_block_size=blk)
     eng = R.Engine(cfg)
     model = OracleModel(shape_of(cfg), mode="bf16")
     prompts = W.prompts(n_prompts, P, cfg.vocab, seed=61)
