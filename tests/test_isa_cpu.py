@@ -1,8 +1,9 @@
 """Direct loads into LDS in the compiled kernels: the wait state after M0 and M0 as a clobber.
 
 ``global_load_lds`` takes its LDS address from M0, and on gfx950 a scalar write of M0 needs one wait state (any
-instruction, or ``s_nop 0``) before it.  The compiler inserts that for its own builtin but does not look inside inline
-assembly, which is how the kernels issue these loads, so the built code is checked instruction by instruction."""
+instruction, or ``s_nop 0``) before it; a scalar register that a vector instruction wrote needs five.  The compiler
+inserts these for its own builtin but does not look inside inline assembly, which is how the kernels issue these loads,
+so the built code is checked instruction by instruction."""
 import os
 import re
 import subprocess
@@ -24,9 +25,21 @@ def _instructions(text):
 
 
 def _loads_without_wait_state(ins):
-    """(direct loads into LDS, those that come directly behind a write of M0)"""
+    """(direct loads into LDS, writes of M0 or of their base registers that stand too close before them)"""
     at = [i for i, s in enumerate(ins) if s.startswith(("global_load_lds", "buffer_load")) and "lds" in s]
-    return len(at), [ins[i - 1] for i in at if re.match(r"\w+ m0,", ins[i - 1])]
+    bad = [ins[i - 1] for i in at if re.match(r"\w+ m0,", ins[i - 1])]
+    for i in at:
+        base = re.search(r"s\[(\d+):(\d+)\]", ins[i])
+        regs = ["m0"] + ([f"s{r}" for r in range(int(base[1]), int(base[2]) + 1)] if base else [])
+        states = 0
+        for s in reversed(ins[max(0, i - 5):i]):
+            if states >= 5:
+                break
+            if re.match(rf"v_\w+ ({'|'.join(regs)}),", s):
+                bad.append(s)
+            nop = re.match(r"s_nop (\d+)", s)
+            states += int(nop[1]) + 1 if nop else 1
+    return len(at), bad
 
 
 def test_every_direct_load_into_lds_has_its_wait_state(tmp_path):
@@ -41,7 +54,7 @@ def test_every_direct_load_into_lds_has_its_wait_state(tmp_path):
         loads += n
         bad += b
     assert loads > 0, "no direct load into LDS found: the check looks at the wrong code"
-    assert not bad, f"{len(bad)} of {loads} loads follow a write of M0 directly, e.g. {bad[0]}"
+    assert not bad, f"{len(bad)} writes stand too close before {loads} loads, e.g. {bad[0]}"
 
 
 # Two direct loads to one LDS address by the compiler's builtin, with a helper's load elsewhere between them: the
