@@ -403,6 +403,27 @@ def test_bf16_prefill_every_token(heads, nkv, hd, blk, P):
     log(f"  worst token {worst:.3g} of its norm")
 
 
+# the LM head after a prefill stores a prompt's row for every member that is not a copy in its operand: 40 rows three
+# times, one row 67 times, 70 rows (more than 64) twice, 8 prompts of 7 members copied as far as 64 rows go
+@pytest.mark.parametrize("dtype,mode,shape,tol", [(R.DTYPE_FP32, "fp32", "tiny", 1e-4), (R.DTYPE_BF16, "bf16", SMALL_BF16, 3e-2)])
+@pytest.mark.parametrize("n_prompts,G", [(40, 3), (1, 67), (70, 2), (8, 7)])
+def test_prefill_logits_of_every_member(n_prompts, G, dtype, mode, shape, tol):
+    log(f"prefill logits of every member: {mode}, {n_prompts} prompts, G={G}")
+    P = 3
+    cfg = R.model_config(shape, dtype, P, 1, n_prompts * G)
+    eng = R.Engine(cfg, group_size=G)
+    model = OracleModel(shape_of(cfg), mode=mode)
+    prompts = W.prompts(n_prompts, P, cfg.vocab, seed=67)
+    want = np.stack([model.prefill(p)[1] for p in prompts])
+    logits = torch.full((n_prompts, G, cfg.vocab), float("nan"), dtype=torch.float32, device="cuda:0")
+    R.rollout_prefill(eng.ctx, to_dev(prompts, torch), n_prompts, P, G, logits)
+    eng.synchronize()
+    eng.close()
+    got = logits.cpu().numpy()
+    assert np.max(np.abs(got - want[:, None])) <= tol
+    assert np.array_equal(got, np.repeat(got[:, :1], G, axis=1))  # rows of a group are equal
+
+
 @pytest.mark.parametrize("name", [n for n, t in TILE_ROWS.items() if t[0]])
 def test_bf16_tile_gemm_rows(name):
     rows, _, shape = TILE_ROWS[name]
